@@ -214,8 +214,9 @@ int sparse_decode_attn(const scout_problem* p, const void* q, const void* k_pool
  *     nothing.  They take about  B * Hkv * nsplit * G * (d + 2) * 4  bytes, where
  *     nsplit is the number of workgroups the library spreads a pair over: about
  *     256 / (B * Hkv) for bf16 with d = 128 (none at all from 192 pairs on, where
- *     a workgroup finishes its pair), at most 64.  All five benchmark
- *     configurations need at most 1.1 MiB.
+ *     a workgroup finishes its pair), at most 64; fp32 and d = 64 are sized as
+ *     min(k, 4096 / (B * Hkv * ceil(G / 4))) splits, at most 64, whatever runs.
+ *     All five benchmark configurations need at most 1.1 MiB.
  *   - The buffer's device address is looked up on the first call on each device
  *     (hipGetSymbolAddress); make that first call outside a graph capture.
  *   - Every call on a GPU uses that GPU's one buffer, which keeps the last
@@ -361,9 +362,10 @@ int scout_layer_step(const scout_problem* p, const void* q, const void* digest,
 
 /*
  * Tuning knob for measurements: force the attention kernel family, the split
- * count per pair and the workgroup size.  family: 0 = automatic, 1 = generic
- * vector-ALU kernel, 2 = MFMA kernel (bf16 and d = 128 only; otherwise
- * SCOUT_EUNSUPPORTED at the call), 3 = as 2, but scout_layer_step launches the
+ * count per pair and the workgroup size.  family: 0 = automatic (the matrix
+ * cores, for every type and head dim), 1 = generic
+ * vector-ALU kernel, 2 = MFMA kernel (can be forced for bf16 and d = 128 only;
+ * otherwise SCOUT_EUNSUPPORTED at the call), 3 = as 2, but scout_layer_step launches the
  * scoring and the selection on their own instead of inside the attention kernel,
  * 4 = as 2, but only the scoring on its own.
  * nsplit: 0 = automatic, else 1..64.

@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -21,16 +23,25 @@ FLAGS = [
 CALIB_LIB = os.path.join(HERE, "libscout_calib.so")
 
 
-def _hipcc(sources, out, verbose):
-    cmd = ["hipcc", *FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           *[os.path.join(CSRC, s) for s in sources], "-o", out]
+def _run(cmd, verbose):
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(ln for ln in res.stderr.splitlines() if noise not in ln)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + err)
     if verbose and err.strip():
         print(err)
+
+
+def _hipcc(sources, out, verbose):
+    """Every source to an object of its own (in parallel: the kernels share no device symbols), then one link."""
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(max_workers=4) as pool:
+        objs = [os.path.join(tmp, s + ".o") for s in sources]
+        compile_flags = [f for f in FLAGS if f != "-shared"]
+        list(pool.map(lambda so: _run(["hipcc", *compile_flags, *inc, "-c", os.path.join(CSRC, so[0]), "-o", so[1]], verbose),
+                      zip(sources, objs)))
+        _run(["hipcc", "--offload-arch=gfx950", "-fPIC", "-shared", *objs, "-o", out], verbose)
     return out
 
 

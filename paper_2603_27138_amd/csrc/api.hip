@@ -21,12 +21,11 @@ int launch_topk(const Dims&, const float*, const int32_t*, int32_t*, int32_t*, i
                 int32_t*, int32_t*, hipStream_t);
 int launch_recall(const Dims&, const float*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
                   hipStream_t);
-bool mfma_supported(const Dims&, int);
 int launch_attn(const Dims&, int, int, int, const void*, const void*, const void*, long long,
                 const int32_t*, const int32_t*, const int32_t*, Partials, Epilogue, hipStream_t);
 int launch_combine(const Dims&, Partials, Epilogue, hipStream_t);
-bool select_attend_supported(const Dims&, int);
-int launch_select_attend(const Dims&, const void*, const float*, const int32_t*, const void*, const void*,
+bool select_attend_supported(const Dims&);
+int launch_select_attend(const Dims&, int, const void*, const float*, const int32_t*, const void*, const void*,
                          long long, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, Partials,
                          Epilogue, hipStream_t);
 bool step_kernel_supported(const Dims&, int);
@@ -134,10 +133,22 @@ struct AttnPlan {
   int family, nsplit, waves;
 };
 
+// Splits per pair of the vector-ALU family (one wave per pair, split and four heads): enough waves to fill the chip.
+static int valu_splits(const Dims& D) {
+  const long long pairs = (long long)D.B * D.Hkv, chunks = (D.G + kValuHeadsPerWave - 1) / kValuHeadsPerWave;
+  const long long want = (4096 + pairs * chunks - 1) / (pairs > 0 ? pairs * chunks : 1);
+  const long long ns = want > D.k ? D.k : want;
+  return ns > kMaxSplit ? kMaxSplit : (int)ns;
+}
+
 static int plan_attn(const Dims& D, int dtype, AttnPlan* out) {
   int fam = g_family;
-  if (fam == 0) fam = mfma_supported(D, dtype) ? 2 : 1;
-  if (fam == 2 && !mfma_supported(D, dtype)) return SCOUT_EUNSUPPORTED;
+  if (fam == 2 && (dtype != SCOUT_BF16 || D.d != 128)) return SCOUT_EUNSUPPORTED;  // forcing it is for the shapes it was tuned on
+  // The matrix cores serve every type and head dim.  With the vector-ALU family, bf16 with d = 64 (8 sequences x 8 KV
+  // heads, 128 blocks of 16 tokens) took 18.0 us for the attention and 15.2 us for folding its 64 splits, and the
+  // selection could not ride in its head (6.6 us more); with the matrix cores selection and attention take 13.2 us
+  // and the fold of 4 splits 3.9 us.  fp32, d = 128, 2 sequences of 64k tokens: 63.5 against 115 us for the same pass.
+  if (fam == 0) fam = 2;
   const long long pairs = (long long)D.B * D.Hkv;
   int ns = g_nsplit, waves = 1;
   if (fam == 2) {
@@ -156,9 +167,7 @@ static int plan_attn(const Dims& D, int dtype, AttnPlan* out) {
       }
     }
   } else if (ns == 0) {
-    const long long chunks = (D.G + kValuHeadsPerWave - 1) / kValuHeadsPerWave;
-    long long want = (4096 + pairs * chunks - 1) / (pairs > 0 ? pairs * chunks : 1);
-    ns = (int)(want > D.k ? D.k : want);
+    ns = valu_splits(D);
   }
   if (ns < 1) ns = 1;
   if (ns > kMaxSplit) ns = kMaxSplit;
@@ -426,10 +435,15 @@ int sparse_decode_attn_static(const scout_problem* p, const void* q, const void*
   E.m = m;
   E.l = l;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  size_t off_m, off_l;
+  // fp32 and d = 64 problems are sized by the vector-ALU family's splits, whichever family serves them: what fits the
+  // buffer and what is refused does not depend on the kernel that happens to run
+  if (g_family == 0 && g_nsplit == 0 && (p->dtype != SCOUT_BF16 || D.d != 128) &&
+      static_layout(D, AttnPlan{1, valu_splits(D), 1}, &off_m, &off_l) > (size_t)SCOUT_STATIC_SCRATCH_BYTES)
+    return SCOUT_ESCRATCH;
   if (A.family == 2 && A.nsplit == 1)  // one workgroup per pair finishes the pair itself: no scratch at all
     return launch_attn(D, p->dtype, 2, A.waves, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu,
                        Partials{nullptr, nullptr, nullptr, 1, waves_magic(A)}, E, st);
-  size_t off_m, off_l;
   if (static_layout(D, A, &off_m, &off_l) > (size_t)SCOUT_STATIC_SCRATCH_BYTES) return SCOUT_ESCRATCH;
   char* base = static_cast<char*>(static_scratch(&rc));
   if (base == nullptr) return rc;
@@ -541,15 +555,15 @@ int scout_layer_step(const scout_problem* p, const void* q, const void* digest,
   if (scores == nullptr) scores = reinterpret_cast<float*>(static_cast<char*>(ws) + L.scores);
   rc = launch_score(D, p->dtype, q, digest, scores, st);
   if (rc != SCOUT_OK) return rc;
-  if (g_fuse_select && A.family == 2 && A.waves == 8 && select_attend_supported(D, p->dtype)) {
+  if (g_fuse_select && A.family == 2 && A.waves == 8 && select_attend_supported(D)) {
     // selection rides in the head of the attention kernel: two launches for the whole step
     Partials P = carve(ws, L, A);
     if (A.nsplit == 1)
-      return launch_select_attend(D, q, scores, block_table, k_pool, v_pool, n_slots, sel_all, sel_gpu,
+      return launch_select_attend(D, p->dtype, q, scores, block_table, k_pool, v_pool, n_slots, sel_all, sel_gpu,
                                   slot_gpu, n_gpu, sel_host, n_host, P, E, st);
     Epilogue part{};
     part.mode = 0;
-    rc = launch_select_attend(D, q, scores, block_table, k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu,
+    rc = launch_select_attend(D, p->dtype, q, scores, block_table, k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu,
                               n_gpu, sel_host, n_host, P, part, st);
     if (rc != SCOUT_OK) return rc;
     return launch_combine(D, P, E, st);

@@ -11,12 +11,12 @@
 // exponentials are bare v_exp_f32; m is converted back to natural-log units
 // where it leaves the library.
 //
-// Two kernel families write the same per-split partials into the workspace:
-//   attn_mfma_kernel  bf16, d = 128: the G query heads of a KV head form one MFMA
-//                     operand, K and V rows go from HBM straight into MFMA operand
+// Two kernel families write the same per-split partials into the workspace, both for every supported
+// (dtype, d, S):
+//   attn_mfma_kernel  the G query heads of a KV head form one MFMA operand (bf16, or fp32 on the fp32
+//                     matrix instructions), K and V rows go from HBM straight into MFMA operand
 //                     registers (no LDS), in units of 16 tokens.
-//   attn_valu_kernel  any supported (dtype, d, S): plain vector ALU, used for
-//                     fp32 and the other shapes.
+//   attn_valu_kernel  plain vector ALU; only where the caller asks for it (scout_set_attn_mode).
 // combine_kernel folds the splits (and optionally the host partial) together.
 #include "select.h"
 
@@ -52,8 +52,6 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float x, float y) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){x, y}, bf16x2));
 }
-
-constexpr int kMfmaD = 128;
 
 // The host's partial for one output element (mode 2 only); loaded ahead of the point of use so
 // that its latency hides behind the fold.
@@ -103,33 +101,57 @@ __device__ __forceinline__ void finish(const Dims& D, const Epilogue& E, int bh,
 }
 
 // The work of a pair is cut into units of 16 tokens (a block of S tokens is S/16 units; a unit's K
-// rows and V rows are 4 KiB each, contiguous).  The pair's units are dealt to the waves that share
+// rows and V rows are contiguous, 4 KiB each at bf16, d = 128).  The pair's units are dealt to the waves that share
 // the pair (all waves of all its workgroups) in contiguous ranges whose lengths differ by at most
 // one, so no wave waits for a neighbour that got a whole block more.  For each unit:
-//   logits^T[token][head] = K[token][:] . Q[head][:]            4 x mfma 16x16x32
+//   logits^T[token][head] = K[token][:] . Q[head][:]            bf16: d/32 x mfma 16x16x32, fp32: d/4 x mfma 16x16x4
 //   online softmax per head (heads live in lane % 16)
-//   out^T[dim][head]    += V^T[dim][token] . P^T[token][head]   8 x mfma 16x16x16
+//   out^T[dim][head]    += V^T[dim][token] . P^T[token][head]   bf16: d/16 x mfma 16x16x16, fp32: d/4 x mfma 16x16x4
 // Operand layout of the 16x16 MFMAs: lane L supplies, for A, row L%16 and for B, column L%16, the
-// contraction elements of group L/16 (8 of them for x32, 4 for x16); the result has column L%16 and
+// contraction elements of group L/16 (8 of them for x32, 4 for x16, 1 for x4); the result has column L%16 and
 // rows 4*(L/16)+i.  The contraction index may be labelled freely as long as A and B agree, which
 // lets the logits leave the first product in exactly the registers the second one needs: lane L
 // ends up with the logits of head L%16 for tokens 4*(L/16) + i (i = 0..3), so the value rows are
-// loaded in that same token order.  Element r of a lane's 16-byte value chunk feeds product r, whose
-// output row index then means channel 8*row + r.
+// loaded in that same token order.  Element e of a lane's value chunk c feeds product r = c * CPC + e, whose
+// output row index R then means channel CPC * (R + 16 * c) + e.
+//
+// fp32 goes through the fp32 matrix instructions (products and sums in binary32, as on the vector ALU,
+// and the softmax weights are not rounded): 2048 matrix cycles per unit of 16 KiB at d = 128 are 8 bytes
+// per cycle and SIMD, 2.5 times what HBM delivers, so the pass stays bandwidth-bound.
 //
 // The waves of a workgroup fold their partials through LDS; with one split per pair the workgroup
 // finishes the pair itself (Epilogue modes 1 and 2), so the whole attention is one launch and
 // nothing goes through the workspace.
 
 constexpr int kUnitTokens = 16;
-constexpr int kUnitBytes = kUnitTokens * kMfmaD * 2;  // of K, and of V
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
-// K and V rows of one unit in MFMA operand registers (32 VGPRs).
+// How a unit of (element type DT, head dim DH) lies in the lanes.
+template <int DT, int DH>
+struct Tile {
+  static constexpr int ES = DT == SCOUT_BF16 ? 2 : 4;  // bytes per element
+  static constexpr int ROWB = DH * ES;                 // bytes per token row
+  static constexpr int UNITB = kUnitTokens * ROWB;     // bytes of K, and of V, per unit
+  static constexpr int KL = ROWB / 64;                 // 16-byte K loads per lane: chunk 4 * s + kg of row ln
+  static constexpr int CB = ROWB / 16 < 16 ? ROWB / 16 : 16;  // bytes of a lane's value chunk
+  static constexpr int VC = ROWB / 16 / CB;            // value chunks per lane and row: chunk ln + 16 * c
+  static constexpr int CPC = CB / ES;                  // channels per value chunk
+  static constexpr int NR = DH / 16;                   // products (accumulator tiles) of the second contraction
+  // channel of accumulator tile r, row index R
+  static __device__ __forceinline__ constexpr int channel(int r, int R) { return CPC * (R + 16 * (r / CPC)) + r % CPC; }
+};
+
+// The group's queries as operand registers: 16-byte chunk 4 * s + kg of head ln.
+template <int DT, int DH>
+using QRegs = u32x4[Tile<DT, DH>::KL];
+
+// K and V rows of one unit in MFMA operand registers.
+template <int DT, int DH>
 struct UnitRegs {
-  u32x4 k[4];  // contraction step s: row = token ln, 16-byte chunk 4*s + kg
-  u32x4 v[4];  // row = token 4*kg + i, 16-byte chunk ln
+  u32x4 k[Tile<DT, DH>::KL];     // contraction step s: row = token ln, 16-byte chunk 4*s + kg
+  u32x4 v[4][Tile<DT, DH>::VC];  // row = token 4*kg + i, chunk ln + 16*c (8-byte chunks use half the register)
 };
 
 // One unit, checked: where it starts in the pools (element offset) and how many of its tokens
@@ -140,6 +162,7 @@ struct Entry {
 };
 
 // sel / slot_list point at the pair's list (global memory or LDS); u is wave-uniform.
+template <int DH>
 __device__ __forceinline__ Entry read_entry(const int32_t* sel, const int32_t* slot_list, int u, int u_end,
                                             int ush, int S, int ctx, long long n_slots, int tile_stride) {
   Entry e{0, 0};
@@ -150,7 +173,7 @@ __device__ __forceinline__ Entry read_entry(const int32_t* sel, const int32_t* s
     int valid = ctx - j * S - sub * kUnitTokens;
     valid = valid > kUnitTokens ? kUnitTokens : valid;
     if (j >= 0 && valid > 0 && slot >= 0 && slot < n_slots) {
-      e.elem_off = (size_t)slot * tile_stride + sub * kUnitTokens * kMfmaD;
+      e.elem_off = (size_t)slot * tile_stride + sub * kUnitTokens * DH;
       e.valid = valid;
     }
   }
@@ -161,38 +184,59 @@ __device__ __forceinline__ Entry read_entry(const int32_t* sel, const int32_t* s
 // when the entry is void: then every lane gets zeros without touching memory.  That keeps the issue
 // path free of branches, so the compiler can count outstanding loads exactly and a wave can wait for
 // one unit while the next ones are still in flight.
-__device__ __forceinline__ void issue_unit(UnitRegs& T, const uint16_t* __restrict__ k_pool,
-                                           const uint16_t* __restrict__ v_pool, const Entry& e, int ln,
-                                           int kg) {
-  const int bytes = e.valid > 0 ? kUnitBytes : 0;
-  const __amdgpu_buffer_rsrc_t kr =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(k_pool + e.elem_off), 0, bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t vr =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(v_pool + e.elem_off), 0, bytes, 0x00020000);
-  const int koff = ln * 256 + kg * 16;   // row ln, 16-byte chunk 4*s + kg
-  const int voff = kg * 1024 + ln * 16;  // row 4*kg + i, chunk ln
+template <int DT, int DH>
+__device__ __forceinline__ void issue_unit(UnitRegs<DT, DH>& T, const void* __restrict__ k_pool,
+                                           const void* __restrict__ v_pool, const Entry& e, int ln, int kg) {
+  using L = Tile<DT, DH>;
+  const int bytes = e.valid > 0 ? L::UNITB : 0;
+  char* kp = static_cast<char*>(const_cast<void*>(k_pool)) + e.elem_off * L::ES;
+  char* vp = static_cast<char*>(const_cast<void*>(v_pool)) + e.elem_off * L::ES;
+  const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(kp, 0, bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(vp, 0, bytes, 0x00020000);
+  const int koff = ln * L::ROWB + kg * 16;           // row ln, 16-byte chunk 4*s + kg
+  const int voff = kg * 4 * L::ROWB + ln * L::CB;    // row 4*kg + i, chunk ln + 16*c
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
+  for (int s = 0; s < L::KL; ++s)
     T.k[s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, koff + s * 64, 0, 0));
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    T.v[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(vr, voff + i * 256, 0, 0));
+#pragma unroll
+    for (int c = 0; c < L::VC; ++c) {
+      const int off = voff + i * L::ROWB + c * 16 * L::CB;
+      if constexpr (L::CB == 16) {
+        T.v[i][c] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(vr, off, 0, 0));
+      } else {
+        const u32x2 w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(vr, off, 0, 0));
+        T.v[i][c][0] = w[0];
+        T.v[i][c][1] = w[1];
+      }
+    }
 }
 
-// Online-softmax state of one wave: head ln, channels 8*(4*kg + i) + r in acc[r][i].
+// Online-softmax state of one wave: head ln, channel Tile::channel(r, 4*kg + i) in acc[r][i].
+template <int NR>
 struct WaveState {
-  f32x4 acc[8];
+  f32x4 acc[NR];
   float m, l;
 };
 
 // Fold one unit into the wave's state.  `valid` tokens of the unit count (0: the unit is void and
 // leaves the state as it is), so this too runs without a data-dependent branch around loads.
-__device__ __forceinline__ void consume_unit(WaveState& W, UnitRegs& T, const u32x4 (&qreg)[4], int valid,
-                                             float scale2, int kg) {
+template <int DT, int DH>
+__device__ __forceinline__ void consume_unit(WaveState<DH / 16>& W, UnitRegs<DT, DH>& T,
+                                             const QRegs<DT, DH>& qreg, int valid, float scale2, int kg) {
+  using L = Tile<DT, DH>;
   f32x4 st = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
-    st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(T.k[s]), as_bf16x8(qreg[s]), st, 0, 0, 0);
+  for (int s = 0; s < L::KL; ++s) {
+    if constexpr (DT == SCOUT_BF16) {
+      st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(T.k[s]), as_bf16x8(qreg[s]), st, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        st = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(T.k[s][e]), __uint_as_float(qreg[s][e]), st, 0, 0, 0);
+    }
+  }
   // st[i] = logit of head ln, token 4*kg + i
   float x[4];
 #pragma unroll
@@ -203,7 +247,8 @@ __device__ __forceinline__ void consume_unit(WaveState& W, UnitRegs& T, const u3
     for (int i = 0; i < 4; ++i) {
       if (4 * kg + i >= valid) {
         x[i] = -INFINITY;
-        T.v[i] = (u32x4){0, 0, 0, 0};
+#pragma unroll
+        for (int c = 0; c < L::VC; ++c) T.v[i][c] = (u32x4){0, 0, 0, 0};
       }
     }
   }
@@ -218,34 +263,50 @@ __device__ __forceinline__ void consume_unit(WaveState& W, UnitRegs& T, const u3
     const float alpha = exp2_diff(W.m, m_new);
     W.l *= alpha;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) W.acc[r] *= alpha;
+    for (int r = 0; r < L::NR; ++r) W.acc[r] *= alpha;
     W.m = m_new;
   }
-  // weights go into the second product as bf16; sum what is actually used
-  const uint32_t p01 = cvt_pk_bf16(p[0], p[1]), p23 = cvt_pk_bf16(p[2], p[3]);
-  W.l += (bf16_lo(p01) + bf16_hi(p01)) + (bf16_lo(p23) + bf16_hi(p23));
-  const s16x4 preg = __builtin_bit_cast(s16x4, (uint2){p01, p23});
+  if constexpr (DT == SCOUT_BF16) {
+    // weights go into the second product as bf16; sum what is actually used
+    const uint32_t p01 = cvt_pk_bf16(p[0], p[1]), p23 = cvt_pk_bf16(p[2], p[3]);
+    W.l += (bf16_lo(p01) + bf16_hi(p01)) + (bf16_lo(p23) + bf16_hi(p23));
+    const s16x4 preg = __builtin_bit_cast(s16x4, (uint2){p01, p23});
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const uint32_t a01 = pack_halves(T.v[0][r >> 1], T.v[1][r >> 1], r & 1);
-    const uint32_t a23 = pack_halves(T.v[2][r >> 1], T.v[3][r >> 1], r & 1);
-    W.acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, (uint2){a01, a23}), preg,
-                                                         W.acc[r], 0, 0, 0);
+    for (int r = 0; r < L::NR; ++r) {
+      const uint32_t a01 = pack_halves(T.v[0][0][r >> 1], T.v[1][0][r >> 1], r & 1);
+      const uint32_t a23 = pack_halves(T.v[2][0][r >> 1], T.v[3][0][r >> 1], r & 1);
+      W.acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, (uint2){a01, a23}), preg,
+                                                           W.acc[r], 0, 0, 0);
+    }
+  } else {
+    W.l += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < L::NR; ++r)
+        W.acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(T.v[i][r / 4][r % 4]), p[i], W.acc[r], 0, 0, 0);
   }
 }
 
 // B operand of the first product: Q^T, column = head ln, zero beyond G
-__device__ __forceinline__ void load_q(u32x4 (&qreg)[4], const Dims& D, const uint16_t* __restrict__ q, int b,
+template <int DT, int DH>
+__device__ __forceinline__ void load_q(QRegs<DT, DH>& qreg, const Dims& D, const void* __restrict__ q, int b,
                                        int g, int ln, int kg) {
+  using L = Tile<DT, DH>;
   const int G = D.G;
   const int hsafe = ln < G ? ln : G - 1;
-  const uint16_t* qrow = q + ((size_t)b * D.Hq + g * G + hsafe) * kMfmaD + kg * 8;
+  const char* qrow = static_cast<const char*>(q) + ((size_t)b * D.Hq + g * G + hsafe) * L::ROWB + kg * 16;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) qreg[s] = *reinterpret_cast<const u32x4*>(qrow + s * 32);
+  for (int s = 0; s < L::KL; ++s) qreg[s] = *reinterpret_cast<const u32x4*>(qrow + s * 64);
   const uint32_t keep = ln < G ? 0xffffffffu : 0u;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) qreg[s] &= keep;
+  for (int s = 0; s < L::KL; ++s) qreg[s] &= keep;
 }
+
+// Units in flight per wave: one where a unit is 4 KiB or more of K and of V each; two of the 2 KiB units of
+// bf16 with d = 64, which ask for as many bytes.
+template <int DT, int DH>
+constexpr int unit_depth() { return Tile<DT, DH>::UNITB >= 4096 ? 1 : 2; }
 
 // The attention of one workgroup: its share (split) of the pair's list, folded over the waves
 // through LDS, then the epilogue.  sel / slot_list: the pair's list in global memory or LDS.
@@ -253,15 +314,17 @@ __device__ __forceinline__ void load_q(u32x4 (&qreg)[4], const Dims& D, const ui
 // j-th unit, units dealt to the pair's waves in stride: v, v + waves, ...), fetched by the wave
 // itself in the same trip as the count: no staging through LDS and no barrier before the first tile
 // request.  At most 64 units per wave; sel / slot_list are not read.
-template <int WAVES, int DEPTH, bool PRIVATE = false>
-__device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int split, const u32x4 (&qreg)[4],
-                                            const uint16_t* __restrict__ k_pool,
-                                            const uint16_t* __restrict__ v_pool, long long n_slots,
+template <int DT, int DH, int WAVES, int DEPTH, bool PRIVATE = false>
+__device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int split,
+                                            const QRegs<DT, DH>& qreg,
+                                            const void* __restrict__ k_pool,
+                                            const void* __restrict__ v_pool, long long n_slots,
                                             const int32_t* sel, const int32_t* slot_list, int n, int ctx,
                                             const Partials& P, const Epilogue& E, float* smem, int my_sel = -1,
                                             int my_slot = -1) {
-  // per wave: [G][132] floats of o (padded rows), then m[16], l[16]
-  constexpr int ROW = kMfmaD + 4;
+  // per wave: [G][DH + 4] floats of o (padded rows), then m[16], l[16]
+  using L = Tile<DT, DH>;
+  constexpr int ROW = DH + 4;
   const int pair = b * D.Hkv + g;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -286,9 +349,9 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   const int u0 = v * per + (v < extra ? v : extra);
   const int u1 = u0 + per + (v < extra ? 1 : 0);
 
-  WaveState W;
+  WaveState<L::NR> W;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) W.acc[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int r = 0; r < L::NR; ++r) W.acc[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
   W.m = -INFINITY;
   W.l = 0.0f;
 
@@ -297,7 +360,6 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   // workgroup (64 KiB requested per compute unit at any time) beats two, three and four (17.0, 17.4,
   // 17.7 and 19.0 us for 64.5 MiB of tiles).
   if constexpr (PRIVATE) {
-    static_assert(DEPTH == 1, "one unit in flight");
     // unit v + j * n_waves of the pair is this wave's j-th; its list entry sits in lane j
     auto entry = [&](int j, int u) {
       Entry e{0, 0};
@@ -308,55 +370,62 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
         int valid = ctx - bj * S - sub * kUnitTokens;
         valid = valid > kUnitTokens ? kUnitTokens : valid;
         if (bj >= 0 && valid > 0 && slot >= 0 && slot < n_slots) {
-          e.elem_off = (size_t)slot * D.tile_stride + sub * kUnitTokens * kMfmaD;
+          e.elem_off = (size_t)slot * D.tile_stride + sub * kUnitTokens * DH;
           e.valid = valid;
         }
       }
       return e;
     };
-    UnitRegs b0;
-    Entry e0 = entry(0, v);
-    issue_unit(b0, k_pool, v_pool, e0, ln, kg);
-    int j = 0;
-    for (int u = v; u < n_units; u += n_waves) {
-      ++j;
-      const Entry nx = entry(j, u + n_waves);
-      consume_unit(W, b0, qreg, e0.valid, scale2, kg);
-      e0 = nx;
-      issue_unit(b0, k_pool, v_pool, nx, ln, kg);
-    }
-  } else {
-    UnitRegs buf[DEPTH];
+    UnitRegs<DT, DH> buf[DEPTH];
     Entry ent[DEPTH];
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      ent[d] = read_entry(sel, slot_list, u0 + d, u1, ush, S, ctx, n_slots, D.tile_stride);
-      issue_unit(buf[d], k_pool, v_pool, ent[d], ln, kg);
+      ent[d] = entry(d, v + d * n_waves);
+      issue_unit<DT, DH>(buf[d], k_pool, v_pool, ent[d], ln, kg);
+    }
+    int j = DEPTH;
+    for (int u = v; u < n_units; u += DEPTH * n_waves) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        const Entry nx = entry(j, u + (d + DEPTH) * n_waves);
+        ++j;
+        consume_unit<DT, DH>(W, buf[d], qreg, ent[d].valid, scale2, kg);
+        ent[d] = nx;
+        issue_unit<DT, DH>(buf[d], k_pool, v_pool, nx, ln, kg);
+      }
+    }
+  } else {
+    UnitRegs<DT, DH> buf[DEPTH];
+    Entry ent[DEPTH];
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      ent[d] = read_entry<DH>(sel, slot_list, u0 + d, u1, ush, S, ctx, n_slots, D.tile_stride);
+      issue_unit<DT, DH>(buf[d], k_pool, v_pool, ent[d], ln, kg);
     }
     for (int u = u0; u < u1; u += DEPTH) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
-        const Entry nx = read_entry(sel, slot_list, u + d + DEPTH, u1, ush, S, ctx, n_slots, D.tile_stride);
-        consume_unit(W, buf[d], qreg, ent[d].valid, scale2, kg);
+        const Entry nx = read_entry<DH>(sel, slot_list, u + d + DEPTH, u1, ush, S, ctx, n_slots, D.tile_stride);
+        consume_unit<DT, DH>(W, buf[d], qreg, ent[d].valid, scale2, kg);
         ent[d] = nx;
-        issue_unit(buf[d], k_pool, v_pool, nx, ln, kg);
+        issue_unit<DT, DH>(buf[d], k_pool, v_pool, nx, ln, kg);
       }
     }
   }
-  f32x4(&acc)[8] = W.acc;
+  f32x4(&acc)[L::NR] = W.acc;
   float m_run = W.m, l_run = W.l;
 
   // lanes kg = 0..3 of a head saw disjoint tokens under a common maximum
   l_run = sum_xor32(sum_xor16(l_run));
 
   // the host's partial for the outputs this thread will finish: requested now, used after the fold
-  constexpr int kOutPerThread = 16 * kMfmaD / (WAVES * kWave);
+  constexpr int kOutPerThread = (16 * DH + WAVES * kWave - 1) / (WAVES * kWave);
   HostPart hp[kOutPerThread];
 #pragma unroll
   for (int t = 0; t < kOutPerThread; ++t) {
     const int idx = threadIdx.x + t * WAVES * kWave;
-    const int hh = idx < G * kMfmaD ? idx / kMfmaD : 0;
-    hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % kMfmaD);
+    const int hh = idx < G * DH ? idx / DH : 0;
+    hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
   }
 
   // fold the waves of the workgroup through LDS
@@ -366,10 +435,11 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   if (ln < G) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      // acc[r][i]: channel 8*(4*kg + i) + r
-      float* dst = wo + ln * ROW + 8 * (4 * kg + i);
-      *reinterpret_cast<float4*>(dst) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
+      // four consecutive accumulator tiles are four consecutive channels
+#pragma unroll
+      for (int r = 0; r < L::NR; r += 4)
+        *reinterpret_cast<float4*>(wo + ln * ROW + L::channel(r, 4 * kg + i)) =
+            make_float4(acc[r][i], acc[r + 1][i], acc[r + 2][i], acc[r + 3][i]);
     }
     if (kg == 0) {
       wm[ln] = m_run;
@@ -380,8 +450,8 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   const size_t pbase = (size_t)pair * P.nsplit + split;
   if (E.mode == 0) {
     // partial of this split: four channels per thread, 16-byte LDS reads and one 16-byte store
-    for (int item = threadIdx.x; item < G * (kMfmaD / 4); item += WAVES * kWave) {
-      const int h = item / (kMfmaD / 4), c = (item % (kMfmaD / 4)) * 4;
+    for (int item = threadIdx.x; item < G * (DH / 4); item += WAVES * kWave) {
+      const int h = item / (DH / 4), c = (item % (DH / 4)) * 4;
       float mw[WAVES];
       float M = -INFINITY;
 #pragma unroll
@@ -399,7 +469,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
         o.x += f * x.x; o.y += f * x.y; o.z += f * x.z; o.w += f * x.w;
         l += f * base[G * ROW + 16 + h];
       }
-      *reinterpret_cast<float4*>(P.o + (pbase * G + h) * kMfmaD + c) = o;
+      *reinterpret_cast<float4*>(P.o + (pbase * G + h) * DH + c) = o;
       if (c == 0) {
         P.m[pbase * G + h] = M;
         P.l[pbase * G + h] = l;
@@ -410,8 +480,8 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
 #pragma unroll
   for (int t = 0; t < kOutPerThread; ++t) {
     const int idx = threadIdx.x + t * WAVES * kWave;
-    if (idx >= G * kMfmaD) break;
-    const int h = idx / kMfmaD, c = idx % kMfmaD;
+    if (idx >= G * DH) break;
+    const int h = idx / DH, c = idx % DH;
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) M = fmaxf(M, smem[(size_t)w * wstride + G * ROW + h]);
@@ -424,7 +494,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
       l += f * base[G * ROW + 16 + h];
     }
     if (E.mode == 0) {
-      P.o[(pbase * G + h) * kMfmaD + c] = o;
+      P.o[(pbase * G + h) * DH + c] = o;
       if (c == 0) {
         P.m[pbase * G + h] = M;
         P.l[pbase * G + h] = l;
@@ -468,10 +538,10 @@ static bool xcd_grid(const Dims& D, int nsplit, dim3& grid) {
   return false;
 }
 
-template <int WAVES, int DEPTH>
+template <int DT, int DH, int WAVES, int DEPTH>
 __global__ __launch_bounds__(WAVES* kWave) void attn_mfma_kernel(
-    Dims D, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool,
-    const uint16_t* __restrict__ v_pool, long long n_slots, const int32_t* __restrict__ sel_gpu,
+    Dims D, const void* __restrict__ q, const void* __restrict__ k_pool,
+    const void* __restrict__ v_pool, long long n_slots, const int32_t* __restrict__ sel_gpu,
     const int32_t* __restrict__ slot_gpu, const int32_t* __restrict__ n_gpu, Partials P, Epilogue E) {
   extern __shared__ float smem[];
   int b, g, pair, split;
@@ -480,7 +550,7 @@ __global__ __launch_bounds__(WAVES* kWave) void attn_mfma_kernel(
   // The pair's whole list is copied to LDS by all threads at once, in the same round trip that
   // brings the count and the queries: which entries a wave needs depends on the count, and a
   // second, dependent trip to memory would cost more than the few hundred bytes read in vain.
-  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (kMfmaD + 4) + 32));
+  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
   int* l_slot = l_sel + D.k;
   const size_t list0 = (size_t)pair * D.k;
   const int n = n_gpu[pair];
@@ -489,20 +559,20 @@ __global__ __launch_bounds__(WAVES* kWave) void attn_mfma_kernel(
     l_sel[t] = sel_gpu[list0 + t];
     l_slot[t] = slot_gpu[list0 + t];
   }
-  u32x4 qreg[4];
-  load_q(qreg, D, q, b, g, lane & 15, lane >> 4);
+  QRegs<DT, DH> qreg;
+  load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
   __syncthreads();
-  attend_pair<WAVES, DEPTH>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, n, ctx, P, E, smem);
+  attend_pair<DT, DH, WAVES, DEPTH>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, n, ctx, P, E, smem);
 }
 
 // The same attention with the list entries fetched by the waves themselves (see attend_pair, PRIVATE):
 // used when no wave can have more than 64 units.  Without the staging of the list through LDS and its
 // barrier the first tile request leaves one trip to memory after the wave started: 16.4 us against
 // 17.0 us for config 3's 64.5 MiB of tiles (config 2: 10.4 against 10.9, config 5: 30.0 against 30.6).
-template <int WAVES, bool REMAP>
+template <int DT, int DH, int WAVES, bool REMAP>
 __global__ __launch_bounds__(WAVES* kWave) void attn_mfma_private_kernel(
-    Dims D, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool,
-    const uint16_t* __restrict__ v_pool, long long n_slots, const int32_t* __restrict__ sel_gpu,
+    Dims D, const void* __restrict__ q, const void* __restrict__ k_pool,
+    const void* __restrict__ v_pool, long long n_slots, const int32_t* __restrict__ sel_gpu,
     const int32_t* __restrict__ slot_gpu, const int32_t* __restrict__ n_gpu, Partials P, Epilogue E) {
   extern __shared__ float smem[];
   int b, g, pair, split;
@@ -519,9 +589,9 @@ __global__ __launch_bounds__(WAVES* kWave) void attn_mfma_private_kernel(
   }
   const int n = n_gpu[pair];
   const int ctx = D.ctx_len[b];
-  u32x4 qreg[4];
-  load_q(qreg, D, q, b, g, lane & 15, lane >> 4);
-  attend_pair<WAVES, 1, true>(D, b, g, split, qreg, k_pool, v_pool, n_slots, nullptr, nullptr, n, ctx, P, E, smem,
+  QRegs<DT, DH> qreg;
+  load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), true>(D, b, g, split, qreg, k_pool, v_pool, n_slots, nullptr, nullptr, n, ctx, P, E, smem,
                               my_sel, my_slot);
 }
 
@@ -556,9 +626,9 @@ __device__ __forceinline__ Hint load_hint(const Dims& D, int pair, int lane, con
 // they were issued, and a touch takes a loaded memory system's full latency).  The touch goes through a
 // buffer descriptor that covers the unit, or nothing: no branch, so nothing ever waits for its value.
 // The caller keeps tk and tv alive (an empty asm that names them) until its own later loads have returned.
-template <int WAVES>
+template <int DT, int DH, int WAVES>
 __device__ __forceinline__ void touch_hint(const Dims& D, const Hint& h, const Partials& P, int v, int lane,
-                                           const uint16_t* k_pool, const uint16_t* v_pool, long long n_slots,
+                                           const void* k_pool, const void* v_pool, long long n_slots,
                                            uint32_t& tk, uint32_t& tv) {
   int n = __builtin_amdgcn_readfirstlane(h.n_old);
   n = n < 0 ? 0 : (n > D.k ? D.k : n);
@@ -573,14 +643,16 @@ __device__ __forceinline__ void touch_hint(const Dims& D, const Hint& h, const P
                              : __builtin_amdgcn_readlane(h.s_hi, e & (kWave - 1));
   const bool ok = u0 < n_units && slot >= 0 && slot < n_slots;
   slot = ok ? slot : 0;
-  const size_t off = (size_t)slot * D.tile_stride + sub * kUnitTokens * kMfmaD;
-  const int bytes = ok ? kUnitBytes : 0;
-  const __amdgpu_buffer_rsrc_t kr =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(k_pool + off), 0, bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t vr =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(v_pool + off), 0, bytes, 0x00020000);
-  tk = __builtin_amdgcn_raw_buffer_load_b32(kr, lane * 64, 0, 0);  // one dword of every 64 bytes of the unit
-  tv = __builtin_amdgcn_raw_buffer_load_b32(vr, lane * 64, 0, 0);
+  const size_t off = (size_t)slot * D.tile_stride + sub * kUnitTokens * DH;
+  using L = Tile<DT, DH>;
+  const int bytes = ok ? L::UNITB : 0;
+  char* kp = static_cast<char*>(const_cast<void*>(k_pool)) + off * L::ES;
+  char* vp = static_cast<char*>(const_cast<void*>(v_pool)) + off * L::ES;
+  const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(kp, 0, bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(vp, 0, bytes, 0x00020000);
+  constexpr int kStep = L::UNITB / kWave;  // one dword of every 64 bytes of a 4 KiB unit
+  tk = __builtin_amdgcn_raw_buffer_load_b32(kr, lane * kStep, 0, 0);
+  tv = __builtin_amdgcn_raw_buffer_load_b32(vr, lane * kStep, 0, 0);
 }
 
 // Selection and attention of a pair in one launch (the non-pipelined description of Sec. 3.2:
@@ -590,11 +662,11 @@ __device__ __forceinline__ void touch_hint(const Dims& D, const Hint& h, const P
 // lists out, because the host needs to know which selected blocks are its own.
 // SEL_WAVES = 8: all waves share the keys and exchange counts through LDS; SEL_WAVES = 1: one wave
 // holds all keys and selects without a barrier while the others wait (kept for comparison).
-template <int SEL_WAVES, int KPL, bool REMAP>
+template <int DT, int DH, int SEL_WAVES, int KPL, bool REMAP>
 __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
-    Dims D, const uint16_t* __restrict__ q, const float* __restrict__ scores,
-    const int32_t* __restrict__ table, const uint16_t* __restrict__ k_pool,
-    const uint16_t* __restrict__ v_pool, long long n_slots, int32_t* __restrict__ sel_all,
+    Dims D, const void* __restrict__ q, const float* __restrict__ scores,
+    const int32_t* __restrict__ table, const void* __restrict__ k_pool,
+    const void* __restrict__ v_pool, long long n_slots, int32_t* __restrict__ sel_all,
     int32_t* __restrict__ sel_gpu, int32_t* __restrict__ slot_gpu, int32_t* __restrict__ n_gpu,
     int32_t* __restrict__ sel_host, int32_t* __restrict__ n_host, Partials P, Epilogue E) {
   constexpr int WAVES = 8;
@@ -605,13 +677,13 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   // LDS after the fold area: resident list (block, slot), the selector's exchange words, the count
   const int kpad = (D.k + 3) & ~3;  // keeps what follows 16-byte aligned
-  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (kMfmaD + 4) + 32));
+  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
   int* l_slot = l_sel + kpad;
   int* l_x = l_slot + kpad;
   int* l_n = l_x + selector_lds_ints<WAVES>();
 
-  u32x4 qreg[4];
-  load_q(qreg, D, q, b, g, lane & 15, lane >> 4);
+  QRegs<DT, DH> qreg;
+  load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
   const int ctx = D.ctx_len[b];  // once, here: the attention below must not wait for it again
 
   const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
@@ -626,7 +698,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     int slot[KPL];
     load_keys<SEL_WAVES, KPL>(D, scores, table, pair, nb, sw, lane, key, slot);
     __builtin_amdgcn_sched_barrier(0);
-    touch_hint<WAVES>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
+    touch_hint<DT, DH, WAVES>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
     __builtin_amdgcn_sched_barrier(0);
     Selector<SEL_WAVES, KPL> S{l_x, 0, sw};
     uint32_t sel = 0;
@@ -675,7 +747,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     if (tid == 0) l_n[0] = ng;
   }
   __syncthreads();
-  attend_pair<WAVES, 1>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>()>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
   asm volatile("" ::"v"(touched_k), "v"(touched_v));  // the touches stay loads, their registers reserved until they have returned
 }
 
@@ -697,17 +769,17 @@ constexpr int kStepEntryBytes = 512;  // one digest entry: min row and max row o
 template <int KPL>
 __global__ __launch_bounds__(8 * kWave) void step_kernel(
     Dims D, const uint16_t* q, const char* digest, const int32_t* __restrict__ table,
-    const uint16_t* __restrict__ k_pool, const uint16_t* __restrict__ v_pool, long long n_slots,
+    const void* __restrict__ k_pool, const void* __restrict__ v_pool, long long n_slots,
     float* scores, int32_t* __restrict__ sel_all, int32_t* __restrict__ sel_gpu,
     int32_t* __restrict__ slot_gpu, int32_t* __restrict__ n_gpu, int32_t* __restrict__ sel_host,
     int32_t* __restrict__ n_host, Partials P, Epilogue E) {
-  constexpr int WAVES = 8;
+  constexpr int WAVES = 8, DT = SCOUT_BF16, DH = 128;
   extern __shared__ float smem[];
   const int b = blockIdx.z, g = blockIdx.y, pair = grid_pair();
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int kpad = (D.k + 3) & ~3;
-  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (kMfmaD + 4) + 32));
+  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
   int* l_slot = l_sel + kpad;
   int* l_x = l_slot + kpad;
   int* l_n = l_x + selector_lds_ints<WAVES>();
@@ -723,13 +795,13 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     slot[r] = table[trow + (i < D.max_blocks ? i : D.max_blocks - 1)];
   }
   // the group's queries: thread t < 256 folds channel t % 128, negative (t < 128) or positive parts
-  const int fc = threadIdx.x & (kMfmaD - 1);
-  const bool fpos = threadIdx.x >= kMfmaD;
-  const uint16_t* qbase = q + ((size_t)b * D.Hq + g * D.G) * kMfmaD + fc;
+  const int fc = threadIdx.x & (DH - 1);
+  const bool fpos = threadIdx.x >= DH;
+  const uint16_t* qbase = q + ((size_t)b * D.Hq + g * D.G) * DH + fc;
   float qv[16];
-  if (threadIdx.x < 2 * kMfmaD) {
+  if (threadIdx.x < 2 * DH) {
 #pragma unroll
-    for (int h = 0; h < 16; ++h) qv[h] = bf16_bits_to_f32(qbase[(size_t)(h < D.G ? h : D.G - 1) * kMfmaD]);
+    for (int h = 0; h < 16; ++h) qv[h] = bf16_bits_to_f32(qbase[(size_t)(h < D.G ? h : D.G - 1) * DH]);
   }
   const int ctx = D.ctx_len[b];
   int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;
@@ -751,12 +823,12 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
   u32x4 raw[kStepBatch];
   load_batch(raw, wave);
 
-  if (threadIdx.x < 2 * kMfmaD) {
+  if (threadIdx.x < 2 * DH) {
     double f = 0.0;
 #pragma unroll
     for (int h = 0; h < 16; ++h)
       if (h < D.G) f += (double)(fpos ? fmaxf(qv[h], 0.0f) : fminf(qv[h], 0.0f));
-    coef_lds[(fpos ? kMfmaD : 0) + fc] = f;
+    coef_lds[(fpos ? DH : 0) + fc] = f;
   }
   // rows of the key array that no batch will write
   for (int i = n_batches * 16 + threadIdx.x; i < WAVES * kWave * KPL; i += WAVES * kWave) l_key[i] = 0u;
@@ -765,7 +837,7 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) coef[u][i] = coef_lds[(u >= 2 ? kMfmaD : 0) + (u & 1) * 64 + (lane & 7) * 8 + i];
+    for (int i = 0; i < 8; ++i) coef[u][i] = coef_lds[(u >= 2 ? DH : 0) + (u & 1) * 64 + (lane & 7) * 8 + i];
 
   const bool hi2 = (lane >> 2) & 1;
   const size_t srow = (size_t)pair * D.max_blocks;
@@ -809,8 +881,8 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
   if (scores != nullptr)  // the row's tail beyond the last batch
     for (int j = n_batches * 16 + threadIdx.x; j < D.max_blocks; j += WAVES * kWave) scores[srow + j] = -INFINITY;
 
-  u32x4 qreg[4];
-  load_q(qreg, D, q, b, g, lane & 15, lane >> 4);
+  QRegs<DT, DH> qreg;
+  load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
   __syncthreads();
 
   const int k_eff = D.k < nb ? D.k : nb;
@@ -861,7 +933,7 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     l_n[0] = ng;
   }
   __syncthreads();
-  attend_pair<WAVES, 1>(D, b, g, 0, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
+  attend_pair<DT, DH, WAVES, 1>(D, b, g, 0, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
 }
 
 // ---------------------------------------------------------------- VALU family
@@ -1059,13 +1131,19 @@ __global__ void merge_kernel(Dims D, const float* __restrict__ o_a, const float*
 
 // ------------------------------------------------------------ host launchers
 
-bool mfma_supported(const Dims& D, int dtype) {
-  return dtype == SCOUT_BF16 && D.d == kMfmaD && D.S % kUnitTokens == 0 && D.G <= 16;
+size_t mfma_smem_bytes(const Dims& D, int waves) {
+  return (size_t)waves * (D.G * (D.d + 4) + 32) * sizeof(float);
 }
 
-size_t mfma_smem_bytes(const Dims& D, int waves) {
-  return (size_t)waves * (D.G * (kMfmaD + 4) + 32) * sizeof(float);
-}
+// RUN(DT, DH) for the problem's element type and head dim
+#define SCOUT_BY_TYPE(dtype, d, RUN)                              \
+  do {                                                            \
+    if ((dtype) == SCOUT_BF16 && (d) == 128) RUN(SCOUT_BF16, 128);     \
+    else if ((dtype) == SCOUT_BF16 && (d) == 64) RUN(SCOUT_BF16, 64);  \
+    else if ((dtype) == SCOUT_F32 && (d) == 128) RUN(SCOUT_F32, 128);  \
+    else if ((dtype) == SCOUT_F32 && (d) == 64) RUN(SCOUT_F32, 64);    \
+    else return SCOUT_EUNSUPPORTED;                               \
+  } while (0)
 
 // family 2: MFMA kernel with `waves` waves per workgroup (8 or 16); family 1: vector ALU.
 // E.mode != 0 requires P.nsplit == 1 and family 2 (the workgroup finishes the pair itself).
@@ -1077,58 +1155,42 @@ int launch_attn(const Dims& D, int dtype, int family, int waves, const void* q, 
   if (family == 2) {
     dim3 grid(P.nsplit, D.Hkv, D.B), block(waves * kWave);
     const size_t lds = mfma_smem_bytes(D, waves) + 2 * (size_t)D.k * sizeof(int);
-    const uint16_t* q16 = static_cast<const uint16_t*>(q);
-    const uint16_t* k16 = static_cast<const uint16_t*>(k_pool);
-    const uint16_t* v16 = static_cast<const uint16_t*>(v_pool);
-#define SCOUT_ATTN(W, DP)                                                                               \
-  hipLaunchKernelGGL((attn_mfma_kernel<W, DP>), grid, block, lds, st, D, q16, k16, v16, n_slots, sel_gpu, \
-                     slot_gpu, n_gpu, P, E)
     // units in flight per wave: few.  Requests that only queue in the memory system buy nothing (a
     // compute unit's loads return in the order they were issued), and fewer registers leave room for
     // the next workgroup to start its head while this one folds.
     const long long units_per_wave = (((long long)D.k * (D.S / kUnitTokens)) + P.nsplit * waves - 1) / (P.nsplit * waves);
-    if (waves == 16)
-      SCOUT_ATTN(16, 1);
-    else if (waves == 8 && units_per_wave <= 64 && xcd_grid(D, P.nsplit, grid))
-      hipLaunchKernelGGL((attn_mfma_private_kernel<8, true>), grid, block, mfma_smem_bytes(D, 8), st, D, q16, k16, v16,
-                         n_slots, sel_gpu, slot_gpu, n_gpu, P, E);
-    else if (waves == 8 && units_per_wave <= 64)
-      hipLaunchKernelGGL((attn_mfma_private_kernel<8, false>), grid, block, mfma_smem_bytes(D, 8), st, D, q16, k16, v16,
-                         n_slots, sel_gpu, slot_gpu, n_gpu, P, E);
-    else if (waves == 8)
-      SCOUT_ATTN(8, 1);
-    else if (waves == 4)
-      SCOUT_ATTN(4, 2);
-    else
-      return SCOUT_EINVAL;
+    const bool few = waves == 8 && units_per_wave <= 64;
+    const bool remap = few && xcd_grid(D, P.nsplit, grid);
+    if (waves != 4 && waves != 8 && waves != 16) return SCOUT_EINVAL;
+#define SCOUT_ATTN(KERNEL, LDS)                                                                                     \
+  hipLaunchKernelGGL(KERNEL, grid, block, LDS, st, D, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, P, E)
+#define SCOUT_ATTN_TYPE(DT, DH)                                                            \
+  do {                                                                                     \
+    if (remap) SCOUT_ATTN((attn_mfma_private_kernel<DT, DH, 8, true>), mfma_smem_bytes(D, 8));     \
+    else if (few) SCOUT_ATTN((attn_mfma_private_kernel<DT, DH, 8, false>), mfma_smem_bytes(D, 8)); \
+    else if (waves == 16) SCOUT_ATTN((attn_mfma_kernel<DT, DH, 16, 1>), lds);              \
+    else if (waves == 8) SCOUT_ATTN((attn_mfma_kernel<DT, DH, 8, 1>), lds);                \
+    else SCOUT_ATTN((attn_mfma_kernel<DT, DH, 4, 2>), lds);                                \
+  } while (0)
+    SCOUT_BY_TYPE(dtype, D.d, SCOUT_ATTN_TYPE);
+#undef SCOUT_ATTN_TYPE
 #undef SCOUT_ATTN
   } else {
     if (E.mode != 0) return SCOUT_EINVAL;
     dim3 grid(P.nsplit, pairs, (D.G + kValuHeads - 1) / kValuHeads), block(kWave);
-    if (dtype == SCOUT_BF16 && D.d == 128)
-      hipLaunchKernelGGL((attn_valu_kernel<SCOUT_BF16, 128>), grid, block, 0, st, D, q, k_pool, v_pool,
-                         n_slots, sel_gpu, slot_gpu, n_gpu, P);
-    else if (dtype == SCOUT_BF16 && D.d == 64)
-      hipLaunchKernelGGL((attn_valu_kernel<SCOUT_BF16, 64>), grid, block, 0, st, D, q, k_pool, v_pool,
-                         n_slots, sel_gpu, slot_gpu, n_gpu, P);
-    else if (dtype == SCOUT_F32 && D.d == 128)
-      hipLaunchKernelGGL((attn_valu_kernel<SCOUT_F32, 128>), grid, block, 0, st, D, q, k_pool, v_pool,
-                         n_slots, sel_gpu, slot_gpu, n_gpu, P);
-    else if (dtype == SCOUT_F32 && D.d == 64)
-      hipLaunchKernelGGL((attn_valu_kernel<SCOUT_F32, 64>), grid, block, 0, st, D, q, k_pool, v_pool,
-                         n_slots, sel_gpu, slot_gpu, n_gpu, P);
-    else
-      return SCOUT_EUNSUPPORTED;
+#define SCOUT_VALU(DT, DH)                                                                                             \
+  hipLaunchKernelGGL((attn_valu_kernel<DT, DH>), grid, block, 0, st, D, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, \
+                     n_gpu, P)
+    SCOUT_BY_TYPE(dtype, D.d, SCOUT_VALU);
+#undef SCOUT_VALU
   }
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
-bool select_attend_supported(const Dims& D, int dtype) {
-  return mfma_supported(D, dtype) && D.max_blocks <= 8 * kWave * 16;
-}
+bool select_attend_supported(const Dims& D) { return D.max_blocks <= 8 * kWave * 16; }
 
 // Selection fused into the head of the MFMA attention kernel (8 waves per workgroup).
-int launch_select_attend(const Dims& D, const void* q, const float* scores, const int32_t* table,
+int launch_select_attend(const Dims& D, int dtype, const void* q, const float* scores, const int32_t* table,
                          const void* k_pool, const void* v_pool, long long n_slots, int32_t* sel_all,
                          int32_t* sel_gpu, int32_t* slot_gpu, int32_t* n_gpu, int32_t* sel_host,
                          int32_t* n_host, Partials P, Epilogue E, hipStream_t st) {
@@ -1137,31 +1199,28 @@ int launch_select_attend(const Dims& D, const void* q, const float* scores, cons
   dim3 grid(P.nsplit, D.Hkv, D.B), block(8 * kWave);
   const bool remap = xcd_grid(D, P.nsplit, grid);
   const size_t lds = mfma_smem_bytes(D, 8) + (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4) * sizeof(int);
-  const uint16_t* q16 = static_cast<const uint16_t*>(q);
-  const uint16_t* k16 = static_cast<const uint16_t*>(k_pool);
-  const uint16_t* v16 = static_cast<const uint16_t*>(v_pool);
-#define SCOUT_SA(SW, KPL)                                                                                      \
-  do {                                                                                                         \
-    if (remap)                                                                                                 \
-      hipLaunchKernelGGL((select_attend_kernel<SW, KPL, true>), grid, block, lds, st, D, q16, scores, table, k16, \
-                         v16, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E);             \
-    else                                                                                                       \
-      hipLaunchKernelGGL((select_attend_kernel<SW, KPL, false>), grid, block, lds, st, D, q16, scores, table, k16, \
-                         v16, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E);             \
+#define SCOUT_SA(DT, DH, KPL)                                                                                     \
+  do {                                                                                                            \
+    if (remap)                                                                                                    \
+      hipLaunchKernelGGL((select_attend_kernel<DT, DH, 8, KPL, true>), grid, block, lds, st, D, q, scores, table, \
+                         k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E);     \
+    else                                                                                                          \
+      hipLaunchKernelGGL((select_attend_kernel<DT, DH, 8, KPL, false>), grid, block, lds, st, D, q, scores, table,\
+                         k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E);     \
   } while (0)
   // All eight waves share the keys: measured faster than one wave selecting alone while seven wait
   // (46.9 vs 44.1 us per step at 1024 blocks per pair), a lone wave issues too slowly.
   const int per_lane = (D.max_blocks + 8 * kWave - 1) / (8 * kWave);
-  if (per_lane <= 2)
-    SCOUT_SA(8, 2);
-  else if (per_lane <= 4)
-    SCOUT_SA(8, 4);
-  else if (per_lane <= 8)
-    SCOUT_SA(8, 8);
-  else if (per_lane <= 16)
-    SCOUT_SA(8, 16);
-  else
-    return SCOUT_EUNSUPPORTED;
+#define SCOUT_SA_TYPE(DT, DH)                    \
+  do {                                           \
+    if (per_lane <= 2) SCOUT_SA(DT, DH, 2);      \
+    else if (per_lane <= 4) SCOUT_SA(DT, DH, 4); \
+    else if (per_lane <= 8) SCOUT_SA(DT, DH, 8); \
+    else if (per_lane <= 16) SCOUT_SA(DT, DH, 16); \
+    else return SCOUT_EUNSUPPORTED;              \
+  } while (0)
+  SCOUT_BY_TYPE(dtype, D.d, SCOUT_SA_TYPE);
+#undef SCOUT_SA_TYPE
 #undef SCOUT_SA
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
@@ -1170,7 +1229,7 @@ int launch_select_attend(const Dims& D, const void* q, const float* scores, cons
 // long sequence among short ones cannot hold the launch up for long (2048 blocks = 1 MiB of digest).
 bool step_kernel_supported(const Dims& D, int dtype) {
   // (with a selection per query head the scoring pass of its own serves the G heads of a row in one reading)
-  return select_attend_supported(D, dtype) && D.digest_kind == 0 && D.group_max == 0 && D.share == 1 &&
+  return dtype == SCOUT_BF16 && D.d == 128 && select_attend_supported(D) && D.digest_kind == 0 && D.group_max == 0 && D.share == 1 &&
          D.max_blocks <= 2048;
 }
 
@@ -1187,13 +1246,11 @@ int launch_step(const Dims& D, const void* q, const void* digest, const int32_t*
   const int kpl = per_lane <= 2 ? 2 : per_lane <= 4 ? 4 : per_lane <= 8 ? 8 : 16;
   const size_t lds = mfma_smem_bytes(D, 8) +
                      (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4 + 8 * kWave * kpl) * sizeof(int) +
-                     2 * kMfmaD * sizeof(double);
+                     2 * 128 * sizeof(double);
   const uint16_t* q16 = static_cast<const uint16_t*>(q);
   const char* dg = static_cast<const char*>(digest);
-  const uint16_t* k16 = static_cast<const uint16_t*>(k_pool);
-  const uint16_t* v16 = static_cast<const uint16_t*>(v_pool);
 #define SCOUT_STEP(KPL)                                                                                      \
-  hipLaunchKernelGGL((step_kernel<KPL>), grid, block, lds, st, D, q16, dg, table, k16, v16, n_slots, scores, \
+  hipLaunchKernelGGL((step_kernel<KPL>), grid, block, lds, st, D, q16, dg, table, k_pool, v_pool, n_slots, scores, \
                      sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)
   if (kpl == 2)
     SCOUT_STEP(2);

@@ -1,13 +1,18 @@
-"""ctypes binding of libscout.so: argument marshalling only.
+"""Binding of libscout.so: argument marshalling only.
 
 Every function takes torch CUDA tensors (device memory owned by the caller),
 passes their addresses and the current HIP stream to the C ABI of
 ``include/scout.h`` and raises ``ScoutError`` on a negative return code.  There
 is no CPU fallback: if the library has not been built, loading fails loudly.
+
+A call made goes through the extension module ``_calls`` (csrc/py_calls.cpp), which looks into the
+tensors from C++: a scout_layer_step costs the interpreter a few microseconds instead of the 17 that
+twenty arguments took through ctypes.  A call recorded (prepare) is marshalled by ctypes, once.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -83,6 +88,25 @@ def lib():
     return _lib
 
 
+_calls = None
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
+
+
+def _load_calls():
+    """The extension module that marshals calls, bound to the entry points of the loaded library."""
+    global _calls
+    if not os.path.exists(CALLS_PATH):
+        raise FileNotFoundError(
+            f"{CALLS_PATH} is missing: build it first (python -m paper_2603_27138_amd.build); there is no fallback path")
+    spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    L = lib()
+    mod.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS})
+    _calls = mod
+    return mod
+
+
 _calib = None
 
 
@@ -106,6 +130,11 @@ def calib_lib():
 def _check(fn: str, rc: int):
     if rc != 0:
         raise ScoutError(fn, rc, lib().scout_strerror(rc).decode())
+
+
+def _done(fn: str, rc: int):
+    if rc != 0:
+        _check(fn, rc)
 
 
 _recording = None   # a Prepared being filled: calls are recorded instead of made
@@ -204,12 +233,17 @@ def calib_copy(src: torch.Tensor, dst: torch.Tensor):
 
 
 def build_digests(p: Problem, k_blocks, digest):
+    if _recording is None:
+        return _done("build_digests", (_calls or _load_calls()).build_digests(p, k_blocks, digest))
     _call("build_digests", lib().build_digests, ctypes.byref(p), _ptr(k_blocks), _ptr(digest), _stream())
 
 
 def append_token(p: Problem, ctx_len, k_new, v_new, new_slot, digest, block_table, k_pool, v_pool, n_slots,
                  host_k=None, host_v=None):
     """host_k / host_v: the host's copy of every block (pinned CPU tensors, or device tensors), or None."""
+    if _recording is None:
+        return _done("append_token", (_calls or _load_calls()).append_token(
+            p, ctx_len, k_new, v_new, new_slot, digest, block_table, k_pool, v_pool, n_slots, host_k, host_v))
     hk = None if host_k is None else _ptr_addressable(host_k)
     hv = None if host_v is None else _ptr_addressable(host_v)
     _call("append_token", lib().append_token, ctypes.byref(p), _ptr(ctx_len), _ptr(k_new), _ptr(v_new),
@@ -218,17 +252,25 @@ def append_token(p: Problem, ctx_len, k_new, v_new, new_slot, digest, block_tabl
 
 
 def score_blocks(p: Problem, q, digest, scores, ws):
+    if _recording is None:
+        return _done("score_blocks", (_calls or _load_calls()).score_blocks(p, q, digest, scores, ws))
     _call("score_blocks", lib().score_blocks, ctypes.byref(p), _ptr(q), _ptr(digest), _ptr(scores),
           _ptr(ws), ws.numel(), _stream())
 
 
 def select_topk(p: Problem, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, ws):
+    if _recording is None:
+        return _done("select_topk", (_calls or _load_calls()).select_topk(
+            p, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, ws))
     _call("select_topk", lib().select_topk, ctypes.byref(p), _ptr(scores), _ptr(block_table), _ptr(sel_all),
           _ptr(sel_gpu), _ptr(slot_gpu), _ptr(n_gpu), _ptr(sel_host),
           _ptr(n_host), _ptr(ws), ws.numel(), _stream())
 
 
 def sparse_decode_attn(p: Problem, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, o, m, l, ws):
+    if _recording is None:
+        return _done("sparse_decode_attn", (_calls or _load_calls()).sparse_decode_attn(
+            p, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, o, m, l, ws))
     _call("sparse_decode_attn", lib().sparse_decode_attn, ctypes.byref(p), _ptr(q), _ptr(k_pool), _ptr(v_pool), int(n_slots),
           _ptr(sel_gpu), _ptr(slot_gpu), _ptr(n_gpu), _ptr(o), _ptr(m), _ptr(l),
           _ptr(ws), ws.numel(), _stream())
@@ -236,27 +278,42 @@ def sparse_decode_attn(p: Problem, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu
 
 def sparse_decode_attn_static(p: Problem, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, o, m, l):
     """sparse_decode_attn without a workspace: the library's own static scratch buffer (no allocation)."""
+    if _recording is None:
+        return _done("sparse_decode_attn_static", (_calls or _load_calls()).sparse_decode_attn_static(
+            p, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, o, m, l))
     _call("sparse_decode_attn_static", lib().sparse_decode_attn_static, ctypes.byref(p), _ptr(q), _ptr(k_pool),
           _ptr(v_pool), int(n_slots), _ptr(sel_gpu), _ptr(slot_gpu), _ptr(n_gpu), _ptr(o), _ptr(m), _ptr(l), _stream())
 
 
 def attn_partials(p: Problem, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, ws):
+    if _recording is None:
+        return _done("scout_attn_partials", (_calls or _load_calls()).attn_partials(
+            p, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, ws))
     _call("scout_attn_partials", lib().scout_attn_partials, ctypes.byref(p), _ptr(q), _ptr(k_pool), _ptr(v_pool), int(n_slots),
           _ptr(sel_gpu), _ptr(slot_gpu), _ptr(n_gpu), _ptr(ws), ws.numel(),
           _stream())
 
 
 def attn_finish(p: Problem, host_o, host_m, host_l, out, lse, ws):
+    if _recording is None:
+        return _done("scout_attn_finish", (_calls or _load_calls()).attn_finish(
+            p, host_o, host_m, host_l, out, lse, ws))
     _call("scout_attn_finish", lib().scout_attn_finish, ctypes.byref(p), _ptr(host_o), _ptr(host_m), _ptr(host_l),
           _ptr(out), _ptr(lse), _ptr(ws), ws.numel(), _stream())
 
 
 def merge_partials(p: Problem, o_a, m_a, l_a, o_b, m_b, l_b, out, lse=None):
+    if _recording is None:
+        return _done("merge_partials", (_calls or _load_calls()).merge_partials(
+            p, o_a, m_a, l_a, o_b, m_b, l_b, out, lse))
     _call("merge_partials", lib().merge_partials, ctypes.byref(p), _ptr(o_a), _ptr(m_a), _ptr(l_a), _ptr(o_b),
           _ptr(m_b), _ptr(l_b), _ptr(out), _ptr(lse), _stream())
 
 
 def periodic_recall(p: Problem, q, digest, block_table, recall_blk, recall_slot, evict_blk, n_recall, ws):
+    if _recording is None:
+        return _done("periodic_recall", (_calls or _load_calls()).periodic_recall(
+            p, q, digest, block_table, recall_blk, recall_slot, evict_blk, n_recall, ws))
     _call("periodic_recall", lib().periodic_recall, ctypes.byref(p), _ptr(q), _ptr(digest), _ptr(block_table), _ptr(recall_blk),
           _ptr(recall_slot), _ptr(evict_blk), _ptr(n_recall), _ptr(ws), ws.numel(),
           _stream())
@@ -264,6 +321,9 @@ def periodic_recall(p: Problem, q, digest, block_table, recall_blk, recall_slot,
 
 def recall_fetch(p: Problem, src_k, src_v, recall_blk, recall_slot, n_recall, k_pool, v_pool, n_slots):
     """src_k / src_v: tensors in pinned host memory or on the device."""
+    if _recording is None:
+        return _done("recall_fetch", (_calls or _load_calls()).recall_fetch(
+            p, src_k, src_v, recall_blk, recall_slot, n_recall, k_pool, v_pool, n_slots))
     _call("recall_fetch", lib().recall_fetch, ctypes.byref(p), _ptr_addressable(src_k), _ptr_addressable(src_v), _ptr(recall_blk),
           _ptr(recall_slot), _ptr(n_recall), _ptr(k_pool), _ptr(v_pool),
           int(n_slots), _stream())
@@ -271,6 +331,11 @@ def recall_fetch(p: Problem, src_k, src_v, recall_blk, recall_slot, n_recall, k_
 
 def recall_scatter(p: Problem, staged, tile_off, recall_blk, recall_slot, n_recall, k_pool, v_pool, n_slots):
     """staged: device buffer of packed tiles [tiles][2][S][d]; tile_off: first tile of each pair."""
+    assert staged.numel() % (p.S * p.d * 2) == 0
+    if _recording is None:
+        return _done("recall_scatter", (_calls or _load_calls()).recall_scatter(
+            p, staged, staged.numel() // (p.S * p.d * 2), tile_off, recall_blk, recall_slot, n_recall, k_pool, v_pool,
+            n_slots))
     tile_elems = p.S * p.d * 2
     assert staged.numel() % tile_elems == 0
     _call("recall_scatter", lib().recall_scatter, ctypes.byref(p), _ptr(staged), staged.numel() // tile_elems,
@@ -289,6 +354,10 @@ def calib_gather(p: Problem, k_pool, v_pool, n_slots, slot_gpu, n_gpu, sink=None
 
 def layer_step(p: Problem, q, digest, block_table, k_pool, v_pool, n_slots, host_o, host_m, host_l, scores,
                sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, out, lse, ws):
+    if _recording is None:
+        return _done("scout_layer_step", (_calls or _load_calls()).layer_step(
+            p, q, digest, block_table, k_pool, v_pool, n_slots, host_o, host_m, host_l, scores, sel_all, sel_gpu,
+            slot_gpu, n_gpu, sel_host, n_host, out, lse, ws))
     _call("scout_layer_step", lib().scout_layer_step, ctypes.byref(p), _ptr(q), _ptr(digest), _ptr(block_table), _ptr(k_pool),
           _ptr(v_pool), int(n_slots), _ptr(host_o), _ptr(host_m), _ptr(host_l),
           _ptr(scores), _ptr(sel_all), _ptr(sel_gpu), _ptr(slot_gpu), _ptr(n_gpu),

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -46,10 +47,29 @@ def _hipcc(sources, out, verbose):
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every kernel source into libscout.so next to this file (and the measurement aids into
-    libscout_calib.so, a library of their own); returns the path of libscout.so."""
+    """Compile every kernel source into libscout.so next to this file (the measurement aids into
+    libscout_calib.so, a library of their own, and the Python entry points into _calls.so); returns the path of
+    libscout.so."""
+    build_calls(verbose)
     _hipcc(["calib.hip"], CALIB_LIB, verbose)
     return _hipcc(SOURCES, LIB, verbose)
+
+
+# the entry points as Python functions on torch tensors (CPython extension)
+CALLS_LIB = os.path.join(HERE, "_calls.so")
+
+
+def build_calls(verbose: bool = False) -> str:
+    """Compile the argument marshalling (plain C++17 against the installed torch's headers) into _calls.so."""
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    inc = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], os.path.join(tdir, "include"),
+           os.path.join(tdir, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include"]
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f"-I{i}" for i in inc],
+          os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS_LIB, "-L", os.path.join(tdir, "lib"),
+          "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
+    return CALLS_LIB
 
 
 HOST_LIB = os.path.join(HERE, "libscout_host.so")

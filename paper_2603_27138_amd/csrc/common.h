@@ -83,12 +83,12 @@ __device__ __forceinline__ int grid_pair() { return blockIdx.z * gridDim.y + blo
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
-__device__ __forceinline__ int num_blocks_of(const Dims& D, int b) {
-  int ctx = D.ctx_len[b];
+__device__ __forceinline__ int num_blocks(const Dims& D, int ctx) {
   if (ctx < 0) ctx = 0;
   int nb = (ctx + D.S - 1) >> D.s_shift;
   return nb < D.max_blocks ? nb : D.max_blocks;
 }
+__device__ __forceinline__ int num_blocks_of(const Dims& D, int b) { return num_blocks(D, D.ctx_len[b]); }
 
 // number of lanes below this one whose bit is set in a 64-bit wave mask
 __device__ __forceinline__ int mbcnt64(uint64_t mask) {

@@ -16,85 +16,193 @@ namespace scout {
 
 // ------------------------------------------------------------------ digest
 
-template <int DT>
-__global__ __launch_bounds__(256) void digest_kernel(Dims D, const void* __restrict__ k_blocks,
-                                                     void* __restrict__ digest) {
+// Every key is read once, so the pass is a stream bound by HBM, and what decides its rate is which bytes a wave asks for
+// together: a wave takes whole blocks (tiles of S x d elements, contiguous), one at a time or as many as make eight
+// 16-byte requests per lane, all of them out before the first is used.  With 16 lanes of a wave on one block and the
+// next 16 lanes on the next (four pieces 8 KiB apart per request, one row in flight per lane) 8 sequences x 8 KV heads
+// of 16k to 32k tokens (bf16, d = 128, blocks of 32; 400 MB) took 99 us, with whole blocks per wave 76 us (5.8 TB/s; a bare
+// read of 512 MiB reaches 6.3).  NT: see launch_digest.
+//
+// The rows of a block are dealt to the wave's groups of lanes (ROWB / 16 lanes per row) in contiguous ranges, and the
+// groups' results are joined in token order with strict comparisons, so that the result is that of one thread that
+// walks through the block's valid tokens: of equal elements (zeros of either sign) the first one stays, a NaN in the
+// first token stays, later ones are passed over.
+template <int DT, int DH, int S>
+struct DigestTile {
+  static constexpr int ES = DT == SCOUT_BF16 ? 2 : 4, EPL = 16 / ES;  // element bytes, elements per 16-byte request
+  static constexpr int LPR = DH * ES / 16;                            // lanes per token row
+  static constexpr int RPG = S * LPR / kWave;                         // token rows per group of lanes
+  static constexpr int NBLK = RPG >= 8 ? 1 : 8 / RPG;                 // blocks per wave
+};
+
+// lower: the value of the group with the earlier tokens
+__device__ __forceinline__ float first_min(float lower, float higher) { return higher < lower ? higher : lower; }
+__device__ __forceinline__ float first_max(float lower, float higher) { return higher > lower ? higher : lower; }
+
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+template <bool NT>
+__device__ __forceinline__ u32x4 load_key(const u32x4* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  return *p;
+}
+
+template <int DT, int DH, int S, bool NT>
+__global__ __launch_bounds__(256) void digest_kernel(Dims D, const void* __restrict__ k_blocks, void* __restrict__ digest) {
+  using L = DigestTile<DT, DH, S>;
   const int pair = grid_pair();  // grid (x, Hkv, B)
-  const int b = blockIdx.z;
-  const int cpt = D.d / 8;  // 8-channel chunks per token row
-  const int j = blockIdx.x * (blockDim.x / cpt) + threadIdx.x / cpt;
-  const int c0 = (threadIdx.x % cpt) * 8;
-  const int nb = num_blocks_of(D, b);
-  if (j >= nb) return;
-  int ctx = D.ctx_len[b];
-  int valid = ctx - j * D.S;
-  if (valid > D.S) valid = D.S;
-  const size_t row0 = ((size_t)pair * D.max_blocks + j) * D.S;
-  float mn[8], mx[8], x[8];
-  load8<DT>(k_blocks, row0 * D.d + c0, mn);
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int j0 = (blockIdx.x * 4 + wave) * L::NBLK;
+  const int ctx = D.ctx_len[blockIdx.z];
+  const int nb = num_blocks(D, ctx);
+  if (j0 >= nb) return;
+  const int grp = lane / L::LPR;
+  const u32x4* tile = static_cast<const u32x4*>(k_blocks) + ((size_t)pair * D.max_blocks + j0) * (S * L::LPR) +
+                      grp * L::RPG * L::LPR + lane % L::LPR;
+  u32x4 raw[L::NBLK][L::RPG];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) mx[i] = mn[i];
-  for (int t = 1; t < valid; ++t) {
-    load8<DT>(k_blocks, (row0 + t) * D.d + c0, x);
+  for (int n = 0; n < L::NBLK; ++n) {
+    if (j0 + n < nb) {  // wave-uniform
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      mn[i] = x[i] < mn[i] ? x[i] : mn[i];
-      mx[i] = x[i] > mx[i] ? x[i] : mx[i];
+      for (int i = 0; i < L::RPG; ++i)
+        raw[n][i] = load_key<NT>(tile + (size_t)n * (S * L::LPR) + i * L::LPR);
     }
   }
-  const size_t o_min = (((size_t)pair * D.max_blocks + j) * 2 + 0) * D.d + c0;
-  const size_t o_max = o_min + D.d;
-  if (DT == SCOUT_BF16) {
-    // the values came out of bf16 storage, so the upper halves are exact
-    uint16_t* dg = static_cast<uint16_t*>(digest);
-    uint4 a, c;
-    a.x = (__float_as_uint(mn[0]) >> 16) | (__float_as_uint(mn[1]) & 0xffff0000u);
-    a.y = (__float_as_uint(mn[2]) >> 16) | (__float_as_uint(mn[3]) & 0xffff0000u);
-    a.z = (__float_as_uint(mn[4]) >> 16) | (__float_as_uint(mn[5]) & 0xffff0000u);
-    a.w = (__float_as_uint(mn[6]) >> 16) | (__float_as_uint(mn[7]) & 0xffff0000u);
-    c.x = (__float_as_uint(mx[0]) >> 16) | (__float_as_uint(mx[1]) & 0xffff0000u);
-    c.y = (__float_as_uint(mx[2]) >> 16) | (__float_as_uint(mx[3]) & 0xffff0000u);
-    c.z = (__float_as_uint(mx[4]) >> 16) | (__float_as_uint(mx[5]) & 0xffff0000u);
-    c.w = (__float_as_uint(mx[6]) >> 16) | (__float_as_uint(mx[7]) & 0xffff0000u);
-    *reinterpret_cast<uint4*>(dg + o_min) = a;
-    *reinterpret_cast<uint4*>(dg + o_max) = c;
-  } else {
-    float* dg = static_cast<float*>(digest);
-    float4* pmin = reinterpret_cast<float4*>(dg + o_min);
-    float4* pmax = reinterpret_cast<float4*>(dg + o_max);
-    pmin[0] = make_float4(mn[0], mn[1], mn[2], mn[3]);
-    pmin[1] = make_float4(mn[4], mn[5], mn[6], mn[7]);
-    pmax[0] = make_float4(mx[0], mx[1], mx[2], mx[3]);
-    pmax[1] = make_float4(mx[4], mx[5], mx[6], mx[7]);
+#pragma unroll
+  for (int n = 0; n < L::NBLK; ++n) {
+    const int j = j0 + n;
+    if (j >= nb) break;
+    const int valid = ctx - j * S;
+    float mn[L::EPL], mx[L::EPL];
+    auto element = [&](int i, int e) {
+      if constexpr (DT == SCOUT_BF16) return (e & 1) ? bf16_hi(raw[n][i][e >> 1]) : bf16_lo(raw[n][i][e >> 1]);
+      else return __uint_as_float(raw[n][i][e]);
+    };
+    // group 0 starts with the first token itself, the others with values that give way to any number
+#pragma unroll
+    for (int e = 0; e < L::EPL; ++e) {
+      mn[e] = grp == 0 ? element(0, e) : INFINITY;
+      mx[e] = grp == 0 ? element(0, e) : -INFINITY;
+    }
+    if (valid >= S) {  // wave-uniform
+#pragma unroll
+      for (int i = 0; i < L::RPG; ++i)
+#pragma unroll
+        for (int e = 0; e < L::EPL; ++e) {
+          const float x = element(i, e);
+          mn[e] = first_min(mn[e], x);
+          mx[e] = first_max(mx[e], x);
+        }
+    } else {  // the sequence's last block, partly filled
+#pragma unroll
+      for (int i = 0; i < L::RPG; ++i)
+        if (grp * L::RPG + i < valid) {
+#pragma unroll
+          for (int e = 0; e < L::EPL; ++e) {
+            const float x = element(i, e);
+            mn[e] = first_min(mn[e], x);
+            mx[e] = first_max(mx[e], x);
+          }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < L::EPL; ++e) {
+      if constexpr (L::LPR == 8) {
+        const float pn = __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(mn[e]), 0x128, 0xf, 0xf, false));  // row_ror:8
+        const float px = __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(mx[e]), 0x128, 0xf, 0xf, false));
+        mn[e] = (lane & 8) ? first_min(pn, mn[e]) : first_min(mn[e], pn);
+        mx[e] = (lane & 8) ? first_max(px, mx[e]) : first_max(mx[e], px);
+      }
+      // a swap of a value with itself leaves the lower row's (half's) value in the first result, the higher one's in
+      // the second, in all lanes
+      if constexpr (L::LPR <= 16) {
+        const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(mn[e]), __float_as_uint(mn[e]), false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx[e]), __float_as_uint(mx[e]), false, false);
+        mn[e] = first_min(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        mx[e] = first_max(__uint_as_float(b[0]), __uint_as_float(b[1]));
+      }
+      const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(mn[e]), __float_as_uint(mn[e]), false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx[e]), __float_as_uint(mx[e]), false, false);
+      mn[e] = first_min(__uint_as_float(a[0]), __uint_as_float(a[1]));
+      mx[e] = first_max(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    }
+    // the entry's min row from the first LPR lanes, its max row from the next
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (DT == SCOUT_BF16) {  // the values came out of bf16 storage, so the upper halves are exact
+        const float lo = lane < L::LPR ? mn[2 * i] : mx[2 * i], hi = lane < L::LPR ? mn[2 * i + 1] : mx[2 * i + 1];
+        w[i] = (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
+      } else {
+        w[i] = __float_as_uint(lane < L::LPR ? mn[i] : mx[i]);
+      }
+    }
+    if (lane < 2 * L::LPR)
+      __builtin_nontemporal_store(w, static_cast<u32x4*>(digest) + ((size_t)pair * D.max_blocks + j) * 2 * L::LPR + lane);
   }
 }
 
-// Mean pooling (Sec. 2.2 names it next to min/max pooling): the digest of a block is the sum of its
-// valid keys in binary32, added in token order, one rounding per token, so that the append of a token
-// is one addition and gives the bits a rebuild would give; the mean is sum / count where it is used.
-template <int DT>
-__global__ __launch_bounds__(256) void digest_sum_kernel(Dims D, const void* __restrict__ k_blocks,
-                                                         float* __restrict__ digest) {
+// A thread takes 8 channels of a block and walks through its tokens, ROWS of them requested at a time (bf16 sums of
+// 400 MB of keys: 92 us instead of 104 with one; fp32 rows are twice as long and gain nothing from more than two).  This is how
+// the sums of mean pooling are made (Sec. 2.2 names mean pooling next to min/max pooling): the digest of a block is the
+// sum of its valid keys in binary32, added in token order, one rounding per token, so that the append of a token
+// is one addition and gives the bits a rebuild would give; the mean is sum / count where it is used.  And it is how
+// the min/max digests of 2 KiB tiles are made: there the join of eight groups of lanes costs digest_kernel more than
+// its order of requests gains (bf16, d = 64, blocks of 16, 8 x 8 pairs
+// of 16k to 32k tokens: 65 us there, 39 us here).
+template <int DT, bool SUM, int ROWS, bool NT>
+__global__ __launch_bounds__(256) void digest_rows_kernel(Dims D, const void* __restrict__ k_blocks, void* __restrict__ digest) {
+  constexpr int W = DT == SCOUT_BF16 ? 1 : 2;  // 16-byte words per 8 elements
   const int pair = grid_pair();  // grid (x, Hkv, B)
-  const int b = blockIdx.z;
-  const int cpt = D.d / 8;
+  const int cpt = D.d / 8;       // 8-channel chunks per token row
   const int j = blockIdx.x * (blockDim.x / cpt) + threadIdx.x / cpt;
   const int c0 = (threadIdx.x % cpt) * 8;
-  const int nb = num_blocks_of(D, b);
-  if (j >= nb) return;
-  int valid = D.ctx_len[b] - j * D.S;
-  if (valid > D.S) valid = D.S;
-  const size_t row0 = ((size_t)pair * D.max_blocks + j) * D.S;
-  float sum[8], x[8];
-  load8<DT>(k_blocks, row0 * D.d + c0, sum);
-  for (int t = 1; t < valid; ++t) {
-    load8<DT>(k_blocks, (row0 + t) * D.d + c0, x);
+  const int ctx = D.ctx_len[blockIdx.z];
+  if (j >= num_blocks(D, ctx)) return;
+  const int valid = ctx - j * D.S;
+  const u32x4* p = static_cast<const u32x4*>(k_blocks) + (((size_t)pair * D.max_blocks + j) * D.S * cpt + c0 / 8) * W;
+  float lo[8], hi[8];  // SUM: lo is the sum
+  for (int t0 = 0; t0 < D.S && t0 < valid; t0 += ROWS) {  // ROWS divides S
+    u32x4 raw[ROWS][W];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sum[i] = sum[i] + x[i];
+    for (int i = 0; i < ROWS; ++i)  // rows beyond `valid` lie inside the block and are not used
+#pragma unroll
+      for (int w = 0; w < W; ++w) raw[i][w] = load_key<NT>(p + (size_t)(t0 + i) * cpt * W + w);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      float x[8];
+      load8<DT>(raw[i], 0, x);
+      if (t0 + i < valid) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (SUM) {
+            lo[e] = t0 + i == 0 ? x[e] : lo[e] + x[e];
+          } else {
+            lo[e] = t0 + i == 0 ? x[e] : first_min(lo[e], x[e]);
+            hi[e] = t0 + i == 0 ? x[e] : first_max(hi[e], x[e]);
+          }
+        }
+      }
+    }
   }
-  float4* out = reinterpret_cast<float4*>(digest + ((size_t)pair * D.max_blocks + j) * D.d + c0);
-  out[0] = make_float4(sum[0], sum[1], sum[2], sum[3]);
-  out[1] = make_float4(sum[4], sum[5], sum[6], sum[7]);
+  const size_t entry = (size_t)pair * D.max_blocks + j;
+  if constexpr (SUM) {
+    float4* out = reinterpret_cast<float4*>(static_cast<float*>(digest) + entry * D.d + c0);
+    out[0] = make_float4(lo[0], lo[1], lo[2], lo[3]);
+    out[1] = make_float4(lo[4], lo[5], lo[6], lo[7]);
+  } else {
+    static_assert(SUM || DT == SCOUT_BF16, "layout");
+    u32x4 a, c;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // the values came out of bf16 storage, so the upper halves are exact
+      a[i] = (__float_as_uint(lo[2 * i]) >> 16) | (__float_as_uint(lo[2 * i + 1]) & 0xffff0000u);
+      c[i] = (__float_as_uint(hi[2 * i]) >> 16) | (__float_as_uint(hi[2 * i + 1]) & 0xffff0000u);
+    }
+    u32x4* out = static_cast<u32x4*>(digest) + entry * 2 * cpt + c0 / 8;
+    __builtin_nontemporal_store(a, out);
+    __builtin_nontemporal_store(c, out + cpt);
+  }
 }
 
 // ------------------------------------------------------------------- score
@@ -102,8 +210,6 @@ __global__ __launch_bounds__(256) void digest_sum_kernel(Dims D, const void* __r
 constexpr int kScoreWaves = 4;      // waves per workgroup
 constexpr int kScoreBatch = 8;      // wave-wide loads per batch
 constexpr int kScoreBatches = 1;    // batches per wave (with more than one, two are kept in flight)
-
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 // The score of a block is sum_c P_c*max_j[c] + N_c*min_j[c], with P_c (N_c) the sum over the group's
 // query heads of the positive (negative) parts of q[c]: the group is folded before the stream.
@@ -463,22 +569,47 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_max_kernel(Dims D, c
 // ------------------------------------------------------------ host launchers
 
 int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, hipStream_t st) {
-  const int cpt = D.d / 8;
-  const int blocks_per_wg = 256 / cpt;
-  dim3 grid((D.max_blocks + blocks_per_wg - 1) / blocks_per_wg, D.Hkv, D.B);
-  if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
-  if (D.digest_kind == 1) {
-    float* sums = static_cast<float*>(digest);
-    if (dtype == SCOUT_BF16)
-      hipLaunchKernelGGL(digest_sum_kernel<SCOUT_BF16>, grid, dim3(256), 0, st, D, k_blocks, sums);
-    else
-      hipLaunchKernelGGL(digest_sum_kernel<SCOUT_F32>, grid, dim3(256), 0, st, D, k_blocks, sums);
+  if (D.max_blocks == 0 || D.Hkv == 0 || D.B == 0) return SCOUT_OK;
+  const long long key_bytes = (long long)D.B * D.Hkv * D.max_blocks * D.S * D.d * (dtype == SCOUT_BF16 ? 2 : 4);
+  // Keys beyond what the 256 MiB memory-side cache holds pass by it (non-temporal loads): 400 MB 76 us instead of 85; of
+  // 200 MB a part may still be there, and loads that pass by miss it (bf16, d = 64: 44 us instead of 39).
+  const bool nt = key_bytes > (256ll << 20);
+  // 128-byte token rows are eight groups of lanes to join for each small block: a thread per row chunk is faster
+  // (bf16, d = 64: 39.2 against 65 us for blocks of 16, 39.0 against 40.8 us for blocks of 32; blocks of 64 are whole waves' work).
+  const bool small_tile = dtype == SCOUT_BF16 && D.d == 64 && D.S <= 32;
+  if (D.digest_kind == 1 || small_tile) {
+    const int per_wg = 256 / (D.d / 8);
+    dim3 grid((D.max_blocks + per_wg - 1) / per_wg, D.Hkv, D.B);
+#define SCOUT_DIGEST_ROWS(DT, SUM, ROWS, MAY_NT)                                                                  \
+  do {                                                                                                            \
+    if (MAY_NT && nt) hipLaunchKernelGGL((digest_rows_kernel<DT, SUM, ROWS, MAY_NT>), grid, dim3(256), 0, st, D, k_blocks, digest); \
+    else hipLaunchKernelGGL((digest_rows_kernel<DT, SUM, ROWS, false>), grid, dim3(256), 0, st, D, k_blocks, digest);   \
+  } while (0)
+    if (D.digest_kind == 0) SCOUT_DIGEST_ROWS(SCOUT_BF16, false, 8, true);
+    else if (dtype == SCOUT_BF16) SCOUT_DIGEST_ROWS(SCOUT_BF16, true, 8, true);
+    else SCOUT_DIGEST_ROWS(SCOUT_F32, true, 2, false);
+#undef SCOUT_DIGEST_ROWS
     return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
   }
-  if (dtype == SCOUT_BF16)
-    hipLaunchKernelGGL(digest_kernel<SCOUT_BF16>, grid, dim3(256), 0, st, D, k_blocks, digest);
-  else
-    hipLaunchKernelGGL(digest_kernel<SCOUT_F32>, grid, dim3(256), 0, st, D, k_blocks, digest);
+#define SCOUT_DIGEST(DT, DH, S_)                                                                                  \
+  do {                                                                                                            \
+    constexpr int per_wg = 4 * DigestTile<DT, DH, S_>::NBLK;                                                      \
+    const dim3 grid((D.max_blocks + per_wg - 1) / per_wg, D.Hkv, D.B);                                            \
+    if (nt) hipLaunchKernelGGL((digest_kernel<DT, DH, S_, true>), grid, dim3(256), 0, st, D, k_blocks, digest);   \
+    else hipLaunchKernelGGL((digest_kernel<DT, DH, S_, false>), grid, dim3(256), 0, st, D, k_blocks, digest);     \
+  } while (0)
+#define SCOUT_DIGEST_S(DT, DH)                     \
+  do {                                             \
+    if (D.S == 16) SCOUT_DIGEST(DT, DH, 16);       \
+    else if (D.S == 32) SCOUT_DIGEST(DT, DH, 32);  \
+    else SCOUT_DIGEST(DT, DH, 64);                 \
+  } while (0)
+  if (dtype == SCOUT_BF16 && D.d == 128) SCOUT_DIGEST_S(SCOUT_BF16, 128);
+  else if (dtype == SCOUT_BF16) SCOUT_DIGEST(SCOUT_BF16, 64, 64);
+  else if (D.d == 128) SCOUT_DIGEST_S(SCOUT_F32, 128);
+  else SCOUT_DIGEST_S(SCOUT_F32, 64);
+#undef SCOUT_DIGEST_S
+#undef SCOUT_DIGEST
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 

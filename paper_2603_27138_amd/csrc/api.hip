@@ -10,7 +10,7 @@
 namespace scout {
 
 int launch_digest(const Dims&, int, const void*, void*, hipStream_t);
-int launch_score(const Dims&, int, const void*, const void*, float*, hipStream_t);
+int launch_score(const Dims&, int, const void*, const void*, float*, uint32_t*, hipStream_t);
 int launch_recall_fetch(const Dims&, int, const void*, const void*, const int32_t*, const int32_t*, const int32_t*,
                         void*, void*, long long, hipStream_t);
 int launch_recall_scatter(const Dims&, int, const void*, long long, const int32_t*, const int32_t*, const int32_t*,
@@ -186,7 +186,17 @@ static uint32_t waves_magic(const AttnPlan& A) {
 static Partials carve(void* ws, const WsLayout& L, const AttnPlan& A) {
   char* base = static_cast<char*>(ws);
   return Partials{reinterpret_cast<float*>(base + L.part_o), reinterpret_cast<float*>(base + L.part_m),
-                  reinterpret_cast<float*>(base + L.part_l), A.nsplit, waves_magic(A)};
+                  reinterpret_cast<float*>(base + L.part_l), A.nsplit, waves_magic(A), nullptr, 0};
+}
+
+// The same with a counter per pair, for a launch that folds its own splits.  The counters lie at the end of the m rows,
+// which are sized for kMaxSplit splits and packed for A.nsplit: free below kMaxSplit (false where they are not).
+static bool carve_counters(const Dims& D, void* ws, const WsLayout& L, const AttnPlan& A, Partials* P) {
+  if (A.nsplit >= kMaxSplit) return false;
+  const size_t pairs = (size_t)D.B * D.Hkv;
+  P->arrived = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + L.part_m) + pairs * (kMaxSplit * D.G - 1);
+  P->g_magic = (65536u + D.G - 1) / D.G;
+  return true;
 }
 
 // Attention over the listed blocks, then what E asks for.  One launch when a single MFMA workgroup
@@ -329,7 +339,7 @@ int score_blocks(const scout_problem* p, const void* q, const void* digest, floa
   if (rc != SCOUT_OK) return rc;
   if (q == nullptr || digest == nullptr || scores == nullptr) return SCOUT_EINVAL;
   if (!aligned16(q) || !aligned16(digest) || !aligned16(scores)) return SCOUT_EINVAL;
-  return launch_score(D, p->dtype, q, digest, scores, static_cast<hipStream_t>(stream));
+  return launch_score(D, p->dtype, q, digest, scores, nullptr, static_cast<hipStream_t>(stream));
 }
 
 int select_topk(const scout_problem* p, const float* scores, const int32_t* block_table,
@@ -443,14 +453,14 @@ int sparse_decode_attn_static(const scout_problem* p, const void* q, const void*
     return SCOUT_ESCRATCH;
   if (A.family == 2 && A.nsplit == 1)  // one workgroup per pair finishes the pair itself: no scratch at all
     return launch_attn(D, p->dtype, 2, A.waves, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu,
-                       Partials{nullptr, nullptr, nullptr, 1, waves_magic(A)}, E, st);
+                       Partials{nullptr, nullptr, nullptr, 1, waves_magic(A), nullptr, 0}, E, st);
   if (static_layout(D, A, &off_m, &off_l) > (size_t)SCOUT_STATIC_SCRATCH_BYTES) return SCOUT_ESCRATCH;
   char* base = static_cast<char*>(static_scratch(&rc));
   if (base == nullptr) return rc;
   // Nothing in the buffer has to start at zero: the first pass writes the partial of every (pair, split,
   // head) it was launched for, an empty share included, before the combine pass reads any of them.
   const Partials P{reinterpret_cast<float*>(base), reinterpret_cast<float*>(base + off_m),
-                   reinterpret_cast<float*>(base + off_l), A.nsplit, waves_magic(A)};
+                   reinterpret_cast<float*>(base + off_l), A.nsplit, waves_magic(A), nullptr, 0};
   Epilogue part{};
   part.mode = 0;
   rc = launch_attn(D, p->dtype, A.family, A.waves, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, P, part, st);
@@ -486,7 +496,7 @@ int periodic_recall(const scout_problem* p, const void* q, const void* digest, i
   if (rc != SCOUT_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* scores = reinterpret_cast<float*>(static_cast<char*>(ws) + L.scores);
-  rc = launch_score(D, p->dtype, q, digest, scores, st);
+  rc = launch_score(D, p->dtype, q, digest, scores, nullptr, st);
   if (rc != SCOUT_OK) return rc;
   return launch_recall(D, scores, block_table, recall_blk, recall_slot, evict_blk, n_recall, st);
 }
@@ -553,21 +563,22 @@ int scout_layer_step(const scout_problem* p, const void* q, const void* digest,
     return launch_step(D, q, digest, block_table, k_pool, v_pool, n_slots, scores, sel_all, sel_gpu, slot_gpu, n_gpu,
                        sel_host, n_host, carve(ws, L, A), E, st);
   if (scores == nullptr) scores = reinterpret_cast<float*>(static_cast<char*>(ws) + L.scores);
-  rc = launch_score(D, p->dtype, q, digest, scores, st);
-  if (rc != SCOUT_OK) return rc;
   if (g_fuse_select && A.family == 2 && A.waves == 8 && select_attend_supported(D)) {
-    // selection rides in the head of the attention kernel: two launches for the whole step
+    // selection rides in the head of the attention kernel, and the last workgroup of a pair folds its splits: two
+    // launches for the whole step
     Partials P = carve(ws, L, A);
-    if (A.nsplit == 1)
-      return launch_select_attend(D, p->dtype, q, scores, block_table, k_pool, v_pool, n_slots, sel_all, sel_gpu,
-                                  slot_gpu, n_gpu, sel_host, n_host, P, E, st);
+    const bool fold = A.nsplit > 1 && carve_counters(D, ws, L, A, &P);
+    rc = launch_score(D, p->dtype, q, digest, scores, P.arrived, st);
+    if (rc != SCOUT_OK) return rc;
     Epilogue part{};
     part.mode = 0;
     rc = launch_select_attend(D, p->dtype, q, scores, block_table, k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu,
-                              n_gpu, sel_host, n_host, P, part, st);
-    if (rc != SCOUT_OK) return rc;
+                              n_gpu, sel_host, n_host, P, A.nsplit == 1 || fold ? E : part, st);
+    if (rc != SCOUT_OK || A.nsplit == 1 || fold) return rc;
     return launch_combine(D, P, E, st);
   }
+  rc = launch_score(D, p->dtype, q, digest, scores, nullptr, st);
+  if (rc != SCOUT_OK) return rc;
   rc = launch_topk(D, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, st);
   if (rc != SCOUT_OK) return rc;
   return run_attn(D, p->dtype, A, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, ws, L, E, st);

@@ -308,20 +308,146 @@ __device__ __forceinline__ void load_q(QRegs<DT, DH>& qreg, const Dims& D, const
 template <int DT, int DH>
 constexpr int unit_depth() { return Tile<DT, DH>::UNITB >= 4096 ? 1 : 2; }
 
+// ---- The fold of a pair's splits by the workgroup that arrives last.
+//
+// The splits of a pair run on compute units of different XCDs, each with an L2 of its own, so what one leaves for
+// another is written through to device memory and read past the caches (agent scope), and a workgroup counts itself as
+// arrived only when its stores have been acknowledged.  Nobody waits for anybody: the workgroup that finds itself the
+// last one does the rest, the others end.  A launch of its own (combine_kernel) costs a kernel boundary and the trip
+// that reads the partials: a step of one sequence (8 pairs of 16 splits) took
+// 19.1 us with it and 17.0 without, 4 sequences of 131k tokens (32 x 8) 30.7 and 29.4, 8 of 32k (64 x 4) 29.3 and 28.9, 16
+// of 32k (128 x 2) 35.1 and 34.7.
+constexpr int kAgentScope = 16;  // cache policy sc1 of the buffer instructions
+
+struct SharedPartials {
+  __amdgpu_buffer_rsrc_t o, m, l;  // the pair's rows: (split * G + h) * d floats of o, split * G + h of m and l
+};
+
+template <int DH>
+__device__ __forceinline__ SharedPartials shared_partials(const Partials& P, int pair, int G) {
+  const size_t row0 = (size_t)pair * P.nsplit * G;
+  const int rows = P.nsplit * G;
+  return SharedPartials{__builtin_amdgcn_make_buffer_rsrc(P.o + row0 * DH, 0, rows * DH * 4, 0x00020000),
+                        __builtin_amdgcn_make_buffer_rsrc(P.m + row0, 0, rows * 4, 0x00020000),
+                        __builtin_amdgcn_make_buffer_rsrc(P.l + row0, 0, rows * 4, 0x00020000)};
+}
+
+// Four channels from c on of row `row`; the thread with the first channels stores m and l too.
+__device__ __forceinline__ void store_split(const SharedPartials& R, int row, int c, int dh, float4 o, float m, float l) {
+  const u32x4 w = {__float_as_uint(o.x), __float_as_uint(o.y), __float_as_uint(o.z), __float_as_uint(o.w)};
+  __builtin_amdgcn_raw_buffer_store_b128(w, R.o, (row * dh + c) * 4, 0, kAgentScope);
+  if (c == 0) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m), R.m, row * 4, 0, kAgentScope);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(l), R.l, row * 4, 0, kAgentScope);
+  }
+}
+
+// Every thread of the workgroup calls this after its store_split calls.  `flag`: a word of LDS outside smem.
+// The threads take 4 channels of a head each, as many times over (`parts`) as the workgroup has threads and smem areas
+// for; part i folds splits i, i + parts, ..., four of them requested at a time, and the parts meet in LDS.
+template <int DH, int WAVES>
+__device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pair, const Partials& P, const Epilogue& E,
+                                            float* smem, int* flag) {
+  constexpr int ROW = DH + 4, Q = DH / 4;  // Q: threads per head
+  constexpr int NTHREADS = WAVES * kWave;
+  const int G = D.G, wstride = G * ROW + 32;
+  __builtin_amdgcn_s_waitcnt(0);  // the partial's stores have been acknowledged
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *flag = (int)__hip_atomic_fetch_add(P.arrived + pair, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*flag) != P.nsplit - 1) return;
+
+  constexpr int kOutPerThread = (16 * DH + NTHREADS - 1) / NTHREADS;
+  HostPart hp[kOutPerThread];
+#pragma unroll
+  for (int t = 0; t < kOutPerThread; ++t) {
+    const int idx = threadIdx.x + t * NTHREADS;
+    const int hh = idx < G * DH ? idx / DH : 0;
+    hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
+  }
+  const int slab = threadIdx.x / Q;                               // below 32
+  const int part = (int)(((uint32_t)slab * P.g_magic) >> 16);     // slab / G
+  const int h = slab - part * G, c = (threadIdx.x % Q) * 4;
+  int parts = (int)(((uint32_t)(NTHREADS / Q) * P.g_magic) >> 16);  // NTHREADS / Q is 16 or 32
+  parts = parts < WAVES ? parts : WAVES;
+  parts = parts < P.nsplit ? parts : P.nsplit;
+  const SharedPartials R = shared_partials<DH>(P, pair, G);
+  if (part < parts) {
+    constexpr int GROUP = 4;
+    float M = -INFINITY, l = 0.0f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = part; s0 < P.nsplit; s0 += GROUP * parts) {
+      u32x4 w[GROUP];
+      float ms[GROUP], ls[GROUP];
+#pragma unroll
+      for (int j = 0; j < GROUP; ++j) {  // rows beyond the last split lie outside the descriptors and read as zeros
+        const int row = (s0 + j * parts) * G + h;
+        w[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(R.o, (row * DH + c) * 4, 0, kAgentScope));
+        ms[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(R.m, row * 4, 0, kAgentScope));
+        ls[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(R.l, row * 4, 0, kAgentScope));
+      }
+      float Mn = M;
+#pragma unroll
+      for (int j = 0; j < GROUP; ++j) {
+        if (s0 + j * parts >= P.nsplit) ms[j] = -INFINITY;
+        Mn = fmaxf(Mn, ms[j]);
+      }
+      const float f0 = exp2_diff(M, Mn);
+      o.x *= f0; o.y *= f0; o.z *= f0; o.w *= f0;
+      l *= f0;
+#pragma unroll
+      for (int j = 0; j < GROUP; ++j) {
+        if (s0 + j * parts < P.nsplit) {
+          const float f = exp2_diff(ms[j], Mn);
+          o.x += f * __uint_as_float(w[j][0]); o.y += f * __uint_as_float(w[j][1]);
+          o.z += f * __uint_as_float(w[j][2]); o.w += f * __uint_as_float(w[j][3]);
+          l += f * ls[j];
+        }
+      }
+      M = Mn;
+    }
+    float* area = smem + (size_t)part * wstride;
+    *reinterpret_cast<float4*>(area + h * ROW + c) = o;
+    if (c == 0) {
+      area[G * ROW + h] = M;
+      area[G * ROW + 16 + h] = l;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kOutPerThread; ++t) {
+    const int idx = threadIdx.x + t * NTHREADS;
+    if (idx >= G * DH) break;
+    const int hh = idx / DH, cc = idx % DH;
+    float M = -INFINITY, o = 0.0f, l = 0.0f;
+    for (int w = 0; w < parts; ++w) M = fmaxf(M, smem[(size_t)w * wstride + G * ROW + hh]);
+    for (int w = 0; w < parts; ++w) {
+      const float* base = smem + (size_t)w * wstride;
+      const float f = exp2_diff(base[G * ROW + hh], M);
+      o += f * base[hh * ROW + cc];
+      l += f * base[G * ROW + 16 + hh];
+    }
+    finish(D, E, b * D.Hq + g * G + hh, cc, o, l, M, hp[t]);
+  }
+}
+
 // The attention of one workgroup: its share (split) of the pair's list, folded over the waves
 // through LDS, then the epilogue.  sel / slot_list: the pair's list in global memory or LDS.
 // PRIVATE: the wave holds its own list entries in registers instead (lane j: the entry of the wave's
 // j-th unit, units dealt to the pair's waves in stride: v, v + waves, ...), fetched by the wave
 // itself in the same trip as the count: no staging through LDS and no barrier before the first tile
 // request.  At most 64 units per wave; sel / slot_list are not read.
-template <int DT, int DH, int WAVES, int DEPTH, bool PRIVATE = false>
+// FOLD: P.nsplit > 1, and the workgroup of a pair that finishes last folds the pair's partials and applies E itself
+// (fold_splits); `flag` is a word of LDS outside smem.
+template <int DT, int DH, int WAVES, int DEPTH, bool PRIVATE = false, bool FOLD = false>
 __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int split,
                                             const QRegs<DT, DH>& qreg,
                                             const void* __restrict__ k_pool,
                                             const void* __restrict__ v_pool, long long n_slots,
                                             const int32_t* sel, const int32_t* slot_list, int n, int ctx,
                                             const Partials& P, const Epilogue& E, float* smem, int my_sel = -1,
-                                            int my_slot = -1) {
+                                            int my_slot = -1, int* flag = nullptr) {
   // per wave: [G][DH + 4] floats of o (padded rows), then m[16], l[16]
   using L = Tile<DT, DH>;
   constexpr int ROW = DH + 4;
@@ -425,7 +551,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   for (int t = 0; t < kOutPerThread; ++t) {
     const int idx = threadIdx.x + t * WAVES * kWave;
     const int hh = idx < G * DH ? idx / DH : 0;
-    hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
+    if constexpr (!FOLD) hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
   }
 
   // fold the waves of the workgroup through LDS
@@ -448,7 +574,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   }
   __syncthreads();
   const size_t pbase = (size_t)pair * P.nsplit + split;
-  if (E.mode == 0) {
+  if (FOLD || E.mode == 0) {
     // partial of this split: four channels per thread, 16-byte LDS reads and one 16-byte store
     for (int item = threadIdx.x; item < G * (DH / 4); item += WAVES * kWave) {
       const int h = item / (DH / 4), c = (item % (DH / 4)) * 4;
@@ -469,12 +595,17 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
         o.x += f * x.x; o.y += f * x.y; o.z += f * x.z; o.w += f * x.w;
         l += f * base[G * ROW + 16 + h];
       }
-      *reinterpret_cast<float4*>(P.o + (pbase * G + h) * DH + c) = o;
-      if (c == 0) {
-        P.m[pbase * G + h] = M;
-        P.l[pbase * G + h] = l;
+      if constexpr (FOLD) {
+        store_split(shared_partials<DH>(P, pair, G), split * G + h, c, DH, o, M, l);
+      } else {
+        *reinterpret_cast<float4*>(P.o + (pbase * G + h) * DH + c) = o;
+        if (c == 0) {
+          P.m[pbase * G + h] = M;
+          P.l[pbase * G + h] = l;
+        }
       }
     }
+    if constexpr (FOLD) fold_splits<DH, WAVES>(D, b, g, pair, P, E, smem, flag);
     return;
   }
 #pragma unroll
@@ -493,15 +624,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
       o += f * base[h * ROW + c];
       l += f * base[G * ROW + 16 + h];
     }
-    if (E.mode == 0) {
-      P.o[(pbase * G + h) * DH + c] = o;
-      if (c == 0) {
-        P.m[pbase * G + h] = M;
-        P.l[pbase * G + h] = l;
-      }
-    } else {
-      finish(D, E, b * D.Hq + g * G + h, c, o, l, M, hp[t]);
-    }
+    finish(D, E, b * D.Hq + g * G + h, c, o, l, M, hp[t]);
   }
 }
 
@@ -660,9 +783,8 @@ __device__ __forceinline__ void touch_hint(const Dims& D, const Hint& h, const P
 // repeats the cheap selection from the scores (integer work on a few KiB of keys), keeps the
 // resident list in LDS and goes straight on to its share of the units; split 0 also writes the
 // lists out, because the host needs to know which selected blocks are its own.
-// SEL_WAVES = 8: all waves share the keys and exchange counts through LDS; SEL_WAVES = 1: one wave
-// holds all keys and selects without a barrier while the others wait (kept for comparison).
-template <int DT, int DH, int SEL_WAVES, int KPL, bool REMAP>
+// FOLD: several splits per pair, folded in this launch (P.arrived).
+template <int DT, int DH, int KPL, bool REMAP, bool FOLD>
 __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     Dims D, const void* __restrict__ q, const float* __restrict__ scores,
     const int32_t* __restrict__ table, const void* __restrict__ k_pool,
@@ -689,18 +811,18 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
   uint32_t touched_k = 0, touched_v = 0;
 
-  if (SEL_WAVES == WAVES || wave == 0) {  // wave-uniform
-    const int sw = SEL_WAVES == WAVES ? wave : 0;
+  {
+    const int sw = wave;
     int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;
     nb = nb < D.max_blocks ? nb : D.max_blocks;
     const int k_eff = D.k < nb ? D.k : nb;
     uint32_t key[KPL];
     int slot[KPL];
-    load_keys<SEL_WAVES, KPL>(D, scores, table, pair, nb, sw, lane, key, slot);
+    load_keys<WAVES, KPL>(D, scores, table, pair, nb, sw, lane, key, slot);
     __builtin_amdgcn_sched_barrier(0);
     touch_hint<DT, DH, WAVES>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
     __builtin_amdgcn_sched_barrier(0);
-    Selector<SEL_WAVES, KPL> S{l_x, 0, sw};
+    Selector<WAVES, KPL> S{l_x, 0, sw};
     uint32_t sel = 0;
     if (k_eff > 0) sel = S.best(key, k_eff, false);
     uint32_t gpu = 0;
@@ -731,7 +853,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     }
     const int tid = sw * kWave + lane;
     if (writer) {
-      for (int t = tid; t < D.k; t += SEL_WAVES * kWave) {
+      for (int t = tid; t < D.k; t += WAVES * kWave) {
         if (t >= k_eff) sel_all[out0 + t] = -1;
         if (t >= ng) {
           sel_gpu[out0 + t] = -1;
@@ -747,7 +869,8 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     if (tid == 0) l_n[0] = ng;
   }
   __syncthreads();
-  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>()>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P,
+                                                                E, smem, -1, -1, l_n + 1);
   asm volatile("" ::"v"(touched_k), "v"(touched_v));  // the touches stay loads, their registers reserved until they have returned
 }
 
@@ -1199,14 +1322,14 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
   dim3 grid(P.nsplit, D.Hkv, D.B), block(8 * kWave);
   const bool remap = xcd_grid(D, P.nsplit, grid);
   const size_t lds = mfma_smem_bytes(D, 8) + (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4) * sizeof(int);
-#define SCOUT_SA(DT, DH, KPL)                                                                                     \
-  do {                                                                                                            \
-    if (remap)                                                                                                    \
-      hipLaunchKernelGGL((select_attend_kernel<DT, DH, 8, KPL, true>), grid, block, lds, st, D, q, scores, table, \
-                         k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E);     \
-    else                                                                                                          \
-      hipLaunchKernelGGL((select_attend_kernel<DT, DH, 8, KPL, false>), grid, block, lds, st, D, q, scores, table,\
-                         k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E);     \
+#define SCOUT_SA_RUN(DT, DH, KPL, REMAP, FOLD)                                                                     \
+  hipLaunchKernelGGL((select_attend_kernel<DT, DH, KPL, REMAP, FOLD>), grid, block, lds, st, D, q, scores, table, \
+                     k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)
+#define SCOUT_SA(DT, DH, KPL)                                                      \
+  do {                                                                             \
+    if (remap) SCOUT_SA_RUN(DT, DH, KPL, true, false);                             \
+    else if (P.arrived != nullptr) SCOUT_SA_RUN(DT, DH, KPL, false, true);         \
+    else SCOUT_SA_RUN(DT, DH, KPL, false, false);                                  \
   } while (0)
   // All eight waves share the keys: measured faster than one wave selecting alone while seven wait
   // (46.9 vs 44.1 us per step at 1024 blocks per pair), a lone wave issues too slowly.
@@ -1222,6 +1345,7 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
   SCOUT_BY_TYPE(dtype, D.d, SCOUT_SA_TYPE);
 #undef SCOUT_SA_TYPE
 #undef SCOUT_SA
+#undef SCOUT_SA_RUN
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 

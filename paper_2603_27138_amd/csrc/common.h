@@ -37,6 +37,9 @@ struct Partials {
   float* l;
   int nsplit;
   uint32_t waves_magic;  // MFMA family: ceil(2^32 / (nsplit * waves per workgroup)), 0 if that is 1
+  uint32_t* arrived;     // [pairs], zero before the launch: splits of the pair whose partial is stored; null where the
+                         // partials are folded by a launch of their own
+  uint32_t g_magic;      // ceil(2^16 / G): x / G for x < 32 without a division
 };
 
 // What happens to a finished (sequence, query head) result.

@@ -236,7 +236,7 @@ constexpr int kScoreBatches = 1;    // batches per wave (with more than one, two
 // coefficient vector instead of two and a division by the block's token count at the end.
 template <int DT, int DH, bool MEAN>
 __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
-    Dims D, const void* q, const void* digest, float* scores) {
+    Dims D, const void* q, const void* digest, float* scores, uint32_t* arrived) {
   constexpr bool DIG16 = DT == SCOUT_BF16 && !MEAN;  // digest elements are bf16
   constexpr int EPL = DIG16 ? 8 : 4;               // digest elements per 16-byte load
   constexpr int ESZ = (DT == SCOUT_BF16) ? 2 : 4;  // bytes per query element
@@ -255,6 +255,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nb = num_blocks_of(D, b);
+  if (arrived != nullptr && blockIdx.x == 0 && threadIdx.x == 0) arrived[pair] = 0;  // see launch_score
   const int j_wave = (blockIdx.x * kScoreWaves + wave) * BLK_PER_WAVE;
   const bool active = j_wave < D.max_blocks;  // a wave past the row still helps with the fold
 
@@ -414,7 +415,7 @@ constexpr int score_max_entries(int lines) { return 16 / lines < 4 ? 16 / lines 
 // one pass over the KV head's digests serves its G query heads), instead of their maximum into the KV head's row.
 template <int DT, int DH, int HC, bool ROWS>
 __global__ __launch_bounds__(kScoreWaves* kWave) void score_max_kernel(Dims D, const void* q, const void* digest,
-                                                                      float* scores) {
+                                                                      float* scores, uint32_t* arrived) {
   constexpr int EPL = (DT == SCOUT_BF16) ? 8 : 4;   // elements per 16-byte load
   constexpr int ESZ = (DT == SCOUT_BF16) ? 2 : 4;
   constexpr int EB = 2 * DH * ESZ;                  // bytes per digest entry
@@ -445,6 +446,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_max_kernel(Dims D, c
   const int j_wave = (blockIdx.x * kScoreWaves + wave) * BLK_PER_WAVE;
   const bool active = j_wave < D.max_blocks;
   const int n_rows = ROWS ? D.G : 1;  // rows of `scores` per pair
+  if (arrived != nullptr && blockIdx.x == 0 && (int)threadIdx.x < n_rows) arrived[pair * n_rows + threadIdx.x] = 0;
   if ((int)blockIdx.x * kScoreWaves * BLK_PER_WAVE >= nb) {  // as in score_kernel: only the rows' tails to mark
     for (int t = threadIdx.x; t < kScoreWaves * BLK_PER_WAVE; t += NT) {
       const int j = (int)blockIdx.x * kScoreWaves * BLK_PER_WAVE + t;
@@ -615,47 +617,48 @@ int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, 
 
 template <int HC, bool ROWS>
 static int launch_score_max_hc(const Dims& D, int dtype, const void* q, const void* digest, float* scores,
-                               hipStream_t st) {
+                               uint32_t* arrived, hipStream_t st) {
   const int lines = 2 * D.d * (dtype == SCOUT_BF16 ? 2 : 4) / 128;
   const int blocks_per_wg = score_max_entries(lines) * 8 * kScoreWaves;  // 8 entries per wave-wide load
   dim3 grid((D.max_blocks + blocks_per_wg - 1) / blocks_per_wg, D.Hkv, D.B);
   dim3 block(kScoreWaves * kWave);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
   if (dtype == SCOUT_BF16 && D.d == 128)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_BF16, 128, HC, ROWS>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_max_kernel<SCOUT_BF16, 128, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
   else if (dtype == SCOUT_BF16 && D.d == 64)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_BF16, 64, HC, ROWS>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_max_kernel<SCOUT_BF16, 64, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
   else if (dtype == SCOUT_F32 && D.d == 128)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_F32, 128, HC, ROWS>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_max_kernel<SCOUT_F32, 128, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
   else if (dtype == SCOUT_F32 && D.d == 64)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_F32, 64, HC, ROWS>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_max_kernel<SCOUT_F32, 64, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
   else
     return SCOUT_EUNSUPPORTED;
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
-int launch_score_max(const Dims& D, int dtype, const void* q, const void* digest, float* scores, hipStream_t st) {
+static int launch_score_max(const Dims& D, int dtype, const void* q, const void* digest, float* scores, uint32_t* arrived,
+                            hipStream_t st) {
   // groups of 5 to 8 heads in one pass of eight, every other size in passes of four
-  if (D.G > 4 && D.G <= 8) return launch_score_max_hc<8, false>(D, dtype, q, digest, scores, st);
-  return launch_score_max_hc<4, false>(D, dtype, q, digest, scores, st);
+  if (D.G > 4 && D.G <= 8) return launch_score_max_hc<8, false>(D, dtype, q, digest, scores, arrived, st);
+  return launch_score_max_hc<4, false>(D, dtype, q, digest, scores, arrived, st);
 }
 
 // A selection per query head (D describes every query head as a pair of its own that shares its KV head's
 // rows): the same kernel over the KV heads, every head's estimate to its own row.
 static int launch_score_rows(const Dims& D, int dtype, const void* q, const void* digest, float* scores,
-                             hipStream_t st) {
+                             uint32_t* arrived, hipStream_t st) {
   Dims K = D;
   K.G = D.share;
   K.Hkv = D.Hkv / D.share;
   K.share = 1;
   K.share_magic = 0;
-  if (K.G > 4 && K.G <= 8) return launch_score_max_hc<8, true>(K, dtype, q, digest, scores, st);
-  return launch_score_max_hc<4, true>(K, dtype, q, digest, scores, st);
+  if (K.G > 4 && K.G <= 8) return launch_score_max_hc<8, true>(K, dtype, q, digest, scores, arrived, st);
+  return launch_score_max_hc<4, true>(K, dtype, q, digest, scores, arrived, st);
 }
 
 template <bool MEAN>
 static int launch_score_sum(const Dims& D, int dtype, const void* q, const void* digest, float* scores,
-                            hipStream_t st) {
+                            uint32_t* arrived, hipStream_t st) {
   const int entry_bytes = MEAN ? D.d * 4 : 2 * D.d * (dtype == SCOUT_BF16 ? 2 : 4);
   const int lines = entry_bytes / 128;  // 128-byte lines per digest entry
   const int blocks_per_wg = kScoreBatch / lines * 8 * kScoreBatches * kScoreWaves;
@@ -663,24 +666,26 @@ static int launch_score_sum(const Dims& D, int dtype, const void* q, const void*
   dim3 block(kScoreWaves * kWave);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
   if (dtype == SCOUT_BF16 && D.d == 128)
-    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 128, MEAN>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
   else if (dtype == SCOUT_BF16 && D.d == 64)
-    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 64, MEAN>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
   else if (dtype == SCOUT_F32 && D.d == 128)
-    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 128, MEAN>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
   else if (dtype == SCOUT_F32 && D.d == 64)
-    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 64, MEAN>), grid, block, 0, st, D, q, digest, scores);
+    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
   else
     return SCOUT_EUNSUPPORTED;
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
-int launch_score(const Dims& D, int dtype, const void* q, const void* digest, float* scores,
+// arrived: null, or a word per pair that the launch leaves at zero, for the launch that attends to these scores
+// (Partials::arrived).
+int launch_score(const Dims& D, int dtype, const void* q, const void* digest, float* scores, uint32_t* arrived,
                  hipStream_t st) {
-  if (D.digest_kind == 1) return D.group_max ? SCOUT_EUNSUPPORTED : launch_score_sum<true>(D, dtype, q, digest, scores, st);
-  if (D.group_max) return launch_score_max(D, dtype, q, digest, scores, st);
-  if (D.share > 1) return launch_score_rows(D, dtype, q, digest, scores, st);
-  return launch_score_sum<false>(D, dtype, q, digest, scores, st);
+  if (D.digest_kind == 1) return D.group_max ? SCOUT_EUNSUPPORTED : launch_score_sum<true>(D, dtype, q, digest, scores, arrived, st);
+  if (D.group_max) return launch_score_max(D, dtype, q, digest, scores, arrived, st);
+  if (D.share > 1) return launch_score_rows(D, dtype, q, digest, scores, arrived, st);
+  return launch_score_sum<false>(D, dtype, q, digest, scores, arrived, st);
 }
 
 }  // namespace scout

@@ -29,7 +29,8 @@ int launch_select_attend(const Dims&, int, const void*, const float*, const int3
                          long long, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, Partials,
                          Epilogue, hipStream_t);
 bool step_kernel_supported(const Dims&, int);
-int launch_step(const Dims&, const void*, const void*, const int32_t*, const void*, const void*, long long, float*,
+bool step_kernel_small(const Dims&, int);
+int launch_step(const Dims&, int, const void*, const void*, const int32_t*, const void*, const void*, long long, float*,
                 int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, Partials, Epilogue, hipStream_t);
 int launch_merge(const Dims&, int, const float*, const float*, const float*, const float*,
                  const float*, const float*, void*, float*, hipStream_t);
@@ -558,9 +559,12 @@ int scout_layer_step(const scout_problem* p, const void* q, const void* digest,
   E.out = out;
   E.lse = lse;
   E.dtype_out = p->dtype;
-  if (g_fuse_select && g_fuse_step && A.family == 2 && A.waves == 8 && A.nsplit == 1 && step_kernel_supported(D, p->dtype))
-    // the pairs alone fill the chip: the whole step of a pair in one workgroup, one launch
-    return launch_step(D, q, digest, block_table, k_pool, v_pool, n_slots, scores, sel_all, sel_gpu, slot_gpu, n_gpu,
+  if (g_fuse_step && g_nsplit == 0 && A.family == 2 && A.waves == 8 && step_kernel_small(D, p->dtype)) A.nsplit = 1;
+  if (g_fuse_select && g_fuse_step && A.family == 2 && A.waves == 8 && A.nsplit == 1 &&
+      (step_kernel_supported(D, p->dtype) || step_kernel_small(D, p->dtype)))
+    // the pairs alone fill the chip, or have too little to read for more: the whole step of a pair in one workgroup,
+    // one launch
+    return launch_step(D, p->dtype, q, digest, block_table, k_pool, v_pool, n_slots, scores, sel_all, sel_gpu, slot_gpu, n_gpu,
                        sel_host, n_host, carve(ws, L, A), E, st);
   if (scores == nullptr) scores = reinterpret_cast<float*>(static_cast<char*>(ws) + L.scores);
   if (g_fuse_select && A.family == 2 && A.waves == 8 && select_attend_supported(D)) {

@@ -18,6 +18,7 @@
 //                     registers (no LDS), in units of 16 tokens.
 //   attn_valu_kernel  plain vector ALU; only where the caller asks for it (scout_set_attn_mode).
 // combine_kernel folds the splits (and optionally the host partial) together.
+#include "score_tile.h"
 #include "select.h"
 
 namespace scout {
@@ -34,7 +35,6 @@ __device__ __forceinline__ float exp2_diff(float a, float b) {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -876,27 +876,25 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
 
 // The whole layer-step of a pair in one launch (the non-pipelined sequence of Sec. 3.2: score every
 // block against its digest, keep the top-k, attend to the resident ones, merge with the host's
-// partial), for launches in which the pairs alone fill the chip (one workgroup per pair, nothing to
-// combine afterwards).  The workgroup streams the pair's digest rows, keeps the scores as selection
+// partial), one workgroup per pair, nothing to combine afterwards: where the pairs alone fill the chip, and where a
+// pair has so little to read that a second launch costs more than it brings (see step_kernel_supported).
+// The workgroup streams the pair's digest rows, keeps the scores as selection
 // keys in LDS (they go to global memory only if the caller wants them), selects, and goes on to the
-// attention without a second launch or a trip of the scores through HBM.  bf16, d = 128, min/max
+// attention without a second launch or a trip of the scores through HBM.  Min/max
 // digests, the group's heads summed.
 //
-// Scoring repeats score_kernel's arithmetic operation for operation (the same stream layout, the same
-// order of the binary64 FMAs, the same three exchange steps), so a score has the same bits whichever
-// kernel made it.  A wave keeps one batch of 16 blocks (8 KiB) in flight, the next requested as soon
+// Scoring is ScoreTile's, as in score_kernel, so a score has the same bits whichever
+// kernel made it.  A wave keeps one batch (8 KiB) in flight, the next requested as soon
 // as one is scored (two or four in flight measured the same: 62.8, 62.0 against 62.2 us at batch 32).
-constexpr int kStepBatch = 8;         // wave-wide loads per batch: 16 blocks
-constexpr int kStepEntryBytes = 512;  // one digest entry: min row and max row of 128 bf16
-
-template <int KPL>
+template <int DT, int DH, int KPL>
 __global__ __launch_bounds__(8 * kWave) void step_kernel(
-    Dims D, const uint16_t* q, const char* digest, const int32_t* __restrict__ table,
+    Dims D, const void* q, const char* digest, const int32_t* __restrict__ table,
     const void* __restrict__ k_pool, const void* __restrict__ v_pool, long long n_slots,
     float* scores, int32_t* __restrict__ sel_all, int32_t* __restrict__ sel_gpu,
     int32_t* __restrict__ slot_gpu, int32_t* __restrict__ n_gpu, int32_t* __restrict__ sel_host,
     int32_t* __restrict__ n_host, Partials P, Epilogue E) {
-  constexpr int WAVES = 8, DT = SCOUT_BF16, DH = 128;
+  using T = ScoreTile<DT, DH, false>;
+  constexpr int WAVES = 8;
   extern __shared__ float smem[];
   const int b = blockIdx.z, g = blockIdx.y, pair = grid_pair();
   const int lane = lane_id();
@@ -907,7 +905,7 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
   int* l_x = l_slot + kpad;
   int* l_n = l_x + selector_lds_ints<WAVES>();
   uint32_t* l_key = reinterpret_cast<uint32_t*>(l_n + 4);                       // [WAVES * 64 * KPL]
-  double* coef_lds = reinterpret_cast<double*>(l_key + WAVES * kWave * KPL);    // [2][128]: N_c, P_c
+  double* coef_lds = reinterpret_cast<double*>(l_key + WAVES * kWave * KPL);    // [2][DH]: N_c, P_c
 
   // table entries of the elements this thread will hold in the selection: requested first, used last
   const size_t trow = (size_t)kv_row(D, pair) * D.max_blocks;
@@ -917,33 +915,30 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     const int i = (wave * KPL + r) * kWave + lane;
     slot[r] = table[trow + (i < D.max_blocks ? i : D.max_blocks - 1)];
   }
-  // the group's queries: thread t < 256 folds channel t % 128, negative (t < 128) or positive parts
+  // the group's queries: thread t < 2 * DH folds channel t % DH, negative (t < DH) or positive parts
   const int fc = threadIdx.x & (DH - 1);
   const bool fpos = threadIdx.x >= DH;
-  const uint16_t* qbase = q + ((size_t)b * D.Hq + g * D.G) * DH + fc;
+  const size_t q0 = ((size_t)b * D.Hq + g * D.G) * DH + fc;
   float qv[16];
   if (threadIdx.x < 2 * DH) {
 #pragma unroll
-    for (int h = 0; h < 16; ++h) qv[h] = bf16_bits_to_f32(qbase[(size_t)(h < D.G ? h : D.G - 1) * DH]);
+    for (int h = 0; h < 16; ++h) qv[h] = load1<DT>(q, q0 + (size_t)(h < D.G ? h : D.G - 1) * DH);
   }
   const int ctx = D.ctx_len[b];
   int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;
   nb = nb < D.max_blocks ? nb : D.max_blocks;
 
-  const char* dpair = digest + trow * kStepEntryBytes;
+  const char* dpair = digest + trow * T::EB;
   const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(dpair), 0, nb * kStepEntryBytes, 0x00020000);
-  const int n_batches = (nb + 15) >> 4;
-  // byte offset of load `it` of the batch that starts at block j0: group it / 4, line it % 4 of its entries
-  const int voff0 = (lane >> 3) * kStepEntryBytes + (lane & 7) * 16;
-  auto load_batch = [&](u32x4(&dst)[kStepBatch], int batch) {
-    const int base = batch < n_batches ? batch * 16 * kStepEntryBytes + voff0 : nb * kStepEntryBytes;  // beyond: reads zeros
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(dpair), 0, nb * T::EB, 0x00020000);
+  const int n_batches = (nb + T::BLOCKS - 1) / T::BLOCKS;
+  auto load_batch = [&](u32x4(&dst)[kScoreBatch], int batch) {
+    const int base = (batch < n_batches ? batch * T::BLOCKS : nb) * T::EB;  // beyond: reads zeros
 #pragma unroll
-    for (int it = 0; it < kStepBatch; ++it)
-      dst[it] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, base + (it >> 2) * 8 * kStepEntryBytes + (it & 3) * 128, 0, 0));
+    for (int it = 0; it < kScoreBatch; ++it)
+      dst[it] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, base + T::offset(lane, it), 0, 0));
   };
-  u32x4 raw[kStepBatch];
+  u32x4 raw[kScoreBatch];
   load_batch(raw, wave);
 
   if (threadIdx.x < 2 * DH) {
@@ -954,43 +949,18 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     coef_lds[(fpos ? DH : 0) + fc] = f;
   }
   // rows of the key array that no batch will write
-  for (int i = n_batches * 16 + threadIdx.x; i < WAVES * kWave * KPL; i += WAVES * kWave) l_key[i] = 0u;
+  for (int i = n_batches * T::BLOCKS + threadIdx.x; i < WAVES * kWave * KPL; i += WAVES * kWave) l_key[i] = 0u;
   __syncthreads();
-  double coef[4][8];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) coef[u][i] = coef_lds[(u >= 2 ? DH : 0) + (u & 1) * 64 + (lane & 7) * 8 + i];
+  double coef[T::NL][T::EPL];
+  T::coefficients(coef, coef_lds, lane);
 
-  const bool hi2 = (lane >> 2) & 1;
   const size_t srow = (size_t)pair * D.max_blocks;
-  // scores of the 16 blocks of one batch from its eight loads; a batch beyond the last one holds zeros
+  // scores of the blocks of one batch from its eight loads; a batch beyond the last one holds zeros
   // and only marks rows beyond the sequence
-  auto score_batch = [&](const u32x4(&cur)[kStepBatch], int batch) {
-    double a[2];
-#pragma unroll
-    for (int gq = 0; gq < 2; ++gq) {
-      double acc = 0.0;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const u32x4 w = cur[gq * 4 + u];
-        acc = fma(coef[u][0], (double)bf16_lo(w[0]), acc);
-        acc = fma(coef[u][1], (double)bf16_hi(w[0]), acc);
-        acc = fma(coef[u][2], (double)bf16_lo(w[1]), acc);
-        acc = fma(coef[u][3], (double)bf16_hi(w[1]), acc);
-        acc = fma(coef[u][4], (double)bf16_lo(w[2]), acc);
-        acc = fma(coef[u][5], (double)bf16_hi(w[2]), acc);
-        acc = fma(coef[u][6], (double)bf16_lo(w[3]), acc);
-        acc = fma(coef[u][7], (double)bf16_hi(w[3]), acc);
-      }
-      a[gq] = acc;
-    }
-    const double keep = hi2 ? a[1] : a[0], send = hi2 ? a[0] : a[1];
-    double sc = keep + partner_f64<2>(send);
-    sc += partner_f64<1>(sc);
-    sc += partner_f64<0>(sc);
-    const int j = batch * 16 + (hi2 ? 8 : 0) + (lane >> 3);
-    if ((lane & 3) == 0) {
+  auto score_batch = [&](const u32x4(&cur)[kScoreBatch], int batch) {
+    const double sc = T::scores(cur, coef, lane);
+    const int j = batch * T::BLOCKS + T::entry(lane);
+    if (T::writer(lane)) {
       const bool kept = j < D.n_sink || j >= nb - D.n_tail;  // always-kept blocks rank above every score
       const float val = j < nb ? (kept ? INFINITY : (float)sc) : -INFINITY;
       if (j < WAVES * kWave * KPL) l_key[j] = j < nb ? score_key(val) : 0u;
@@ -1002,7 +972,7 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     load_batch(raw, batch + WAVES);
   }
   if (scores != nullptr)  // the row's tail beyond the last batch
-    for (int j = n_batches * 16 + threadIdx.x; j < D.max_blocks; j += WAVES * kWave) scores[srow + j] = -INFINITY;
+    for (int j = n_batches * T::BLOCKS + threadIdx.x; j < D.max_blocks; j += WAVES * kWave) scores[srow + j] = -INFINITY;
 
   QRegs<DT, DH> qreg;
   load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
@@ -1056,7 +1026,7 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     l_n[0] = ng;
   }
   __syncthreads();
-  attend_pair<DT, DH, WAVES, 1>(D, b, g, 0, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>()>(D, b, g, 0, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
 }
 
 // ---------------------------------------------------------------- VALU family
@@ -1349,17 +1319,34 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
-// One workgroup streams its pair's whole digest row: worth it while a row is short enough that one
-// long sequence among short ones cannot hold the launch up for long (2048 blocks = 1 MiB of digest).
-bool step_kernel_supported(const Dims& D, int dtype) {
+static bool step_kernel_takes(const Dims& D) {
   // (with a selection per query head the scoring pass of its own serves the G heads of a row in one reading)
-  return dtype == SCOUT_BF16 && D.d == 128 && select_attend_supported(D) && D.digest_kind == 0 && D.group_max == 0 && D.share == 1 &&
-         D.max_blocks <= 2048;
+  return D.digest_kind == 0 && D.group_max == 0 && D.share == 1;
+}
+
+// Pairs that alone fill the chip.  One workgroup streams its pair's whole digest row: worth it while a row is short
+// enough that one long sequence among short ones cannot hold the launch up for long (2048 blocks = 1 MiB of digest).
+bool step_kernel_supported(const Dims& D, int dtype) {
+  return step_kernel_takes(D) && dtype == SCOUT_BF16 && D.d == 128 && D.max_blocks <= 2048;
+}
+
+// Pairs with so little to read that one workgroup is done with it before the second launch of a split pair has begun:
+// at most 128 KiB of digests, 512 listed tokens (four units per wave) and 288 KiB of both, whatever the number of pairs.
+// Measured, a layer, one launch against scoring plus split attention, three quarters of the list resident: fp32, d = 64,
+// 1 pair of 128 blocks of 16 with k = 16: 9.2 against 11.3 us; bf16, d = 64, 64 pairs of 512 blocks with k = 32: 12.3 against 13.6; bf16,
+// d = 128, 64 pairs of 256 blocks of 16 with k = 16 (256 KiB): 12.9 against 13.7; with 32 units per pair (16 KiB of
+// digests, 272 KiB) 11.2 against 12.8, 64 KiB of digests (320 KiB) 13.6 against 13.7, 128 KiB 14.9 against 14.2; fp32,
+// d = 128, 16 units (288 KiB) 13.2 against 14.4, 32 units 16.1 against 16.1 and 18.8 against 16.7.
+constexpr int kSmallDigestBytes = 128 << 10, kSmallTokens = 512, kSmallBytes = 288 << 10;
+bool step_kernel_small(const Dims& D, int dtype) {
+  const int row_bytes = 2 * D.d * (dtype == SCOUT_BF16 ? 2 : 4);  // of a token's K and V, and of a digest entry
+  return step_kernel_takes(D) && D.max_blocks * row_bytes <= kSmallDigestBytes && D.k * D.S <= kSmallTokens &&
+         (D.max_blocks + D.k * D.S) * row_bytes <= kSmallBytes;
 }
 
 // Scoring, selection, attention and merge of every pair in one launch, one workgroup per pair
 // (P.nsplit must be 1, E.mode 2).  `scores` may be null.
-int launch_step(const Dims& D, const void* q, const void* digest, const int32_t* table, const void* k_pool,
+int launch_step(const Dims& D, int dtype, const void* q, const void* digest, const int32_t* table, const void* k_pool,
                 const void* v_pool, long long n_slots, float* scores, int32_t* sel_all, int32_t* sel_gpu,
                 int32_t* slot_gpu, int32_t* n_gpu, int32_t* sel_host, int32_t* n_host, Partials P, Epilogue E,
                 hipStream_t st) {
@@ -1370,18 +1357,21 @@ int launch_step(const Dims& D, const void* q, const void* digest, const int32_t*
   const int kpl = per_lane <= 2 ? 2 : per_lane <= 4 ? 4 : per_lane <= 8 ? 8 : 16;
   const size_t lds = mfma_smem_bytes(D, 8) +
                      (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4 + 8 * kWave * kpl) * sizeof(int) +
-                     2 * 128 * sizeof(double);
-  const uint16_t* q16 = static_cast<const uint16_t*>(q);
+                     2 * D.d * sizeof(double);
   const char* dg = static_cast<const char*>(digest);
-#define SCOUT_STEP(KPL)                                                                                      \
-  hipLaunchKernelGGL((step_kernel<KPL>), grid, block, lds, st, D, q16, dg, table, k_pool, v_pool, n_slots, scores, \
+#define SCOUT_STEP(DT, DH, KPL)                                                                              \
+  hipLaunchKernelGGL((step_kernel<DT, DH, KPL>), grid, block, lds, st, D, q, dg, table, k_pool, v_pool, n_slots, scores, \
                      sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)
-  if (kpl == 2)
-    SCOUT_STEP(2);
-  else if (kpl == 4)
-    SCOUT_STEP(4);
-  else  // rows beyond 2048 blocks: see step_kernel_supported
-    return SCOUT_EUNSUPPORTED;
+#define SCOUT_STEP_TYPE(DT, DH)                \
+  do {                                         \
+    if (kpl != 2) return SCOUT_EUNSUPPORTED;   \
+    SCOUT_STEP(DT, DH, 2);                     \
+  } while (0)
+  if (kpl == 4 && dtype == SCOUT_BF16 && D.d == 128)  // rows beyond 2048 blocks: see step_kernel_supported
+    SCOUT_STEP(SCOUT_BF16, 128, 4);
+  else
+    SCOUT_BY_TYPE(dtype, D.d, SCOUT_STEP_TYPE);
+#undef SCOUT_STEP_TYPE
 #undef SCOUT_STEP
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }

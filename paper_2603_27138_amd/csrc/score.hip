@@ -10,7 +10,7 @@
 // whatever G is.  The pass is a pure stream over the digest cache (HBM-bound);
 // accumulation is binary64 so the binary32 result is the correctly rounded
 // score except for ties of the last binary64 bit.
-#include "common.h"
+#include "score_tile.h"
 
 namespace scout {
 
@@ -38,8 +38,6 @@ struct DigestTile {
 // lower: the value of the group with the earlier tokens
 __device__ __forceinline__ float first_min(float lower, float higher) { return higher < lower ? higher : lower; }
 __device__ __forceinline__ float first_max(float lower, float higher) { return higher > lower ? higher : lower; }
-
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 template <bool NT>
 __device__ __forceinline__ u32x4 load_key(const u32x4* p) {
@@ -208,15 +206,11 @@ __global__ __launch_bounds__(256) void digest_rows_kernel(Dims D, const void* __
 // ------------------------------------------------------------------- score
 
 constexpr int kScoreWaves = 4;      // waves per workgroup
-constexpr int kScoreBatch = 8;      // wave-wide loads per batch
-constexpr int kScoreBatches = 1;    // batches per wave (with more than one, two are kept in flight)
 
 // The score of a block is sum_c P_c*max_j[c] + N_c*min_j[c], with P_c (N_c) the sum over the group's
 // query heads of the positive (negative) parts of q[c]: the group is folded before the stream.
 //
-// Stream layout: a wave-wide load takes one 128-byte line from each of 8 consecutive digest entries
-// (8 lanes x 16 bytes per entry), and NL such loads cover the entries whole.  A lane therefore adds
-// the products of NL loads into one partial sum, and only the 8 lanes of an entry remain to be added
+// Stream layout: ScoreTile.  A lane adds the products of the NL loads of an entry into one partial sum, and only the 8 lanes of an entry remain to be added
 // across lanes: three DPP steps.  Where a batch of kScoreBatch loads holds several 8-entry groups,
 // the first steps exchange half of the remaining sums each instead of adding all of them everywhere.
 // A wave takes one batch, all of it requested at once: many small waves (8192 at 128 pairs x 1024
@@ -237,16 +231,11 @@ constexpr int kScoreBatches = 1;    // batches per wave (with more than one, two
 template <int DT, int DH, bool MEAN>
 __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
     Dims D, const void* q, const void* digest, float* scores, uint32_t* arrived) {
-  constexpr bool DIG16 = DT == SCOUT_BF16 && !MEAN;  // digest elements are bf16
-  constexpr int EPL = DIG16 ? 8 : 4;               // digest elements per 16-byte load
+  using T = ScoreTile<DT, DH, MEAN>;
   constexpr int ESZ = (DT == SCOUT_BF16) ? 2 : 4;  // bytes per query element
-  constexpr int DSZ = DIG16 ? 2 : 4;               // bytes per digest element
-  constexpr int EB = (MEAN ? 1 : 2) * DH * DSZ;    // bytes per digest entry
-  constexpr int NL = EB / 128;                     // 128-byte lines per entry
-  constexpr int NG = kScoreBatch / NL;             // 8-entry groups per batch
-  constexpr int BLK_PER_WAVE = NG * 8 * kScoreBatches;
+  constexpr int EB = T::EB, BLK_PER_WAVE = T::BLOCKS;
   constexpr int NT = kScoreWaves * kWave;
-  static_assert(NL >= 2 && NL <= kScoreBatch && 2 * DH <= NT, "layout");
+  static_assert(2 * DH <= NT, "layout");
 
   __shared__ __align__(16) double coef_lds[2][DH];  // [0]: N_c (goes with the min row), [1]: P_c
 
@@ -284,19 +273,12 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   const char* dpair = static_cast<const char*>(digest) + (size_t)kv_row(D, pair) * D.max_blocks * EB;
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(dpair), 0, active ? nb * EB : 0, 0x00020000);
-  const int voff0 = (j_wave + (lane >> 3)) * EB + (lane & 7) * 16;
-  // byte offset of load `it` of batch `t`: group it / NL of the batch, line it % NL of its entries
-  auto load_off = [&](int t, int it) { return voff0 + (t * NG + it / NL) * 8 * EB + (it % NL) * 128; };
-
-  u32x4 raw[kScoreBatches < 2 ? 1 : 2][kScoreBatch];
+  u32x4 raw[kScoreBatch];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int t = 0; t < (kScoreBatches < 2 ? kScoreBatches : 2); ++t) {
-#pragma unroll
-    for (int it = 0; it < kScoreBatch; ++it)
-      raw[t][it] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, load_off(t, it), 0, 0));
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  for (int it = 0; it < kScoreBatch; ++it)
+    raw[it] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, j_wave * EB + T::offset(lane, it), 0, 0));
+  __builtin_amdgcn_sched_barrier(0);
 
   {
     double f = 0.0;
@@ -306,84 +288,18 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
     if (threadIdx.x < 2 * DH) coef_lds[fpos ? 1 : 0][fc] = f;  // MEAN: both rows hold the plain sum
   }
   __syncthreads();
-  // line u of an entry: min row for u < NL/2, max row after (MEAN: the one row of sums);
-  // channels (u % lines per row) * 128/DSZ + 8 lanes x EPL
-  constexpr int LPR = MEAN ? NL : NL / 2;  // lines per digest row
-  double coef[NL][EPL];
-#pragma unroll
-  for (int u = 0; u < NL; ++u)
-#pragma unroll
-    for (int i = 0; i < EPL; ++i)
-      coef[u][i] = coef_lds[u >= LPR ? 1 : 0][(u % LPR) * (128 / DSZ) + (lane & 7) * EPL + i];
-
-  const bool hi2 = (lane >> 2) & 1, hi1 = (lane >> 1) & 1;
-  const int my_g = NG == 4 ? (hi2 ? 2 : 0) + (hi1 ? 1 : 0) : NG == 2 ? (hi2 ? 1 : 0) : 0;
-  const bool writer = NG == 4 ? (lane & 1) == 0 : NG == 2 ? (lane & 3) == 0 : (lane & 7) == 0;
-
-#pragma unroll
-  for (int t = 0; t < kScoreBatches; ++t) {
-    u32x4(&cur)[kScoreBatch] = raw[t & 1];
-    double a[NG];
-#pragma unroll
-    for (int gq = 0; gq < NG; ++gq) {
-      double acc = 0.0;
-#pragma unroll
-      for (int u = 0; u < NL; ++u) {
-        const u32x4 w = cur[gq * NL + u];
-        if (DIG16) {
-          acc = fma(coef[u][0], (double)bf16_lo(w[0]), acc);
-          acc = fma(coef[u][1], (double)bf16_hi(w[0]), acc);
-          acc = fma(coef[u][2 % EPL], (double)bf16_lo(w[1]), acc);
-          acc = fma(coef[u][3 % EPL], (double)bf16_hi(w[1]), acc);
-          acc = fma(coef[u][4 % EPL], (double)bf16_lo(w[2]), acc);
-          acc = fma(coef[u][5 % EPL], (double)bf16_hi(w[2]), acc);
-          acc = fma(coef[u][6 % EPL], (double)bf16_lo(w[3]), acc);
-          acc = fma(coef[u][7 % EPL], (double)bf16_hi(w[3]), acc);
-        } else {
-          acc = fma(coef[u][0], (double)__uint_as_float(w[0]), acc);
-          acc = fma(coef[u][1], (double)__uint_as_float(w[1]), acc);
-          acc = fma(coef[u][2], (double)__uint_as_float(w[2]), acc);
-          acc = fma(coef[u][3], (double)__uint_as_float(w[3]), acc);
-        }
-      }
-      a[gq] = acc;
+  double coef[T::NL][T::EPL];
+  T::coefficients(coef, coef_lds[0], lane);
+  double sc = T::scores(raw, coef, lane);
+  const int j = j_wave + T::entry(lane);
+  if (T::writer(lane) && j < D.max_blocks) {
+    const bool kept = j < D.n_sink || j >= nb - D.n_tail;  // always-kept blocks rank above every score
+    if (MEAN) {  // sums -> means: the block's token count (the last block may be partly filled)
+      int cnt = D.ctx_len[b] - j * D.S;
+      cnt = cnt > D.S ? D.S : (cnt < 1 ? 1 : cnt);
+      sc = sc / (double)cnt;
     }
-    // the batch after next takes over this buffer
-    if (t + 2 < kScoreBatches) {
-#pragma unroll
-      for (int it = 0; it < kScoreBatch; ++it)
-        cur[it] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, load_off(t + 2, it), 0, 0));
-    }
-    // add across the 8 lanes of an entry; with several groups the first steps exchange and halve
-    if constexpr (NG == 4) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const double keep = hi2 ? a[i + 2] : a[i], send = hi2 ? a[i] : a[i + 2];
-        a[i] = keep + partner_f64<2>(send);
-      }
-      const double keep = hi1 ? a[1] : a[0], send = hi1 ? a[0] : a[1];
-      a[0] = keep + partner_f64<1>(send);
-    } else if constexpr (NG == 2) {
-      const double keep = hi2 ? a[1] : a[0], send = hi2 ? a[0] : a[1];
-      a[0] = keep + partner_f64<2>(send);
-      a[0] += partner_f64<1>(a[0]);
-    } else {
-      a[0] += partner_f64<2>(a[0]);
-      a[0] += partner_f64<1>(a[0]);
-    }
-    a[0] += partner_f64<0>(a[0]);
-    // a[0]: score of entry lane/8 of group my_g of this batch
-    const int j = j_wave + (t * NG + my_g) * 8 + (lane >> 3);
-    if (writer && j < D.max_blocks) {
-      const bool kept = j < D.n_sink || j >= nb - D.n_tail;  // always-kept blocks rank above every score
-      double sc = a[0];
-      if (MEAN) {  // sums -> means: the block's token count (the last block may be partly filled)
-        int cnt = D.ctx_len[b] - j * D.S;
-        cnt = cnt > D.S ? D.S : (cnt < 1 ? 1 : cnt);
-        sc = sc / (double)cnt;
-      }
-      scores[(size_t)pair * D.max_blocks + j] = j < nb ? (kept ? INFINITY : (float)sc) : -INFINITY;
-    }
+    scores[(size_t)pair * D.max_blocks + j] = j < nb ? (kept ? INFINITY : (float)sc) : -INFINITY;
   }
 }
 
@@ -623,16 +539,13 @@ static int launch_score_max_hc(const Dims& D, int dtype, const void* q, const vo
   dim3 grid((D.max_blocks + blocks_per_wg - 1) / blocks_per_wg, D.Hkv, D.B);
   dim3 block(kScoreWaves * kWave);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
-  if (dtype == SCOUT_BF16 && D.d == 128)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_BF16, 128, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
-  else if (dtype == SCOUT_BF16 && D.d == 64)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_BF16, 64, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
-  else if (dtype == SCOUT_F32 && D.d == 128)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_F32, 128, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
-  else if (dtype == SCOUT_F32 && D.d == 64)
-    hipLaunchKernelGGL((score_max_kernel<SCOUT_F32, 64, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived);
-  else
-    return SCOUT_EUNSUPPORTED;
+#define SCOUT_SCORE_MAX(DT, DH)                                                                                             \
+  hipLaunchKernelGGL((score_max_kernel<DT, DH, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived)
+  if (dtype == SCOUT_BF16 && D.d == 128) SCOUT_SCORE_MAX(SCOUT_BF16, 128);
+  else if (dtype == SCOUT_BF16) SCOUT_SCORE_MAX(SCOUT_BF16, 64);
+  else if (D.d == 128) SCOUT_SCORE_MAX(SCOUT_F32, 128);
+  else SCOUT_SCORE_MAX(SCOUT_F32, 64);
+#undef SCOUT_SCORE_MAX
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
@@ -661,7 +574,7 @@ static int launch_score_sum(const Dims& D, int dtype, const void* q, const void*
                             uint32_t* arrived, hipStream_t st) {
   const int entry_bytes = MEAN ? D.d * 4 : 2 * D.d * (dtype == SCOUT_BF16 ? 2 : 4);
   const int lines = entry_bytes / 128;  // 128-byte lines per digest entry
-  const int blocks_per_wg = kScoreBatch / lines * 8 * kScoreBatches * kScoreWaves;
+  const int blocks_per_wg = kScoreBatch / lines * 8 * kScoreWaves;
   dim3 grid((D.max_blocks + blocks_per_wg - 1) / blocks_per_wg, D.Hkv, D.B);
   dim3 block(kScoreWaves * kWave);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;

@@ -329,8 +329,13 @@ constexpr int score_max_entries(int lines) { return 16 / lines < 4 ? 16 / lines 
 
 // ROWS: every head's estimate goes to a row of its own, scores[B][Hq][max_blocks] (a selection per query head:
 // one pass over the KV head's digests serves its G query heads), instead of their maximum into the KV head's row.
-template <int DT, int DH, int HC, bool ROWS>
-__global__ __launch_bounds__(kScoreWaves* kWave) void score_max_kernel(Dims D, const void* q, const void* digest,
+//
+// FEW: registers for two waves per SIMD, for launches that do not fill the chip with more than that anyway
+// (launch_score_max_hc): the coefficients of the steps ahead are read from LDS while the multiply-adds of this one
+// run.  With three waves' registers the compiler reads them step by step and the two waves spent half of their cycles
+// waiting for LDS.
+template <int DT, int DH, int HC, bool ROWS, bool FEW>
+__global__ __launch_bounds__(kScoreWaves* kWave) __attribute__((amdgpu_waves_per_eu(1, FEW ? 2 : 8))) void score_max_kernel(Dims D, const void* q, const void* digest,
                                                                       float* scores, uint32_t* arrived) {
   constexpr int EPL = (DT == SCOUT_BF16) ? 8 : 4;   // elements per 16-byte load
   constexpr int ESZ = (DT == SCOUT_BF16) ? 2 : 4;
@@ -539,8 +544,18 @@ static int launch_score_max_hc(const Dims& D, int dtype, const void* q, const vo
   dim3 grid((D.max_blocks + blocks_per_wg - 1) / blocks_per_wg, D.Hkv, D.B);
   dim3 block(kScoreWaves * kWave);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
+  // Where the line lies, 1024 blocks per pair, us with registers for two waves and without: bf16, d = 128, 8 heads, 512
+  // workgroups 11.6 and 13.6, 1024 18.5 and 21.2; 4 heads 1024 15.0 and 15.5, 1536 23.9 and 23.3, 2048 29.9 and 29.6; bf16, d = 64,
+  // 4 heads, 768 7.3 and 8.0, 1024 8.9 and 8.5, 2048 15.5 and 14.0; fp32, d = 128, 8 heads, 1024 15.0 and 16.6, 1536 (16 heads)
+  // 32.5 and 31.5, 4096 76 and 70.
+  const bool few = (long long)grid.x * grid.y * grid.z <= (dtype == SCOUT_BF16 && D.d == 64 ? 768 : 1024);
 #define SCOUT_SCORE_MAX(DT, DH)                                                                                             \
-  hipLaunchKernelGGL((score_max_kernel<DT, DH, HC, ROWS>), grid, block, 0, st, D, q, digest, scores, arrived)
+  do {                                                                                                                      \
+    if (few)                                                                                                                \
+      hipLaunchKernelGGL((score_max_kernel<DT, DH, HC, ROWS, true>), grid, block, 0, st, D, q, digest, scores, arrived);    \
+    else                                                                                                                    \
+      hipLaunchKernelGGL((score_max_kernel<DT, DH, HC, ROWS, false>), grid, block, 0, st, D, q, digest, scores, arrived);   \
+  } while (0)
   if (dtype == SCOUT_BF16 && D.d == 128) SCOUT_SCORE_MAX(SCOUT_BF16, 128);
   else if (dtype == SCOUT_BF16) SCOUT_SCORE_MAX(SCOUT_BF16, 64);
   else if (D.d == 128) SCOUT_SCORE_MAX(SCOUT_F32, 128);

@@ -337,10 +337,10 @@ int recall_scatter(const scout_problem* p, const void* staged, int64_t n_tiles, 
  * all NULL (nothing offloaded).  sel_host / n_host tell the host which blocks
  * it has to cover for this query.  `scores` may be NULL for a caller that does
  * not need them (they then stay in the workspace or, where one workgroup does
- * the whole step of a pair, on the chip).  Launches: three where a pair is
- * spread over several workgroups (scoring; selection + attention; combine +
- * merge), one where the pairs alone fill the chip (bf16, d = 128, at least 192
- * pairs: every step of a pair in one workgroup).
+ * the whole step of a pair, on the chip).  Launches: two where a pair is
+ * spread over several workgroups (scoring; selection + attention + merge), one
+ * where the pairs alone fill the chip (bf16, d = 128, at least 192 pairs) or
+ * have little to read: every step of a pair in one workgroup.
  *
  * slot_gpu and n_gpu are read before they are written: what they hold on entry
  * is taken as a HINT of where this step's tiles will be (adjacent decode tokens

@@ -1325,9 +1325,12 @@ static bool step_kernel_takes(const Dims& D) {
 }
 
 // Pairs that alone fill the chip.  One workgroup streams its pair's whole digest row: worth it while a row is short
-// enough that one long sequence among short ones cannot hold the launch up for long (2048 blocks = 1 MiB of digest).
+// enough that one long sequence among short ones cannot hold the launch up for long (2048 blocks = 1 MiB of digest:
+// 256 ragged pairs 63.7 us against 65.4 in two launches, 256 equal ones 79.7 and 81.0; of 2049 blocks, which need the next
+// size of the key array, 66 and 63).  Pairs beyond one per compute unit start when others end, and a long row then ends
+// last: 384 ragged pairs of 1024 blocks 69.0 against 73.7, of 2048 blocks 105.0 against 96.6 (equal ones 127.6 and 120.2).
 bool step_kernel_supported(const Dims& D, int dtype) {
-  return step_kernel_takes(D) && dtype == SCOUT_BF16 && D.d == 128 && D.max_blocks <= 2048;
+  return step_kernel_takes(D) && dtype == SCOUT_BF16 && D.d == 128 && D.max_blocks <= (D.B * D.Hkv <= 256 ? 2048 : 1024);
 }
 
 // Pairs with so little to read that one workgroup is done with it before the second launch of a split pair has begun:

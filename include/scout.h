@@ -193,8 +193,9 @@ int select_topk(const scout_problem* p, const float* scores, const int32_t* bloc
  *   slot_gpu  i32 [B][Hkv][k]         pool slot of the same entry
  *   n_gpu     i32 [B][Hkv]            entries used per pair (clamped to k)
  *   o         f32 [B][Hq][d], m f32 [B][Hq], l f32 [B][Hq]   out
- * Inputs are read in their stored type; products and sums are binary32 (the
- * bf16 kernel rounds softmax weights to bf16 before the value product).
+ * Inputs are read in their stored type; products, sums and
+ * softmax weights are binary32 (bf16 with d = 128 rounds the weights to bf16
+ * before the value product).
  */
 int sparse_decode_attn(const scout_problem* p, const void* q, const void* k_pool,
                        const void* v_pool, int64_t n_slots, const int32_t* sel_gpu,

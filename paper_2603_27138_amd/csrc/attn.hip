@@ -8,7 +8,7 @@
 // pair's block list, and finally with the host's partial.
 //
 // Inside the kernels logits are kept in base-2 units (x * log2(e)), so the
-// exponentials are bare v_exp_f32; m is converted back to natural-log units
+// exponentials are v_exp_f32; m is converted back to natural-log units
 // where it leaves the library.
 //
 // Two kernel families write the same per-split partials into the workspace, both for every supported
@@ -18,12 +18,14 @@
 //                     registers (no LDS), in units of 16 tokens.
 //   attn_valu_kernel  plain vector ALU; only where the caller asks for it (scout_set_attn_mode).
 // combine_kernel folds the splits (and optionally the host partial) together.
+#include <type_traits>
+
 #include "score_tile.h"
 #include "select.h"
 
 namespace scout {
 
-// bare v_exp_f32: results below 2^-126 flush to zero, which is what a softmax weight wants
+// bare v_exp_f32: results below 2^-126 flush to zero, which rescaling factors and rounded weights can afford
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 __device__ __forceinline__ float exp2_diff(float a, float b) {
@@ -106,7 +108,8 @@ __device__ __forceinline__ void finish(const Dims& D, const Epilogue& E, int bh,
 // one, so no wave waits for a neighbour that got a whole block more.  For each unit:
 //   logits^T[token][head] = K[token][:] . Q[head][:]            bf16: d/32 x mfma 16x16x32, fp32: d/4 x mfma 16x16x4
 //   online softmax per head (heads live in lane % 16)
-//   out^T[dim][head]    += V^T[dim][token] . P^T[token][head]   bf16: d/16 x mfma 16x16x16, fp32: d/4 x mfma 16x16x4
+//   out^T[dim][head]    += V^T[dim][token] . P^T[token][head]   bf16: d/16 x mfma 16x16x16 per term of a weight (kWeights32),
+//                                                               fp32: d/4 x mfma 16x16x4
 // Operand layout of the 16x16 MFMAs: lane L supplies, for A, row L%16 and for B, column L%16, the
 // contraction elements of group L/16 (8 of them for x32, 4 for x16, 1 for x4); the result has column L%16 and
 // rows 4*(L/16)+i.  The contraction index may be labelled freely as long as A and B agree, which
@@ -142,6 +145,17 @@ struct Tile {
   // channel of accumulator tile r, row index R
   static __device__ __forceinline__ constexpr int channel(int r, int R) { return CPC * (R + 16 * (r / CPC)) + r % CPC; }
 };
+
+// Whether the softmax weights enter the second product in binary32: for fp32, and for bf16 with d = 64 (bf16 with d = 128
+// rounds them to bf16).  With bf16 values a binary32 weight goes as the sum of three bf16 terms, 24 bits, each multiplied
+// with the values on the bf16 matrix instructions.  8 sequences x 8 KV heads with 128 blocks of 16 tokens listed: the
+// attention takes 8.7 us, 8.5 with weights of one term, 9.8 through the fp32 matrix instructions, 30 on the vector ALU.
+// Error of the outputs against binary64 (2-norm, lists of 64 to 2048 tokens, logits of standard deviation 0.3, 1, 2), three
+// terms and vector ALU: 1.07 and 1.34e-7, 1.42 and 1.60e-7, 2.05 and 2.12e-7; one term: 3e-4 to 1.5e-3.  A term may be zero or negative, which
+// makes a NaN of an infinite value, so a wave whose sums hold a NaN starts over with the weights whole, through the fp32
+// matrix instructions (EXACT): infinite values give what they give everywhere.
+template <int DT, int DH>
+constexpr bool kWeights32 = DT == SCOUT_F32 || DH == 64;
 
 // The group's queries as operand registers: 16-byte chunk 4 * s + kg of head ln.
 template <int DT, int DH>
@@ -222,25 +236,35 @@ struct WaveState {
 
 // Fold one unit into the wave's state.  `valid` tokens of the unit count (0: the unit is void and
 // leaves the state as it is), so this too runs without a data-dependent branch around loads.
-template <int DT, int DH>
+// EXACT: see kWeights32.
+template <int DT, int DH, bool EXACT>
 __device__ __forceinline__ void consume_unit(WaveState<DH / 16>& W, UnitRegs<DT, DH>& T,
                                              const QRegs<DT, DH>& qreg, int valid, float scale2, int kg) {
   using L = Tile<DT, DH>;
+  constexpr bool W32 = kWeights32<DT, DH>;
   f32x4 st = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < L::KL; ++s) {
-    if constexpr (DT == SCOUT_BF16) {
-      st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(T.k[s]), as_bf16x8(qreg[s]), st, 0, 0, 0);
+  if constexpr (DT == SCOUT_BF16) {
+    if constexpr (W32) {
+      static_assert(L::KL == 2, "layout");
+      const f32x4 z = (f32x4){0.f, 0.f, 0.f, 0.f};
+      st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(T.k[0]), as_bf16x8(qreg[0]), z, 0, 0, 0) +
+           __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(T.k[1]), as_bf16x8(qreg[1]), z, 0, 0, 0);
     } else {
+#pragma unroll
+    for (int s = 0; s < L::KL; ++s)
+      st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(T.k[s]), as_bf16x8(qreg[s]), st, 0, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < L::KL; ++s)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         st = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(T.k[s][e]), __uint_as_float(qreg[s][e]), st, 0, 0, 0);
-    }
   }
   // st[i] = logit of head ln, token 4*kg + i
   float x[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) x[i] = st[i] * scale2;
+  for (int i = 0; i < 4; ++i) x[i] = W32 ? st[i] : st[i] * scale2;
   if (valid < kUnitTokens) {  // wave-uniform and rare: a void unit, or the partly filled last block
                               // of a sequence; tokens beyond `valid` are dropped, their value rows zeroed
 #pragma unroll
@@ -254,11 +278,13 @@ __device__ __forceinline__ void consume_unit(WaveState<DH / 16>& W, UnitRegs<DT,
   }
   float bm = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
   bm = max_xor32(max_xor16(bm));  // over the four lanes that share the head
+  if (W32) bm *= scale2;
   const float m_new = fmaxf(W.m, bm);
   const float m_sub = m_new == -INFINITY ? 0.0f : m_new;  // nothing seen yet: weights are 2^-inf = 0
   float p[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) p[i] = fast_exp2(x[i] - m_sub);
+  for (int i = 0; i < 4; ++i)  // W32: scaled and shifted in one rounding, and weights below 2^-126 count, as on the vector ALU
+    p[i] = W32 ? exp2f(fmaf(x[i], scale2, -m_sub)) : fast_exp2(x[i] - m_sub);
   if (__ballot(m_new != W.m) != 0) {  // some head's maximum moved: rescale what has been gathered
     const float alpha = exp2_diff(W.m, m_new);
     W.l *= alpha;
@@ -266,7 +292,7 @@ __device__ __forceinline__ void consume_unit(WaveState<DH / 16>& W, UnitRegs<DT,
     for (int r = 0; r < L::NR; ++r) W.acc[r] *= alpha;
     W.m = m_new;
   }
-  if constexpr (DT == SCOUT_BF16) {
+  if constexpr (!W32) {
     // weights go into the second product as bf16; sum what is actually used
     const uint32_t p01 = cvt_pk_bf16(p[0], p[1]), p23 = cvt_pk_bf16(p[2], p[3]);
     W.l += (bf16_lo(p01) + bf16_hi(p01)) + (bf16_lo(p23) + bf16_hi(p23));
@@ -280,11 +306,36 @@ __device__ __forceinline__ void consume_unit(WaveState<DH / 16>& W, UnitRegs<DT,
     }
   } else {
     W.l += (p[0] + p[1]) + (p[2] + p[3]);
+    if constexpr (DT == SCOUT_BF16 && !EXACT) {
+      s16x4 term[3];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int t = 0; t < 3; ++t) {
+        const uint32_t p01 = cvt_pk_bf16(p[0], p[1]), p23 = cvt_pk_bf16(p[2], p[3]);
+        term[t] = __builtin_bit_cast(s16x4, (uint2){p01, p23});
+        p[0] -= bf16_lo(p01);  // exact
+        p[1] -= bf16_hi(p01);
+        p[2] -= bf16_lo(p23);
+        p[3] -= bf16_hi(p23);
+      }
 #pragma unroll
-      for (int r = 0; r < L::NR; ++r)
-        W.acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(T.v[i][r / 4][r % 4]), p[i], W.acc[r], 0, 0, 0);
+      for (int r = 0; r < L::NR; ++r) {
+        const uint32_t a01 = pack_halves(T.v[0][0][r >> 1], T.v[1][0][r >> 1], r & 1);
+        const uint32_t a23 = pack_halves(T.v[2][0][r >> 1], T.v[3][0][r >> 1], r & 1);
+        const s16x4 v = __builtin_bit_cast(s16x4, (uint2){a01, a23});
+#pragma unroll
+        for (int t = 2; t >= 0; --t) W.acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v, term[t], W.acc[r], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < L::NR; ++r) {
+          float v;
+          if constexpr (DT == SCOUT_BF16) v = (r & 1) ? bf16_hi(T.v[i][0][r >> 1]) : bf16_lo(T.v[i][0][r >> 1]);
+          else v = __uint_as_float(T.v[i][r / 4][r % 4]);
+          W.acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, p[i], W.acc[r], 0, 0, 0);
+        }
+    }
   }
 }
 
@@ -476,67 +527,77 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   const int u1 = u0 + per + (v < extra ? 1 : 0);
 
   WaveState<L::NR> W;
-#pragma unroll
-  for (int r = 0; r < L::NR; ++r) W.acc[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  W.m = -INFINITY;
-  W.l = 0.0f;
-
   // DEPTH units are kept in flight per wave: the loads of the next ones are issued before a unit is
   // consumed.  Measured at the benchmark shapes, one unit in flight per wave with eight waves per
   // workgroup (64 KiB requested per compute unit at any time) beats two, three and four (17.0, 17.4,
   // 17.7 and 19.0 us for 64.5 MiB of tiles).
-  if constexpr (PRIVATE) {
-    // unit v + j * n_waves of the pair is this wave's j-th; its list entry sits in lane j
-    auto entry = [&](int j, int u) {
-      Entry e{0, 0};
-      if (u < n_units) {
-        const int bj = __builtin_amdgcn_readlane(my_sel, j);
-        const long long slot = __builtin_amdgcn_readlane(my_slot, j);
-        const int sub = u & ((1 << ush) - 1);
-        int valid = ctx - bj * S - sub * kUnitTokens;
-        valid = valid > kUnitTokens ? kUnitTokens : valid;
-        if (bj >= 0 && valid > 0 && slot >= 0 && slot < n_slots) {
-          e.elem_off = (size_t)slot * D.tile_stride + sub * kUnitTokens * DH;
-          e.valid = valid;
+  auto gather = [&](auto exact) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < L::NR; ++r) W.acc[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    W.m = -INFINITY;
+    W.l = 0.0f;
+    if constexpr (PRIVATE) {
+      // unit v + j * n_waves of the pair is this wave's j-th; its list entry sits in lane j
+      auto entry = [&](int j, int u) {
+        Entry e{0, 0};
+        if (u < n_units) {
+          const int bj = __builtin_amdgcn_readlane(my_sel, j);
+          const long long slot = __builtin_amdgcn_readlane(my_slot, j);
+          const int sub = u & ((1 << ush) - 1);
+          int valid = ctx - bj * S - sub * kUnitTokens;
+          valid = valid > kUnitTokens ? kUnitTokens : valid;
+          if (bj >= 0 && valid > 0 && slot >= 0 && slot < n_slots) {
+            e.elem_off = (size_t)slot * D.tile_stride + sub * kUnitTokens * DH;
+            e.valid = valid;
+          }
+        }
+        return e;
+      };
+      UnitRegs<DT, DH> buf[DEPTH];
+      Entry ent[DEPTH];
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        ent[d] = entry(d, v + d * n_waves);
+        issue_unit<DT, DH>(buf[d], k_pool, v_pool, ent[d], ln, kg);
+      }
+      int j = DEPTH;
+      for (int u = v; u < n_units; u += DEPTH * n_waves) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+          const Entry nx = entry(j, u + (d + DEPTH) * n_waves);
+          ++j;
+          consume_unit<DT, DH, decltype(exact)::value>(W, buf[d], qreg, ent[d].valid, scale2, kg);
+          ent[d] = nx;
+          issue_unit<DT, DH>(buf[d], k_pool, v_pool, nx, ln, kg);
         }
       }
-      return e;
-    };
-    UnitRegs<DT, DH> buf[DEPTH];
-    Entry ent[DEPTH];
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      ent[d] = entry(d, v + d * n_waves);
-      issue_unit<DT, DH>(buf[d], k_pool, v_pool, ent[d], ln, kg);
-    }
-    int j = DEPTH;
-    for (int u = v; u < n_units; u += DEPTH * n_waves) {
+    } else {
+      UnitRegs<DT, DH> buf[DEPTH];
+      Entry ent[DEPTH];
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
-        const Entry nx = entry(j, u + (d + DEPTH) * n_waves);
-        ++j;
-        consume_unit<DT, DH>(W, buf[d], qreg, ent[d].valid, scale2, kg);
-        ent[d] = nx;
-        issue_unit<DT, DH>(buf[d], k_pool, v_pool, nx, ln, kg);
+        ent[d] = read_entry<DH>(sel, slot_list, u0 + d, u1, ush, S, ctx, n_slots, D.tile_stride);
+        issue_unit<DT, DH>(buf[d], k_pool, v_pool, ent[d], ln, kg);
+      }
+      for (int u = u0; u < u1; u += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+          const Entry nx = read_entry<DH>(sel, slot_list, u + d + DEPTH, u1, ush, S, ctx, n_slots, D.tile_stride);
+          consume_unit<DT, DH, decltype(exact)::value>(W, buf[d], qreg, ent[d].valid, scale2, kg);
+          ent[d] = nx;
+          issue_unit<DT, DH>(buf[d], k_pool, v_pool, nx, ln, kg);
+        }
       }
     }
-  } else {
-    UnitRegs<DT, DH> buf[DEPTH];
-    Entry ent[DEPTH];
+  };
+  gather(std::false_type{});
+  if constexpr (DT == SCOUT_BF16 && kWeights32<DT, DH>) {
+    bool nan = false;
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      ent[d] = read_entry<DH>(sel, slot_list, u0 + d, u1, ush, S, ctx, n_slots, D.tile_stride);
-      issue_unit<DT, DH>(buf[d], k_pool, v_pool, ent[d], ln, kg);
-    }
-    for (int u = u0; u < u1; u += DEPTH) {
+    for (int r = 0; r < L::NR; ++r)
 #pragma unroll
-      for (int d = 0; d < DEPTH; ++d) {
-        const Entry nx = read_entry<DH>(sel, slot_list, u + d + DEPTH, u1, ush, S, ctx, n_slots, D.tile_stride);
-        consume_unit<DT, DH>(W, buf[d], qreg, ent[d].valid, scale2, kg);
-        ent[d] = nx;
-        issue_unit<DT, DH>(buf[d], k_pool, v_pool, nx, ln, kg);
-      }
-    }
+      for (int i = 0; i < 4; ++i) nan |= W.acc[r][i] != W.acc[r][i];
+    if (__ballot(nan) != 0) gather(std::true_type{});  // see kWeights32
   }
   f32x4(&acc)[L::NR] = W.acc;
   float m_run = W.m, l_run = W.l;

@@ -255,11 +255,24 @@ __device__ __forceinline__ void consume_unit(WaveState<DH / 16>& W, UnitRegs<DT,
       st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(T.k[s]), as_bf16x8(qreg[s]), st, 0, 0, 0);
     }
   } else {
+    // a chain per 8 channels, joined pairwise, as on the vector ALU: of one chain over all channels a large logit's error
+    // is what the outputs' error shows (d = 128, logits of standard deviation 2: 6e-7 instead of 2.3e-7, vector ALU 2.4e-7)
+    f32x4 part[L::KL];
 #pragma unroll
-    for (int s = 0; s < L::KL; ++s)
+    for (int s = 0; s < L::KL; ++s) {
+      f32x4 half[2];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        st = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(T.k[s][e]), __uint_as_float(qreg[s][e]), st, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) {
+        if (e % 2 == 0) half[e / 2] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        half[e / 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(T.k[s][e]), __uint_as_float(qreg[s][e]), half[e / 2], 0, 0, 0);
+      }
+      part[s] = half[0] + half[1];
+    }
+#pragma unroll
+    for (int n = L::KL / 2; n > 0; n /= 2)
+#pragma unroll
+      for (int s = 0; s < n; ++s) part[s] += part[s + n];
+    st = part[0];
   }
   // st[i] = logit of head ln, token 4*kg + i
   float x[4];

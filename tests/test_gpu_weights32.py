@@ -134,3 +134,36 @@ def test_weights_below_the_normal_range(dtype, d):
     torch.cuda.synchronize()
     want = 15 * math.exp(-88.5) * 2.0 ** 100
     assert ((o.double() - want).abs() <= want * (2.0 ** -6 if dtype == "bf16" else 1e-4)).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("spread", [0.3, 2.0])
+def test_error_no_larger_than_the_vector_alus(dtype, d, spread):
+    """2-norm of the outputs' error against binary64, summed over lists of 64 to 1024 tokens with logits of the given standard
+    deviation, of the matrix-core kernel and of the vector-ALU kernel on the same lists.  Both are sums of some 4000 rounding errors
+    per case that differ in their order, so the two norms scatter by a few per cent of each other; a logit summed in one
+    chain over 64 or 128 channels, or a rounded weight, shows as 2.2 to thousands of times the vector ALU's."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    square = {1: 0.0, 0: 0.0}
+    for seed, (G, S, k) in enumerate([(4, 16, 4), (8, 32, 16), (16, 16, 64), (4, 32, 32), (8, 16, 16), (16, 32, 4)]):
+        Bn, Hkv = 2, 8
+        rand = dict(device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed))
+        lens = torch.full((Bn,), k * S, dtype=torch.int32, device="cuda")
+        p = B.make_problem(Bn, G * Hkv, Hkv, d, S, B.BF16 if dtype == "bf16" else B.F32, k, k, lens)
+        q = (spread * torch.randn(Bn, G * Hkv, d, **rand)).to(tdt)
+        k_pool, v_pool = (torch.randn(Bn * Hkv * k, S, d, **rand).to(tdt) for _ in range(2))
+        slot = torch.arange(Bn * Hkv * k, dtype=torch.int32, device="cuda").view(Bn, Hkv, k)
+        sel = torch.arange(k, dtype=torch.int32, device="cuda").expand(Bn, Hkv, k).contiguous()
+        n = torch.full((Bn, Hkv), k, dtype=torch.int32, device="cuda")
+        want, _ = _reference(q, k_pool, v_pool, sel, slot, n, lens, S)
+        f32 = dict(dtype=torch.float32, device="cuda")
+        o, m, l = torch.empty(Bn, G * Hkv, d, **f32), torch.empty(Bn, G * Hkv, **f32), torch.empty(Bn, G * Hkv, **f32)
+        for family in square:
+            B.set_attn_mode(family, 0, 0)
+            try:
+                B.sparse_decode_attn(p, q, k_pool, v_pool, slot.numel(), sel, slot, n, o, m, l, B.alloc_workspace(p))
+            finally:
+                B.set_attn_mode(0, 0, 0)
+            torch.cuda.synchronize()
+            square[family] += ((o.double().cpu() - want).norm() / want.norm()).item() ** 2
+    assert square[0] ** 0.5 <= 1.1 * square[1] ** 0.5, square

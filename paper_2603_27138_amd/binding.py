@@ -102,7 +102,8 @@ def _load_calls():
     mod = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(mod)
     L = lib()
-    mod.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS})
+    mod.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS}, Problem, _ptr,
+             _ptr_addressable, _stream)
     _calls = mod
     return mod
 

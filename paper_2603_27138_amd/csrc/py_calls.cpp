@@ -4,15 +4,33 @@
 // arguments through ctypes (a Python call per tensor for its device, its layout and its address, and one
 // for the current stream) took 17 us for scout_layer_step, while its launches take 6.  Here the tensors are
 // looked into directly, and the C ABI is called through the addresses that the ctypes binding has loaded
-// (bind), so there is one copy of the library.  Checks, messages and return codes are binding.py's.
+// (bind), so there is one copy of the library.  Checks, messages and return codes are binding.py's: what is no plain
+// tensor (subclasses, objects with a tensor's attributes, None where one is required) goes through its _ptr, and what
+// torch throws becomes the Python exception that its own calls raise (entry).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "scout.h"
 
 namespace {
+
+// binding.py's Problem, _ptr, _ptr_addressable and _stream, filled by bind().
+struct Binding {
+  PyObject *problem = nullptr, *ptr = nullptr, *ptr_addressable = nullptr, *stream = nullptr;
+} py;
+
+// Calls one of them, which answers with a c_void_p or None; on an error the exception is set.
+void* address_by(PyObject* f, PyObject* arg) {
+  PyObject* const r = PyObject_CallFunctionObjArgs(f, arg, nullptr);
+  PyObject* const value = r == nullptr || r == Py_None ? nullptr : PyObject_GetAttrString(r, "value");
+  void* const address = value == nullptr || value == Py_None ? nullptr : PyLong_AsVoidPtr(value);
+  Py_XDECREF(r);
+  Py_XDECREF(value);
+  return address;
+}
 
 // One argument list on its way to the C ABI: problem, tensors by position, then workspace and stream.
 struct Args {
@@ -39,28 +57,34 @@ struct Args {
 
   const scout_problem* prob() {
     if (!ok) return nullptr;
-    if (PyObject_GetBuffer(next(), &problem, PyBUF_SIMPLE) != 0) {
+    PyObject* const o = next();
+    if (!PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(py.problem))) {
+      PyErr_Format(PyExc_TypeError, "%s: the first argument is a Problem, not %s", fn, Py_TYPE(o)->tp_name);
+      ok = false;
+      return nullptr;
+    }
+    if (PyObject_GetBuffer(o, &problem, PyBUF_SIMPLE) != 0) {
       ok = false;
       return nullptr;
     }
     have_problem = true;
-    if (problem.len != (Py_ssize_t)sizeof(scout_problem)) {
-      PyErr_Format(PyExc_TypeError, "%s: the first argument is a Problem", fn);
+    if (problem.len < (Py_ssize_t)sizeof(scout_problem)) {
+      PyErr_Format(PyExc_TypeError, "%s: the Problem is too small", fn);
       ok = false;
     }
     return static_cast<const scout_problem*>(problem.buf);
   }
 
-  // a contiguous tensor; `pinned`: in device memory or in pinned host memory; None: a null pointer
-  const at::Tensor* tensor(bool pinned) {
-    if (!ok) return nullptr;
-    PyObject* o = next();
-    if (o == Py_None) return nullptr;
-    if (!THPVariable_Check(o)) {
-      PyErr_Format(PyExc_TypeError, "%s: argument %zd is not a tensor", fn, at);
-      ok = false;
-      return nullptr;
-    }
+  // of an object that is no plain tensor: binding.py's answer
+  void* by_python(PyObject* o, bool pinned) {
+    void* const address = address_by(pinned ? py.ptr_addressable : py.ptr, o);
+    if (PyErr_Occurred()) ok = false;
+    return address;
+  }
+
+  // the address of a contiguous tensor; `pinned`: in device memory or in pinned host memory
+  void* address(PyObject* o, bool pinned) {
+    if (!THPVariable_CheckExact(o)) return by_python(o, pinned);
     const at::Tensor& t = THPVariable_Unpack(o);
     if (!t.is_contiguous() || !(t.is_cuda() || (pinned && t.is_pinned()))) {
       PyErr_SetString(PyExc_AssertionError, pinned ? "need a CUDA tensor or a pinned CPU tensor"
@@ -68,33 +92,53 @@ struct Args {
       ok = false;
       return nullptr;
     }
-    return &t;
+    return t.data_ptr();
   }
   template <class T = void>
-  T* dev() {
-    const at::Tensor* t = tensor(false);
-    return t ? static_cast<T*>(t->data_ptr()) : nullptr;
+  T* dev() {  // None: a null pointer
+    if (!ok) return nullptr;
+    PyObject* const o = next();
+    return o == Py_None ? nullptr : static_cast<T*>(address(o, false));
   }
-  void* addressable() {
-    const at::Tensor* t = tensor(true);
-    return t ? t->data_ptr() : nullptr;
+  void* addressable() { return ok ? address(next(), true) : nullptr; }
+  void* addressable_or_none() {
+    if (!ok) return nullptr;
+    PyObject* const o = next();
+    return o == Py_None ? nullptr : address(o, true);
   }
   void* workspace(size_t* bytes) {
-    const at::Tensor* t = tensor(false);
-    *bytes = t ? (size_t)t->numel() : 0;
-    return t ? t->data_ptr() : nullptr;
+    *bytes = 0;
+    if (!ok) return nullptr;
+    PyObject* const o = next();
+    void* const ws = address(o, false);
+    if (!ok) return nullptr;
+    if (THPVariable_CheckExact(o)) {
+      *bytes = (size_t)THPVariable_Unpack(o).numel();
+      return ws;
+    }
+    PyObject* const n = PyObject_CallMethod(o, "numel", nullptr);
+    *bytes = n == nullptr ? 0 : (size_t)PyLong_AsUnsignedLongLongMask(n);
+    Py_XDECREF(n);
+    if (PyErr_Occurred()) ok = false;
+    return ws;
   }
   int64_t integer() {
     if (!ok) return 0;
     PyObject* const as_int = PyNumber_Long(next());  // what int() takes
-    const long long v = as_int ? PyLong_AsLongLong(as_int) : -1;
+    const int64_t v = as_int ? (int64_t)PyLong_AsUnsignedLongLongMask(as_int) : -1;  // the low 64 bits, as ctypes passes them
     Py_XDECREF(as_int);
     if (v == -1 && PyErr_Occurred()) ok = false;
     return v;
   }
 };
 
-void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+void* current_stream() {
+  try {
+    return c10::hip::getCurrentHIPStream().stream();
+  } catch (const c10::Error&) {  // no usable device: what torch.cuda says of it
+    return address_by(py.stream, nullptr);
+  }
+}
 
 // Entry points by address, filled by bind().
 struct Table {
@@ -118,6 +162,7 @@ struct Table {
   do {                                       \
     if (!A.ok) return nullptr;               \
     void* const st = current_stream();       \
+    if (PyErr_Occurred()) return nullptr;    \
     int rc;                                  \
     Py_BEGIN_ALLOW_THREADS                   \
     rc = CALL;                               \
@@ -144,7 +189,7 @@ PyObject* py_append_token(PyObject*, PyObject* const* a, Py_ssize_t n) {
   i32* table = A.dev<i32>();
   void *kp = A.dev(), *vp = A.dev();
   const int64_t slots = A.integer();
-  void *hk = A.addressable(), *hv = A.addressable();
+  void *hk = A.addressable_or_none(), *hv = A.addressable_or_none();
   SCOUT_RETURN(T.append_token(p, ctx, k, v, slot, digest, table, kp, vp, slots, hk, hv, st));
 }
 
@@ -272,8 +317,14 @@ PyObject* py_layer_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
                                   n_gpu, sel_host, n_host, out, lse, ws, nws, st));
 }
 
-// bind(addresses by name): where the loaded library has its entry points.
-PyObject* py_bind(PyObject*, PyObject* d) {
+// bind(addresses by name, Problem, _ptr, _ptr_addressable, _stream): where the loaded library has its entry points, and what
+// binding.py makes of an argument.
+PyObject* py_bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 5 || !PyType_Check(a[1])) {
+    PyErr_SetString(PyExc_TypeError, "bind(addresses, Problem, _ptr, _ptr_addressable, _stream)");
+    return nullptr;
+  }
+  PyObject* const d = a[0];
 #define SCOUT_BIND(NAME)                                                              \
   do {                                                                                \
     PyObject* o = PyDict_Check(d) ? PyDict_GetItemString(d, #NAME) : nullptr;         \
@@ -297,12 +348,29 @@ PyObject* py_bind(PyObject*, PyObject* d) {
   SCOUT_BIND(recall_fetch);
   SCOUT_BIND(recall_scatter);
   SCOUT_BIND(scout_layer_step);
+  PyObject** const kept[] = {&py.problem, &py.ptr, &py.ptr_addressable, &py.stream};
+  for (int i = 0; i < 4; ++i) {
+    Py_INCREF(a[i + 1]);
+    Py_XSETREF(*kept[i], a[i + 1]);
+  }
   Py_RETURN_NONE;
 }
 
-#define SCOUT_METHOD(NAME) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(py_##NAME)), METH_FASTCALL, nullptr}
+// Nothing that torch throws passes into the interpreter's C frames.
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* entry(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  if (py.problem == nullptr && F != py_bind) {
+    PyErr_SetString(PyExc_RuntimeError, "bind() comes first");
+    return nullptr;
+  }
+  return F(self, a, n);
+  END_HANDLE_TH_ERRORS
+}
+
+#define SCOUT_METHOD(NAME) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(entry<py_##NAME>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    {"bind", py_bind, METH_O, nullptr},
+    SCOUT_METHOD(bind),
     SCOUT_METHOD(build_digests),
     SCOUT_METHOD(append_token),
     SCOUT_METHOD(score_blocks),

@@ -39,14 +39,32 @@ struct DigestTile {
 __device__ __forceinline__ float first_min(float lower, float higher) { return higher < lower ? higher : lower; }
 __device__ __forceinline__ float first_max(float lower, float higher) { return higher > lower ? higher : lower; }
 
-template <bool NT>
-__device__ __forceinline__ u32x4 load_key(const u32x4* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  return *p;
+// Whether the batch holds more keys than the 256 MiB memory-side cache (see launch_digest): the lengths of eight sequences,
+// evenly spread, against the sum of theirs at which it does.  Scalar loads, all under way before the first is used: a
+// vector load of all lengths would put its latency in front of every wave's keys.
+__device__ __forceinline__ bool keys_exceed_cache(const Dims& D, int limit) {
+  const int cap = D.max_blocks * D.S;
+  int len[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) len[i] = D.ctx_len[(i * D.B) >> 3];
+  asm volatile("" ::"s"(len[0]), "s"(len[1]), "s"(len[2]), "s"(len[3]), "s"(len[4]), "s"(len[5]), "s"(len[6]), "s"(len[7]));
+  int sum = 0;  // below 8 * 2^20
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int tokens = len[i] < cap ? len[i] : cap;
+    sum += tokens > 0 ? tokens : 0;
+  }
+  return sum > limit;
 }
 
-template <int DT, int DH, int S, bool NT>
-__global__ __launch_bounds__(256) void digest_kernel(Dims D, const void* __restrict__ k_blocks, void* __restrict__ digest) {
+// In front of and behind loads of one side of a branch: the compiler takes plain and non-temporal loads of one address for
+// the same and merges the two sides into plain ones.
+__device__ __forceinline__ void only_here() { asm volatile(""); }
+
+// MAY_NT: the rows could hold that many keys; nt_limit: see keys_exceed_cache.
+template <int DT, int DH, int S, bool MAY_NT>
+__global__ __launch_bounds__(256) void digest_kernel(Dims D, const void* __restrict__ k_blocks, void* __restrict__ digest,
+                                                     int nt_limit) {
   using L = DigestTile<DT, DH, S>;
   const int pair = grid_pair();  // grid (x, Hkv, B)
   const int lane = lane_id();
@@ -59,12 +77,20 @@ __global__ __launch_bounds__(256) void digest_kernel(Dims D, const void* __restr
   const u32x4* tile = static_cast<const u32x4*>(k_blocks) + ((size_t)pair * D.max_blocks + j0) * (S * L::LPR) +
                       grp * L::RPG * L::LPR + lane % L::LPR;
   u32x4 raw[L::NBLK][L::RPG];
+  const bool nt = MAY_NT && keys_exceed_cache(D, nt_limit);
 #pragma unroll
   for (int n = 0; n < L::NBLK; ++n) {
     if (j0 + n < nb) {  // wave-uniform
+      const u32x4* p = tile + (size_t)n * (S * L::LPR);
+      if (nt) {
+        only_here();
 #pragma unroll
-      for (int i = 0; i < L::RPG; ++i)
-        raw[n][i] = load_key<NT>(tile + (size_t)n * (S * L::LPR) + i * L::LPR);
+        for (int i = 0; i < L::RPG; ++i) raw[n][i] = __builtin_nontemporal_load(p + i * L::LPR);
+        only_here();
+      } else {
+#pragma unroll
+        for (int i = 0; i < L::RPG; ++i) raw[n][i] = p[i * L::LPR];
+      }
     }
   }
 #pragma unroll
@@ -149,24 +175,35 @@ __global__ __launch_bounds__(256) void digest_kernel(Dims D, const void* __restr
 // the min/max digests of 2 KiB tiles are made: there the join of eight groups of lanes costs digest_kernel more than
 // its order of requests gains (bf16, d = 64, blocks of 16, 8 x 8 pairs
 // of 16k to 32k tokens: 65 us there, 39 us here).
-template <int DT, bool SUM, int ROWS, bool NT>
-__global__ __launch_bounds__(256) void digest_rows_kernel(Dims D, const void* __restrict__ k_blocks, void* __restrict__ digest) {
+template <int DT, bool SUM, int ROWS, bool MAY_NT>
+__global__ __launch_bounds__(256) void digest_rows_kernel(Dims D, const void* __restrict__ k_blocks, void* __restrict__ digest,
+                                                          int nt_limit) {
   constexpr int W = DT == SCOUT_BF16 ? 1 : 2;  // 16-byte words per 8 elements
   const int pair = grid_pair();  // grid (x, Hkv, B)
   const int cpt = D.d / 8;       // 8-channel chunks per token row
   const int j = blockIdx.x * (blockDim.x / cpt) + threadIdx.x / cpt;
   const int c0 = (threadIdx.x % cpt) * 8;
   const int ctx = D.ctx_len[blockIdx.z];
+  const bool nt = MAY_NT && keys_exceed_cache(D, nt_limit);
   if (j >= num_blocks(D, ctx)) return;
   const int valid = ctx - j * D.S;
   const u32x4* p = static_cast<const u32x4*>(k_blocks) + (((size_t)pair * D.max_blocks + j) * D.S * cpt + c0 / 8) * W;
   float lo[8], hi[8];  // SUM: lo is the sum
   for (int t0 = 0; t0 < D.S && t0 < valid; t0 += ROWS) {  // ROWS divides S
-    u32x4 raw[ROWS][W];
+    u32x4 raw[ROWS][W];  // rows beyond `valid` lie inside the block and are not used
+    if (nt) {
+      only_here();
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i)  // rows beyond `valid` lie inside the block and are not used
+      for (int i = 0; i < ROWS; ++i)
 #pragma unroll
-      for (int w = 0; w < W; ++w) raw[i][w] = load_key<NT>(p + (size_t)(t0 + i) * cpt * W + w);
+        for (int w = 0; w < W; ++w) raw[i][w] = __builtin_nontemporal_load(p + (size_t)(t0 + i) * cpt * W + w);
+      only_here();
+    } else {
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+        for (int w = 0; w < W; ++w) raw[i][w] = p[(size_t)(t0 + i) * cpt * W + w];
+    }
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
       float x[8];
@@ -493,10 +530,14 @@ __global__ __launch_bounds__(kScoreWaves* kWave) __attribute__((amdgpu_waves_per
 
 int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, hipStream_t st) {
   if (D.max_blocks == 0 || D.Hkv == 0 || D.B == 0) return SCOUT_OK;
-  const long long key_bytes = (long long)D.B * D.Hkv * D.max_blocks * D.S * D.d * (dtype == SCOUT_BF16 ? 2 : 4);
   // Keys beyond what the 256 MiB memory-side cache holds pass by it (non-temporal loads): 400 MB 76 us instead of 85; of
-  // 200 MB a part may still be there, and loads that pass by miss it (bf16, d = 64: 44 us instead of 39).
-  const bool nt = key_bytes > (256ll << 20);
+  // 200 MB a part may still be there, and loads that pass by miss it (bf16, d = 64: 44 us instead of 39).  The lengths
+  // decide, on the device: rows of 1 GiB that hold 128 MB of keys took 48 us for their sums with loads that pass by, 31 with
+  // plain ones.  Rows below the line cannot exceed it and are not looked at.
+  constexpr long long kCacheBytes = 256ll << 20;
+  const long long token_bytes = (long long)D.B * D.Hkv * D.d * (dtype == SCOUT_BF16 ? 2 : 4);  // one token in every sequence
+  const bool nt = token_bytes * D.max_blocks * D.S > kCacheBytes;
+  const int nt_limit = (int)(8 * kCacheBytes / token_bytes);  // below 2^24
   // 128-byte token rows are eight groups of lanes to join for each small block: a thread per row chunk is faster
   // (bf16, d = 64: 39.2 against 65 us for blocks of 16, 39.0 against 40.8 us for blocks of 32; blocks of 64 are whole waves' work).
   const bool small_tile = dtype == SCOUT_BF16 && D.d == 64 && D.S <= 32;
@@ -505,8 +546,8 @@ int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, 
     dim3 grid((D.max_blocks + per_wg - 1) / per_wg, D.Hkv, D.B);
 #define SCOUT_DIGEST_ROWS(DT, SUM, ROWS, MAY_NT)                                                                  \
   do {                                                                                                            \
-    if (MAY_NT && nt) hipLaunchKernelGGL((digest_rows_kernel<DT, SUM, ROWS, MAY_NT>), grid, dim3(256), 0, st, D, k_blocks, digest); \
-    else hipLaunchKernelGGL((digest_rows_kernel<DT, SUM, ROWS, false>), grid, dim3(256), 0, st, D, k_blocks, digest);   \
+    if (MAY_NT && nt) hipLaunchKernelGGL((digest_rows_kernel<DT, SUM, ROWS, MAY_NT>), grid, dim3(256), 0, st, D, k_blocks, digest, nt_limit); \
+    else hipLaunchKernelGGL((digest_rows_kernel<DT, SUM, ROWS, false>), grid, dim3(256), 0, st, D, k_blocks, digest, nt_limit);   \
   } while (0)
     if (D.digest_kind == 0) SCOUT_DIGEST_ROWS(SCOUT_BF16, false, 8, true);
     else if (dtype == SCOUT_BF16) SCOUT_DIGEST_ROWS(SCOUT_BF16, true, 8, true);
@@ -518,8 +559,8 @@ int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, 
   do {                                                                                                            \
     constexpr int per_wg = 4 * DigestTile<DT, DH, S_>::NBLK;                                                      \
     const dim3 grid((D.max_blocks + per_wg - 1) / per_wg, D.Hkv, D.B);                                            \
-    if (nt) hipLaunchKernelGGL((digest_kernel<DT, DH, S_, true>), grid, dim3(256), 0, st, D, k_blocks, digest);   \
-    else hipLaunchKernelGGL((digest_kernel<DT, DH, S_, false>), grid, dim3(256), 0, st, D, k_blocks, digest);     \
+    if (nt) hipLaunchKernelGGL((digest_kernel<DT, DH, S_, true>), grid, dim3(256), 0, st, D, k_blocks, digest, nt_limit);   \
+    else hipLaunchKernelGGL((digest_kernel<DT, DH, S_, false>), grid, dim3(256), 0, st, D, k_blocks, digest, nt_limit);     \
   } while (0)
 #define SCOUT_DIGEST_S(DT, DH)                     \
   do {                                             \

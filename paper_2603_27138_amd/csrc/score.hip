@@ -168,7 +168,8 @@ __global__ __launch_bounds__(256) void digest_kernel(Dims D, const void* __restr
 }
 
 // A thread takes 8 channels of a block and walks through its tokens, ROWS of them requested at a time (bf16 sums of
-// 400 MB of keys: 92 us instead of 104 with one; fp32 rows are twice as long and gain nothing from more than two).  This is how
+// 400 MB of keys: 92 us instead of 104 with one; fp32 one: d = 128, blocks of 64, 64 MB of keys take 19.6 us with one, 20.5 with two,
+// 16.2 with four, but 256 MB in blocks of 16 take 44.1, 44.3 and 47.2, and 128 MB, d = 64, 21.2, 21.3 and 24.3).  This is how
 // the sums of mean pooling are made (Sec. 2.2 names mean pooling next to min/max pooling): the digest of a block is the
 // sum of its valid keys in binary32, added in token order, one rounding per token, so that the append of a token
 // is one addition and gives the bits a rebuild would give; the mean is sum / count where it is used.  And it is how
@@ -551,7 +552,7 @@ int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, 
   } while (0)
     if (D.digest_kind == 0) SCOUT_DIGEST_ROWS(SCOUT_BF16, false, 8, true);
     else if (dtype == SCOUT_BF16) SCOUT_DIGEST_ROWS(SCOUT_BF16, true, 8, true);
-    else SCOUT_DIGEST_ROWS(SCOUT_F32, true, 2, false);
+    else SCOUT_DIGEST_ROWS(SCOUT_F32, true, 1, false);
 #undef SCOUT_DIGEST_ROWS
     return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
   }

@@ -588,9 +588,13 @@ static int launch_score_max_hc(const Dims& D, int dtype, const void* q, const vo
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
   // Where the line lies, 1024 blocks per pair, us with registers for two waves and without: bf16, d = 128, 8 heads, 512
   // workgroups 11.6 and 13.6, 1024 18.5 and 21.2; 4 heads 1024 15.0 and 15.5, 1536 23.9 and 23.3, 2048 29.9 and 29.6; bf16, d = 64,
-  // 4 heads, 768 7.3 and 8.0, 1024 8.9 and 8.5, 2048 15.5 and 14.0; fp32, d = 128, 8 heads, 1024 15.0 and 16.6, 1536 (16 heads)
-  // 32.5 and 31.5, 4096 76 and 70.
-  const bool few = (long long)grid.x * grid.y * grid.z <= (dtype == SCOUT_BF16 && D.d == 64 ? 768 : 1024);
+  // 8 heads, own rows, 768 8.0 and 9.4, 1024 beyond the line 11.6 and 11.7; fp32, d = 128, 8 heads, 1024 15.0 and 16.6, 1536 (16 heads)
+  // 32.5 and 31.5, 4096 76 and 70; fp32, d = 64, 8 heads, 1024 14.1 and 14.8, 16 heads 20.0 and 21.3.  One light pass (up to four
+  // heads; fp32, or the maximum with d = 64) gains only where all workgroups run at once, two waves per SIMD: fp32, d = 64, 4 heads, 512
+  // 4.9 and 5.4, 768 9.8 and 8.9; fp32, d = 128, 520 6.8 and 6.5; bf16, d = 64, 520 5.6 and 5.5.
+  const bool light = D.G <= 4 && (D.d == 64 ? !ROWS : dtype == SCOUT_F32);
+  const long long line = light ? 512 : dtype == SCOUT_BF16 && D.d == 64 ? 768 : 1024;
+  const bool few = (long long)grid.x * grid.y * grid.z <= line;
 #define SCOUT_SCORE_MAX(DT, DH)                                                                                             \
   do {                                                                                                                      \
     if (few)                                                                                                                \

@@ -10,7 +10,8 @@ from paper_2603_27138_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,d,line", [("bf16", 128, 1024), ("bf16", 64, 768), ("f32", 64, 1024), ("f32", 128, 1024)])
+@pytest.mark.parametrize("dtype,d,line", [("bf16", 128, 1024), ("bf16", 64, 768), ("f32", 64, 1024), ("f32", 128, 1024),
+                                          ("bf16", 64, 512), ("f32", 64, 512), ("f32", 128, 512)])
 @pytest.mark.parametrize("G", [3, 8, 11])
 @pytest.mark.parametrize("per_head", [0, 1])
 def test_both_register_budgets(dtype, d, line, G, per_head):

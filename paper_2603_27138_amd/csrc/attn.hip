@@ -1415,17 +1415,21 @@ bool step_kernel_supported(const Dims& D, int dtype) {
 }
 
 // Pairs with so little to read that one workgroup is done with it before the second launch of a split pair has begun:
-// at most 128 KiB of digests, 512 listed tokens (four units per wave) and 288 KiB of both, whatever the number of pairs.
+// at most 128 KiB of digests, 512 listed tokens (four units per wave) and 288 KiB of both.
 // Measured, a layer, one launch against scoring plus split attention, three quarters of the list resident: fp32, d = 64,
 // 1 pair of 128 blocks of 16 with k = 16: 9.2 against 11.3 us; bf16, d = 64, 64 pairs of 512 blocks with k = 32: 12.3 against 13.6; bf16,
 // d = 128, 64 pairs of 256 blocks of 16 with k = 16 (256 KiB): 12.9 against 13.7; with 32 units per pair (16 KiB of
 // digests, 272 KiB) 11.2 against 12.8, 64 KiB of digests (320 KiB) 13.6 against 13.7, 128 KiB 14.9 against 14.2; fp32,
-// d = 128, 16 units (288 KiB) 13.2 against 14.4, 32 units 16.1 against 16.1 and 18.8 against 16.7.
-constexpr int kSmallDigestBytes = 128 << 10, kSmallTokens = 512, kSmallBytes = 288 << 10;
+// d = 128, 16 units (288 KiB) 13.2 against 14.4, 32 units 16.1 against 16.1 and 18.8 against 16.7.  Up to 1024 pairs this
+// holds throughout (1024 pairs: 32.4 and 39.8, 41.9 and 47.0, 43.8 and 50.2, 55.9 and 56.3).  With more the workgroups come in many
+// rounds and the attention's part has fewer waves in flight than in a kernel of its own, so it is right only where the digests are
+// half of the tiles or more (2 * max_blocks >= k * S): fp32, d = 128, 32 blocks and 16 units, 1536 pairs 92.1 against 86.3; bf16,
+// d = 64, 128 blocks and 32 units, 4096 pairs 140.6 and 133.4; 512 blocks and 32 units 188.9 and 202.2; 256 and 16 133.9 and 138.9.
+constexpr int kSmallDigestBytes = 128 << 10, kSmallTokens = 512, kSmallBytes = 288 << 10, kSmallPairs = 1024;
 bool step_kernel_small(const Dims& D, int dtype) {
   const int row_bytes = 2 * D.d * (dtype == SCOUT_BF16 ? 2 : 4);  // of a token's K and V, and of a digest entry
   return step_kernel_takes(D) && D.max_blocks * row_bytes <= kSmallDigestBytes && D.k * D.S <= kSmallTokens &&
-         (D.max_blocks + D.k * D.S) * row_bytes <= kSmallBytes;
+         (D.max_blocks + D.k * D.S) * row_bytes <= kSmallBytes && (D.B * D.Hkv <= kSmallPairs || 2 * D.max_blocks >= D.k * D.S);
 }
 
 // Scoring, selection, attention and merge of every pair in one launch, one workgroup per pair
@@ -1438,7 +1442,8 @@ int launch_step(const Dims& D, int dtype, const void* q, const void* digest, con
   if (P.nsplit != 1 || E.mode != 2) return SCOUT_EINVAL;
   dim3 grid(1, D.Hkv, D.B), block(8 * kWave);
   const int per_lane = (D.max_blocks + 8 * kWave - 1) / (8 * kWave);
-  const int kpl = per_lane <= 2 ? 2 : per_lane <= 4 ? 4 : per_lane <= 8 ? 8 : 16;
+  const int kpl = per_lane <= 2 ? 2 : 4;  // longer rows: see step_kernel_supported
+  if (per_lane > 4) return SCOUT_EUNSUPPORTED;
   const size_t lds = mfma_smem_bytes(D, 8) +
                      (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4 + 8 * kWave * kpl) * sizeof(int) +
                      2 * D.d * sizeof(double);
@@ -1451,7 +1456,7 @@ int launch_step(const Dims& D, int dtype, const void* q, const void* digest, con
     if (kpl != 2) return SCOUT_EUNSUPPORTED;   \
     SCOUT_STEP(DT, DH, 2);                     \
   } while (0)
-  if (kpl == 4 && dtype == SCOUT_BF16 && D.d == 128)  // rows beyond 2048 blocks: see step_kernel_supported
+  if (kpl == 4 && dtype == SCOUT_BF16 && D.d == 128)  // rows of 1025 to 2048 blocks: only these take them
     SCOUT_STEP(SCOUT_BF16, 128, 4);
   else
     SCOUT_BY_TYPE(dtype, D.d, SCOUT_STEP_TYPE);

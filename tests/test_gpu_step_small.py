@@ -1,6 +1,7 @@
 """The one-launch step of pairs with little to read, against the same step by separate launches: every element type and
 head dim, groups of 1, 5 and 16 heads, rows of one block, rows that end inside and at the end of a batch of the scoring
-stream, empty sequences, budgets above the block count, and the largest budget and row that take the route.
+stream, empty sequences, budgets above the block count; then sizes on each limit of the route and one beyond it, where the
+untouched workspace shows which route a call took (a launch of its own for the scores leaves them there).
 
 Scores and lists are equal bit for bit.  Outputs: both add the same values in binary32 in another order, at most 64 tokens
 per wave and 8 partials: 200 * 2^-24 = 1.2e-5 of the largest value; for bf16 the weights are rounded to bf16 against the
@@ -51,3 +52,73 @@ def test_one_launch_equals_separate_launches(dtype, d, G, S, k, blocks):
     assert torch.equal(torch.isfinite(a["lse"]), fin)
     top = max(1.0, b["lse"][fin].abs().max().item())
     assert (a["lse"] - b["lse"])[fin].abs().max().item() <= (2.0 ** -8 if dtype == "bf16" else 1.2e-5 * top)
+
+
+def _one_launch(dtype, d, S, blocks, k, pairs):
+    """Which calls take the one-launch route: little to read, or (bf16, d = 128) pairs that fill the chip."""
+    row = 2 * d * (2 if dtype == "bf16" else 4)
+    small = (blocks * row <= 128 << 10 and k * S <= 512 and (blocks + k * S) * row <= 288 << 10
+             and (pairs <= 1024 or 2 * blocks >= k * S))
+    fills = dtype == "bf16" and d == 128 and pairs >= 192 and blocks <= (2048 if pairs <= 256 else 1024)
+    return small or fills
+
+
+# blocks, S, k, sequences, one launch: on the limits (digests, listed tokens, both, pairs) and beyond
+LIMITS = {
+    ("bf16", 64): [(512, 16, 32, 2, 1), (513, 16, 32, 2, 0), (512, 16, 33, 2, 0), (40, 64, 8, 2, 1), (40, 64, 9, 2, 0),
+                   (4, 16, 1, 512, 1), (4, 16, 1, 513, 0), (8, 16, 1, 513, 1)],
+    ("bf16", 128): [(256, 16, 20, 2, 1), (257, 16, 19, 2, 0), (256, 16, 21, 2, 0), (64, 16, 32, 2, 1), (65, 16, 32, 2, 0),
+                    (40, 16, 33, 2, 0), (257, 16, 33, 95, 0), (257, 16, 33, 96, 1), (4, 16, 1, 513, 1)],
+    ("f32", 64): [(256, 16, 20, 2, 1), (257, 16, 19, 2, 0), (64, 16, 32, 2, 1), (65, 16, 32, 2, 0), (40, 32, 17, 2, 0),
+                  (4, 16, 1, 512, 1), (4, 16, 1, 513, 0), (8, 16, 1, 513, 1)],
+    ("f32", 128): [(128, 16, 10, 2, 1), (129, 16, 9, 2, 0), (128, 16, 11, 2, 0), (32, 16, 16, 2, 1), (33, 16, 16, 2, 0),
+                   (4, 16, 1, 512, 1), (4, 16, 1, 513, 0), (8, 16, 1, 513, 1)],
+}
+
+
+@pytest.mark.parametrize("dtype,d,blocks,S,k,Bn,one", [(*t, *c) for t, cs in LIMITS.items() for c in cs])
+def test_limits_of_the_route(dtype, d, blocks, S, k, Bn, one):
+    Hkv, G, tdt = 2, 3, torch.bfloat16 if dtype == "bf16" else torch.float32
+    assert _one_launch(dtype, d, S, blocks, k, Bn * Hkv) == bool(one)
+    rand = dict(device="cuda", generator=torch.Generator(device="cuda").manual_seed(blocks + k))
+    lens = torch.randint(0, blocks * S + 1, (Bn,), dtype=torch.int32, **rand)
+    lens[0] = blocks * S
+    p = B.make_problem(Bn, G * Hkv, Hkv, d, S, B.BF16 if dtype == "bf16" else B.F32, blocks, k, lens)
+    slots = Bn * Hkv * blocks
+    k_pool, v_pool = (torch.randn(slots, S, d, **rand).to(tdt) for _ in range(2))
+    q = torch.randn(Bn, G * Hkv, d, **rand).to(tdt)
+    place = torch.randperm(slots, **rand).int().view(Bn, Hkv, blocks)
+    digest = torch.zeros(Bn, Hkv, blocks, 2, d, dtype=tdt, device="cuda")
+    B.build_digests(p, k_pool[place.view(-1).long()].view(Bn, Hkv, blocks, S, d).contiguous(), digest)
+    table = torch.where(torch.rand(Bn, Hkv, blocks, **rand) < 0.7, place, -1).int()
+    ho, hm = torch.randn(Bn, G * Hkv, d, **rand), torch.randn(Bn, G * Hkv, **rand)
+    hl = torch.rand(Bn, G * Hkv, **rand) + 0.5
+    ws = B.alloc_workspace(p)
+    got = []
+    for mode in [(0, 0, 0), (0, 2, 0)]:  # by the rule; two splits per pair, scored by a launch of their own
+        i32 = dict(dtype=torch.int32, device="cuda")
+        lists = [torch.full((Bn, Hkv, k), -7, **i32) for _ in range(4)]
+        n_gpu, n_host = torch.zeros(Bn, Hkv, **i32), torch.zeros(Bn, Hkv, **i32)
+        out = torch.full((Bn, G * Hkv, d), float("nan"), dtype=tdt, device="cuda")
+        lse = torch.full((Bn, G * Hkv), float("nan"), device="cuda")
+        ws.fill_(0x5A)
+        B.set_attn_mode(*mode)
+        try:
+            B.layer_step(p, q, digest, table, k_pool, v_pool, slots, ho, hm, hl, None, lists[0], lists[1], lists[2], n_gpu, lists[3],
+                         n_host, out, lse, ws)
+        finally:
+            B.set_attn_mode(0, 0, 0)
+        torch.cuda.synchronize()
+        untouched = bool((ws == 0x5A).all())
+        assert untouched == (bool(one) and mode[1] == 0), mode
+        got.append((lists + [n_gpu, n_host], out.float(), lse))
+    for a, b in zip(got[0][0], got[1][0]):
+        assert torch.equal(a, b)
+    (_, out, lse), (_, want, want_lse) = got
+    top = max(1.0, want.abs().max().item())
+    vmax = v_pool.float().abs().max().item()
+    # (as above; bf16 with d = 64 keeps its weights in binary32, so that only the output's rounding is left: a step of 2^-7)
+    bound = 2.0 ** -8 * (vmax + top) if (dtype, d) == ("bf16", 128) else (2.0 ** -7 if dtype == "bf16" else 0) * top + 1.2e-5 * top
+    assert (out - want).abs().max().item() <= bound
+    top = max(1.0, want_lse.abs().max().item())
+    assert (lse - want_lse).abs().max().item() <= (2.0 ** -8 if (dtype, d) == ("bf16", 128) else 1.2e-5 * top)

@@ -447,10 +447,10 @@ int sparse_decode_attn_static(const scout_problem* p, const void* q, const void*
   E.l = l;
   hipStream_t st = static_cast<hipStream_t>(stream);
   size_t off_m, off_l;
-  // fp32 and d = 64 problems are sized by the vector-ALU family's splits, whichever family serves them: what fits the
+  // fp32 and d = 64 problems are sized by the vector-ALU family's splits (or a forced count), whichever family serves them: what fits the
   // buffer and what is refused does not depend on the kernel that happens to run
-  if (g_family == 0 && g_nsplit == 0 && (p->dtype != SCOUT_BF16 || D.d != 128) &&
-      static_layout(D, AttnPlan{1, valu_splits(D), 1}, &off_m, &off_l) > (size_t)SCOUT_STATIC_SCRATCH_BYTES)
+  if (g_family == 0 && (p->dtype != SCOUT_BF16 || D.d != 128) &&
+      static_layout(D, AttnPlan{1, g_nsplit ? g_nsplit : valu_splits(D), 1}, &off_m, &off_l) > (size_t)SCOUT_STATIC_SCRATCH_BYTES)
     return SCOUT_ESCRATCH;
   if (A.family == 2 && A.nsplit == 1)  // one workgroup per pair finishes the pair itself: no scratch at all
     return launch_attn(D, p->dtype, 2, A.waves, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu,

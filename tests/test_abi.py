@@ -178,6 +178,22 @@ def test_attention_mode_belongs_to_the_calling_thread(lib):
     assert L.sparse_decode_attn_static(ctypes.byref(big), *args, None) == lib.ESCRATCH
 
 
+@pytest.mark.parametrize("dtype,d", [("F32", 128), ("F32", 64), ("BF16", 64)])
+@pytest.mark.parametrize("nsplit", [0, 1, 3, 64])
+def test_static_scratch_limit_of_the_types_sized_by_vector_alu_splits(lib, dtype, d, nsplit):
+    """fp32 and d = 64 are refused by the partials of the vector-ALU family's splits (or the forced count), whichever kernel
+    runs and however many of them it needs: also where one workgroup per pair would need none."""
+    splits, row = nsplit or 1, 16 * (d + 2) * 4    # (4096 / (pairs * 4) splits: one from 1024 pairs on)
+    pairs = max(1024, (8 << 20) // (row * splits) + 8) if nsplit == 0 else (8 << 20) // (row * splits) + 8
+    p = _problem(lib, B=pairs, Hq=16, Hkv=1, d=d, dtype=getattr(lib, dtype), k=64)
+    L = lib.lib()
+    assert L.scout_set_attn_mode(0, nsplit, 0) == 0
+    try:
+        assert L.sparse_decode_attn_static(ctypes.byref(p), FAKE, FAKE, FAKE, 4, *[FAKE] * 6, None) == lib.ESCRATCH
+    finally:
+        L.scout_set_attn_mode(0, 0, 0)
+
+
 def test_headers_are_plain_c_and_the_binding_has_the_header_layout(lib, tmp_path):
     """The three headers compile as C99 with no warnings, a C program links against the library and
     calls its host-only entry points, and the struct the Python binding marshals has the size and the

@@ -338,10 +338,13 @@ int recall_scatter(const scout_problem* p, const void* staged, int64_t n_tiles, 
  * all NULL (nothing offloaded).  sel_host / n_host tell the host which blocks
  * it has to cover for this query.  `scores` may be NULL for a caller that does
  * not need them (they then stay in the workspace or, where one workgroup does
- * the whole step of a pair, on the chip).  Launches: two where a pair is
- * spread over several workgroups (scoring; selection + attention + merge), one
- * where the pairs alone fill the chip (bf16, d = 128, at least 192 pairs) or
- * have little to read: every step of a pair in one workgroup.
+ * the whole step of a pair, on the chip).  Launches: two as a rule (scoring;
+ * selection + attention + merge); one where the pairs alone fill the chip (bf16,
+ * d = 128, at least 192 pairs of at most 2048 blocks, 1024 beyond 256 pairs) or
+ * have little to read: every step of a pair in one workgroup.  Three, the merge in
+ * a launch of its own, where that is faster (large groups spread over few
+ * workgroups) or a pair is spread over 64; up to four where rows are longer than
+ * 8192 blocks (the selection too).
  *
  * slot_gpu and n_gpu are read before they are written: what they hold on entry
  * is taken as a HINT of where this step's tiles will be (adjacent decode tokens

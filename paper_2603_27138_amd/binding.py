@@ -332,15 +332,13 @@ def recall_fetch(p: Problem, src_k, src_v, recall_blk, recall_slot, n_recall, k_
 
 def recall_scatter(p: Problem, staged, tile_off, recall_blk, recall_slot, n_recall, k_pool, v_pool, n_slots):
     """staged: device buffer of packed tiles [tiles][2][S][d]; tile_off: first tile of each pair."""
-    assert staged.numel() % (p.S * p.d * 2) == 0
-    if _recording is None:
-        return _done("recall_scatter", (_calls or _load_calls()).recall_scatter(
-            p, staged, staged.numel() // (p.S * p.d * 2), tile_off, recall_blk, recall_slot, n_recall, k_pool, v_pool,
-            n_slots))
     tile_elems = p.S * p.d * 2
     assert staged.numel() % tile_elems == 0
-    _call("recall_scatter", lib().recall_scatter, ctypes.byref(p), _ptr(staged), staged.numel() // tile_elems,
-          _ptr(tile_off), _ptr(recall_blk),
+    n_tiles = staged.numel() // tile_elems
+    if _recording is None:
+        return _done("recall_scatter", (_calls or _load_calls()).recall_scatter(
+            p, staged, n_tiles, tile_off, recall_blk, recall_slot, n_recall, k_pool, v_pool, n_slots))
+    _call("recall_scatter", lib().recall_scatter, ctypes.byref(p), _ptr(staged), n_tiles, _ptr(tile_off), _ptr(recall_blk),
           _ptr(recall_slot), _ptr(n_recall), _ptr(k_pool), _ptr(v_pool), int(n_slots), _stream())
 
 

@@ -25,6 +25,7 @@ int launch_attn(const Dims&, int, int, int, const void*, const void*, const void
                 const int32_t*, const int32_t*, const int32_t*, Partials, Epilogue, hipStream_t);
 int launch_combine(const Dims&, Partials, Epilogue, hipStream_t);
 bool select_attend_supported(const Dims&);
+bool fold_pays(const Dims&, int);
 int launch_select_attend(const Dims&, int, const void*, const float*, const int32_t*, const void*, const void*,
                          long long, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, Partials,
                          Epilogue, hipStream_t);
@@ -568,10 +569,10 @@ int scout_layer_step(const scout_problem* p, const void* q, const void* digest,
                        sel_host, n_host, carve(ws, L, A), E, st);
   if (scores == nullptr) scores = reinterpret_cast<float*>(static_cast<char*>(ws) + L.scores);
   if (g_fuse_select && A.family == 2 && A.waves == 8 && select_attend_supported(D)) {
-    // selection rides in the head of the attention kernel, and the last workgroup of a pair folds its splits: two
-    // launches for the whole step
+    // selection rides in the head of the attention kernel, and the last workgroup of a pair folds its splits where that
+    // pays: two launches for the whole step, or three
     Partials P = carve(ws, L, A);
-    const bool fold = A.nsplit > 1 && carve_counters(D, ws, L, A, &P);
+    const bool fold = A.nsplit > 1 && fold_pays(D, A.nsplit) && carve_counters(D, ws, L, A, &P);
     rc = launch_score(D, p->dtype, q, digest, scores, P.arrived, st);
     if (rc != SCOUT_OK) return rc;
     Epilogue part{};

@@ -385,9 +385,9 @@ constexpr int unit_depth() { return Tile<DT, DH>::UNITB >= 4096 ? 1 : 2; }
 // another is written through to device memory and read past the caches (agent scope), and a workgroup counts itself as
 // arrived only when its stores have been acknowledged.  Nobody waits for anybody: the workgroup that finds itself the
 // last one does the rest, the others end.  A launch of its own (combine_kernel) costs a kernel boundary and the trip
-// that reads the partials: a step of one sequence (8 pairs of 16 splits) took
-// 19.1 us with it and 17.0 without, 4 sequences of 131k tokens (32 x 8) 30.7 and 29.4, 8 of 32k (64 x 4) 29.3 and 28.9, 16
-// of 32k (128 x 2) 35.1 and 34.7.
+// that reads the partials: a step of one sequence (8 pairs x 16 splits, 4 heads) takes 16.1 us with it and 14.0 without, 4
+// sequences of 131k tokens (32 x 8, 8 heads) 34.6 and 33.7, 8 of 32k (64 x 4, 4 heads) 23.1 and 22.7.  Where it pays: see
+// fold_pays.
 constexpr int kAgentScope = 16;  // cache policy sc1 of the buffer instructions
 
 struct SharedPartials {
@@ -1359,6 +1359,17 @@ int launch_attn(const Dims& D, int dtype, int family, int waves, const void* q, 
 #undef SCOUT_VALU
   }
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
+}
+
+// Whether the last workgroup of a pair folds its splits, or a launch of its own does.  One workgroup folds nsplit * G * d
+// floats where combine_kernel has one per head, so it pays for few heads or many splits, and with 8 heads of 128 channels also
+// where all workgroups run at once (the fold of one does not hold up the next).  A step with the fold in the launch over
+// one without, bf16, d = 128, lists of 32 to 128 blocks: 1 to 4 heads 0.94 to 1.00 whatever the splits; 8 heads: 8 splits 0.95, 4
+// splits 0.99, 96 pairs x 3 1.01 to 1.02, 128 x 2 0.995 to 1.00, 184 x 2 1.005; 16 heads: 8 splits 0.99, 4 splits 1.01 to 1.02, 3
+// splits 1.02 to 1.03, 2 splits 1.01 to 1.02.  d = 64: up to 8 heads 0.93 to 1.00; 16 heads 0.93 to 0.98 from 4 splits on, 96 x 3 1.00 to
+// 1.02, 128 x 2 1.00, 184 x 2 1.00 to 1.01.  fp32, d = 128: 0.96 to 1.00 from 4 splits on, 128 x 2 0.98 to 1.00, 184 x 2 1.01 to 1.04.
+bool fold_pays(const Dims& D, int nsplit) {
+  return nsplit * 256 >= D.G * D.d || (D.G * D.d <= 1024 && D.B * D.Hkv * nsplit <= 256);
 }
 
 bool select_attend_supported(const Dims& D) { return D.max_blocks <= 8 * kWave * 16; }

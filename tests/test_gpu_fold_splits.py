@@ -1,6 +1,7 @@
 """The fused step's own fold of a pair's splits against the fold by a launch of its own (the separate calls), from the
-lists that the step wrote: split counts from 2 to 63 folded in the launch and 64 by the second launch, groups that divide
-the workgroup's threads and groups that do not, more splits than one pass of the fold requests, shares that are empty.
+lists that the step wrote: split counts and groups on both sides of the line between the two, up to 63 splits folded
+in the launch and 64 by the second launch, groups that divide the workgroup's threads and groups that do not, more splits
+than one pass of the fold requests, shares that are empty.
 
 The workspace starts as garbage, and the step is repeated on it: its counters must come from the step itself.
 
@@ -23,7 +24,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("G,k,nsplits", [(1, 8, (2, 3)), (3, 40, (2, 7, 33)), (4, 64, (16, 63, 64)), (8, 24, (2, 4, 9)),
-                                         (16, 12, (2, 5, 64))])
+                                         (16, 12, (2, 5, 64)), (16, 12, (3, 4, 7, 8, 33)), (8, 24, (3, 33))])
 def test_fold_in_the_launch(dtype, d, G, k, nsplits):
     Hkv, S = 2, 16
     ctx = (S * 90 + 5, 0, 3, S * 41)

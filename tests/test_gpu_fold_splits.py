@@ -7,7 +7,8 @@ The workspace starts as garbage, and the step is repeated on it: its counters mu
 
 The separate attention deals the tokens to the waves in another order, so the partials differ as well as the order in
 which they are added.  Binary32: at most 64 tokens per wave and 64 partials are added, each sum rounded once, and the
-weights are rescaled a few times: 200 * 2^-24 = 1.2e-5 of the largest value.  bf16: a weight is rounded to bf16 against the
+weights are rescaled a few times: 200 * 2^-24 = 1.2e-5 of the largest value.  bf16 (with d = 128; d = 64 keeps its weights
+in binary32 and is held to the same bound): a weight is rounded to bf16 against the
 maximum its wave knows, 2^-9 relative on either side, so 2^-8 on the weight sum (absolutely, on its logarithm) and 2^-8 of
 the largest value vector element on the outputs, and one step of the output's type, 2^-8, more.
 """

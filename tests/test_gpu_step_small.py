@@ -4,7 +4,7 @@ stream, empty sequences, budgets above the block count; then sizes on each limit
 untouched workspace shows which route a call took (a launch of its own for the scores leaves them there).
 
 Scores and lists are equal bit for bit.  Outputs: both add the same values in binary32 in another order, at most 64 tokens
-per wave and 8 partials: 200 * 2^-24 = 1.2e-5 of the largest value; for bf16 the weights are rounded to bf16 against the
+per wave and 8 partials: 200 * 2^-24 = 1.2e-5 of the largest value; for bf16 with d = 128 the weights are rounded to bf16 against the
 maximum a wave knows, 2^-9 relative on either side, and the output to bf16 (see test_gpu_fold_splits.py)."""
 import pytest
 import torch

@@ -117,6 +117,20 @@ def test_append_matches_oracle_bit_for_bit(dtype, d, S):
     assert st.ctx[3] == mb * S and st.ctx[4] == mb * S and st.ctx[0] == 2 * S + 3
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("Hkv,d", [(1, 64), (5, 64), (33, 128)])
+def test_append_rows_below_and_beyond_a_workgroup(dtype, Hkv, d):
+    """Four channels per thread: 16 threads' work, a last wave that is partly empty, and more than 1024 threads' work."""
+    S, mb = 16, 2
+    st = State(dtype, 3, Hkv, d, S, mb, [0, 5, mb * S - 1], seed=19)
+    p = st.problem(Hq=Hkv, k=1)
+    for step in range(3):
+        k, v, ns = st.draw()
+        st.host_append(k, v, ns)
+        st.dev_append(p, k, v, ns)
+        st.assert_same(step)
+
+
 def test_append_rejects_bad_arguments():
     st = State("f32", 1, 1, 64, 16, 2, [3], seed=1)
     p = st.problem(Hq=1, k=1)

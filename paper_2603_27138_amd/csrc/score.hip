@@ -341,60 +341,53 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   }
 }
 
-// The same stream with the group's heads combined by their maximum instead of their sum.  The fold of
-// the group is not possible then: every head keeps its own estimate, sum over channels of the larger
-// of q*min and q*max, which is P_h . max + N_h . min with the positive and negative parts of that head's
-// queries.  G times the multiply-adds of the folded kernel on the same loads, so the arithmetic, not the
-// stream, sets the pace, and everything around the multiply-adds is kept small:
-//  * the per-head coefficients are made once per workgroup, as binary64 in LDS, and a wave takes
-//    16 loads per lane (2 to 8 entries per lane) so that each coefficient it reads serves that many entries;
-//  * heads are taken four at a time, or eight where the group has more than four (one pass, an element
-//    converted to binary64 once, for the common group of eight);
-//  * the sums of (entries per lane) x 4 heads are added across the 8 lanes of an entry by a butterfly
-//    that exchanges half of the remaining sums at each of its three steps, instead of three steps for
-//    every sum: 7/8 of a step per sum.
-// Heads beyond G in the last pass repeat head G - 1, which leaves the maximum as it is.
-template <int N, int LEVEL>
-__device__ __forceinline__ void halve_across(double* a, bool hi) {
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) {
-    const double keep = hi ? a[i + N / 2] : a[i], send = hi ? a[i] : a[i + N / 2];
-    a[i] = keep + partner_f64<LEVEL>(send);
-  }
-}
-
-constexpr int score_max_entries(int lines) { return 16 / lines < 4 ? 16 / lines : 4; }  // per lane
-
+// The same stream with an estimate per head instead of their sum: for the maximum over the group's heads, and for a
+// selection per query head.  The fold of the group is not possible then: a head's estimate is the sum over channels of
+// the larger of q*min and q*max, which is P_h . max + N_h . min with the positive and negative parts of that head's
+// queries, a contraction over 2 d elements of an entry, and the binary64 matrix instructions take it: heads are rows,
+// digest entries are columns.  On the vector ALU every multiply-add needs a coefficient of its own in a register
+// (1 KiB of LDS reads per four of them) and every sum is spread over 8 lanes; here an operand of four heads' coefficients
+// serves 16 entries, and a lane ends up with whole sums.
+//  * an entry belongs to lane % 16, and lane / 16 says which 16 bytes of each 64-byte piece of it the lane holds: element s
+//    of the four lanes is the contraction index of one instruction (any labelling does if both operands agree);
+//  * up to eight heads go four at a time (4x4x4, four blocks: the same four heads times four entries each), more than
+//    eight through 16x16x4; either leaves the estimate of head 4 * quad + lane / 16 for entry lane % 16 in acc[.][quad];
+//  * the coefficients are made once per workgroup, as binary64 in LDS, in the order of use.
+// A wave takes 16 entries.  Bound by the matrix cores behind the head of the stream: 64 pairs x 1024 blocks, bf16, d = 128,
+// eight heads: the multiply-adds take 4.0 us at the rate of the 4x4x4 (7.9 ns per instruction and SIMD; 16x16x4: 28 ns for
+// four times the work), the launch 9.5 (11.4 on the vector ALU; 7.2 with the heads summed); 16 heads 13.1 (19.1), 4 heads
+// 8.0 (8.7); 8 pairs x 600 blocks 4.1 (6.3); 128 x 1024, 16 heads, d = 64 12.7 (18.5), fp32, d = 128 27.1 (38.6).  32 entries per wave, which
+// halves the reads of coefficients, lengthen the chain behind a wave's last load: 10.6 at 64 pairs, 6.2 at 8.
+//
 // ROWS: every head's estimate goes to a row of its own, scores[B][Hq][max_blocks] (a selection per query head:
 // one pass over the KV head's digests serves its G query heads), instead of their maximum into the KV head's row.
-//
-// FEW: registers for two waves per SIMD, for launches that do not fill the chip with more than that anyway
-// (launch_score_max_hc): the coefficients of the steps ahead are read from LDS while the multiply-adds of this one
-// run.  With three waves' registers the compiler reads them step by step and the two waves spent half of their cycles
-// waiting for LDS.
-template <int DT, int DH, int HC, bool ROWS, bool FEW>
-__global__ __launch_bounds__(kScoreWaves* kWave) __attribute__((amdgpu_waves_per_eu(1, FEW ? 2 : 8))) void score_max_kernel(Dims D, const void* q, const void* digest,
-                                                                      float* scores, uint32_t* arrived) {
-  constexpr int EPL = (DT == SCOUT_BF16) ? 8 : 4;   // elements per 16-byte load
-  constexpr int ESZ = (DT == SCOUT_BF16) ? 2 : 4;
-  constexpr int EB = 2 * DH * ESZ;                  // bytes per digest entry
-  constexpr int NL = EB / 128;                      // 128-byte lines per entry
-  constexpr int E = score_max_entries(NL);          // entries per lane
-  constexpr int V = E * HC;                         // sums per lane and pass (HC heads per pass: 4 or 8)
-  constexpr int W = HC == 8 ? 2 : 4;                // elements per step of the inner loop
-  constexpr int BLK_PER_WAVE = 8 * E;
-  constexpr int NT = kScoreWaves * kWave;
-  static_assert(NL >= 2 && NL <= 8 && V >= 8 && (HC / (V / 8) == 2 || HC / (V / 8) == 4), "layout");
+typedef __attribute__((ext_vector_type(2))) double f64x2;
+typedef __attribute__((ext_vector_type(4))) double f64x4;
 
-  // [head][0: N_h, goes with the min row; 1: P_h][channel], the channels of a row in the order in which the
-  // lanes read them: a lane's EPL channels of a line are EPL / 2 reads of 16 bytes, and the 8 lanes of an
-  // entry read 128 consecutive bytes each time (channel by channel they would be 64 bytes apart and
-  // collide on the banks)
-  __shared__ __align__(16) double coef_lds[16][2][DH];
-  constexpr int CPL = 128 / ESZ;  // channels per line
-  auto coef_at = [](int c) {      // where channel c of a row sits
-    const int lr = c / CPL, l8 = (c % CPL) / EPL, i = c % EPL;
-    return ((lr * (EPL / 2) + i / 2) * 8 + l8) * 2 + (i & 1);
+template <int DT, int DH>
+struct HeadTile {
+  static constexpr int ESZ = (DT == SCOUT_BF16) ? 2 : 4;
+  static constexpr int EPL = 16 / ESZ;              // elements per 16-byte load
+  static constexpr int EB = 2 * DH * ESZ;           // bytes per digest entry
+  static constexpr int NU = EB / 64;                // 64-byte pieces per entry: min row, then max row
+  static constexpr int BLOCKS = 16;                 // entries per wave
+  static constexpr int STEPS = NU * EPL;            // instructions of a contraction
+};
+
+// NQ: quads of heads (1, 2, 4); heads beyond G repeat head G - 1, which leaves the maximum as it is.
+template <int DT, int DH, int NQ, bool ROWS>
+__global__ __launch_bounds__(kScoreWaves* kWave) void score_heads_kernel(Dims D, const void* q, const void* digest,
+                                                                         float* scores, uint32_t* arrived) {
+  using T = HeadTile<DT, DH>;
+  constexpr int EPL = T::EPL, EB = T::EB, NU = T::NU, STEPS = T::STEPS;
+  constexpr int NT = kScoreWaves * kWave, HEADS = 4 * NQ;
+  constexpr bool WIDE = NQ == 4;
+
+  // [step / 2][operand][lane of the operand][step % 2]; an operand of 4x4x4 is the same in its four blocks: 16 lanes
+  __shared__ __align__(16) double coef_lds[STEPS * HEADS * 4];
+  auto coef_at = [](int h, int u, int kk, int s) {  // head h, piece u, element s of lane / 16 == kk
+    const int lane16 = WIDE ? kk * 16 + h : (h >> 2) * 16 + kk * 4 + (h & 3);
+    return ((u * EPL + s) / 2 * (HEADS * 4) + lane16) * 2 + (s & 1);
   };
 
   const int pair = grid_pair();  // grid (x, Hkv, B)
@@ -402,128 +395,101 @@ __global__ __launch_bounds__(kScoreWaves* kWave) __attribute__((amdgpu_waves_per
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nb = num_blocks_of(D, b);
-  const int j_wave = (blockIdx.x * kScoreWaves + wave) * BLK_PER_WAVE;
+  const int j_wave = (blockIdx.x * kScoreWaves + wave) * T::BLOCKS;
   const bool active = j_wave < D.max_blocks;
   const int n_rows = ROWS ? D.G : 1;  // rows of `scores` per pair
   if (arrived != nullptr && blockIdx.x == 0 && (int)threadIdx.x < n_rows) arrived[pair * n_rows + threadIdx.x] = 0;
-  if ((int)blockIdx.x * kScoreWaves * BLK_PER_WAVE >= nb) {  // as in score_kernel: only the rows' tails to mark
-    for (int t = threadIdx.x; t < kScoreWaves * BLK_PER_WAVE; t += NT) {
-      const int j = (int)blockIdx.x * kScoreWaves * BLK_PER_WAVE + t;
+  if ((int)blockIdx.x * kScoreWaves * T::BLOCKS >= nb) {  // as in score_kernel: only the rows' tails to mark
+    for (int t = threadIdx.x; t < kScoreWaves * T::BLOCKS; t += NT) {
+      const int j = (int)blockIdx.x * kScoreWaves * T::BLOCKS + t;
       if (j < D.max_blocks)
         for (int r = 0; r < n_rows; ++r) scores[((size_t)pair * n_rows + r) * D.max_blocks + j] = -INFINITY;
     }
     return;
   }
 
-  // queries first (see score_kernel for why the order of issue matters)
-  constexpr int QPT = 16 * DH / NT;  // elements per thread
-  static_assert(16 * DH % NT == 0, "layout");
-  const int heads4 = (D.G + HC - 1) & ~(HC - 1);  // heads that are read, the repeated ones included
+  // queries first (see score_kernel for why the order of issue matters); a thread's elements are dealt so that the
+  // coefficients a wave writes together lie side by side in LDS
+  constexpr int QPT = HEADS * DH / NT;
+  static_assert(HEADS * DH % NT == 0 && 4 * EPL * (NU / 2) == DH, "layout");
+  auto q_elem = [](int e, int& h, int& p, int& kk, int& s) {
+    const int x = e >> 5, s_hi = x % (EPL / 2);
+    s = s_hi * 2 + ((e >> 2) & 1);
+    kk = (e >> 3) & 3;
+    p = x / (EPL / 2) % (NU / 2);  // piece of the row
+    h = (x / (EPL / 2) / (NU / 2)) * 4 + (e & 3);
+  };
   float qreg[QPT];
 #pragma unroll
   for (int i = 0; i < QPT; ++i) {
-    const int e = threadIdx.x + i * NT, h = e / DH, c = e % DH;
+    int h, p, kk, s;
+    q_elem(threadIdx.x + i * NT, h, p, kk, s);
     const int hs = h < D.G ? h : D.G - 1;
-    qreg[i] = load1<DT>(q, ((size_t)b * D.Hq + g * D.G + hs) * DH + c);
+    qreg[i] = load1<DT>(q, ((size_t)b * D.Hq + g * D.G + hs) * DH + (p * 4 + kk) * EPL + s);
   }
   const char* dpair = static_cast<const char*>(digest) + (size_t)kv_row(D, pair) * D.max_blocks * EB;
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(dpair), 0, active ? nb * EB : 0, 0x00020000);
-  const int voff0 = (j_wave + (lane >> 3)) * EB + (lane & 7) * 16;
-  u32x4 raw[E * NL];  // load gq * NL + u: line u of the lane's entry in group gq of 8 entries
+  const int voff0 = (j_wave + (lane & 15)) * EB + (lane >> 4) * 16;
+  u32x4 raw[NU];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int u = 0; u < NL; ++u)  // requested in the order of use: line by line, the E entries of a line together
-#pragma unroll
-    for (int gq = 0; gq < E; ++gq)
-      raw[gq * NL + u] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff0 + gq * 8 * EB + u * 128, 0, 0));
+  for (int u = 0; u < NU; ++u)  // requested in the order of use
+    raw[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff0 + u * 64, 0, 0));
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < QPT; ++i) {
-    const int e = threadIdx.x + i * NT, h = e / DH, c = e % DH;
-    if (h < heads4) {
-      coef_lds[h][0][coef_at(c)] = (double)fminf(qreg[i], 0.0f);
-      coef_lds[h][1][coef_at(c)] = (double)fmaxf(qreg[i], 0.0f);
-    }
+    int h, p, kk, s;
+    q_elem(threadIdx.x + i * NT, h, p, kk, s);
+    coef_lds[coef_at(h, p, kk, s)] = (double)fminf(qreg[i], 0.0f);
+    coef_lds[coef_at(h, p + NU / 2, kk, s)] = (double)fmaxf(qreg[i], 0.0f);
   }
   __syncthreads();
 
-  const bool b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1, b0 = lane & 1;
-  // what the butterfly below leaves in this lane: sums (lane & 7) * V / 8 + r of the V, that is heads
-  // hh_mine + r of the pass for the entry of group gq_mine
-  constexpr int R = V / 8;
-  const int gq_mine = (lane & 7) * R / HC, hh_mine = (lane & 7) * R % HC;
-  const int j = j_wave + gq_mine * 8 + (lane >> 3);
-  const bool kept = j < D.n_sink || j >= nb - D.n_tail;  // always-kept blocks rank above every score
-  double best = -INFINITY;
-  for (int h0 = 0; h0 < D.G; h0 += HC) {
-    double acc[V];  // sum of entry group gq, head h0 + hh at gq * HC + hh
+  f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+  const f64x2* coef = reinterpret_cast<const f64x2*>(coef_lds) + (WIDE ? lane : (lane >> 4) * 4 + (lane & 3));
 #pragma unroll
-    for (int i = 0; i < V; ++i) acc[i] = 0.0;
-    // (the loaded words are declared changed here: otherwise their binary64 forms, which do not depend on
-    // the pass, are all made ahead of the loop and take four times the registers of the words themselves)
+  for (int u = 0; u < NU; ++u) {
 #pragma unroll
-    for (int it = 0; it < E * NL; ++it)
-      asm volatile("" : "+v"(raw[it][0]), "+v"(raw[it][1]), "+v"(raw[it][2]), "+v"(raw[it][3]));
+    for (int s2 = 0; s2 < EPL / 2; ++s2) {
+      f64x2 cf[WIDE ? 1 : NQ];
 #pragma unroll
-    for (int u = 0; u < NL; ++u) {
-      // line u of an entry: min row for u < NL/2, max row after; channels c0 .. c0 + EPL of that row
-      const int row = u / (NL / 2), c0 = (u % (NL / 2)) * CPL + (lane & 7) * EPL;
+      for (int o = 0; o < (WIDE ? 1 : NQ); ++o) cf[o] = coef[(u * (EPL / 2) + s2) * (HEADS * 4) + o * 16];
 #pragma unroll
-      for (int i0 = 0; i0 < EPL; i0 += W) {  // W elements at a time: HC x W coefficients in registers
-        double cf[HC][W];
+      for (int e = 0; e < 2; ++e) {
+        double x;
+        if (DT == SCOUT_BF16) x = (double)(e ? bf16_hi(raw[u][s2 % 4]) : bf16_lo(raw[u][s2 % 4]));
+        else x = (double)__uint_as_float(raw[u][(s2 * 2 + e) % 4]);
+        if constexpr (WIDE) {
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(cf[0][e], x, acc, 0, 0, 0);
+        } else {
 #pragma unroll
-        for (int hh = 0; hh < HC; ++hh)
-#pragma unroll
-          for (int i = 0; i < W; ++i) cf[hh][i] = coef_lds[h0 + hh][row][coef_at(c0 + i0 + i)];
-#pragma unroll
-        for (int gq = 0; gq < E; ++gq) {
-          const u32x4 w = raw[gq * NL + u];
-          double x[W];
-#pragma unroll
-          for (int i = 0; i < W; ++i) {
-            if (DT == SCOUT_BF16)
-              x[i] = (double)(((i0 + i) & 1) ? bf16_hi(w[(i0 + i) >> 1]) : bf16_lo(w[(i0 + i) >> 1]));
-            else
-              x[i] = (double)__uint_as_float(w[i0 + i]);
-          }
-#pragma unroll
-          for (int hh = 0; hh < HC; ++hh)
-#pragma unroll
-            for (int i = 0; i < W; ++i) acc[gq * HC + hh] = fma(cf[hh][i], x[i], acc[gq * HC + hh]);
+          for (int o = 0; o < NQ; ++o) acc[o] = __builtin_amdgcn_mfma_f64_4x4x4f64(cf[o][e], x, acc[o], 0, 0, 0);
         }
       }
     }
-    // across the 8 lanes of an entry: each step keeps the half of the sums that the lane's bit names and
-    // adds the partner's; V / 8 finished sums remain, index (4 b2 + 2 b1 + b0) * V / 8 + r of the V
-    halve_across<V, 2>(acc, b2);
-    halve_across<V / 2, 1>(acc, b1);
-    halve_across<V / 4, 0>(acc, b0);
-    if constexpr (ROWS) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int h = h0 + hh_mine + r;
-        if (h < D.G && j < D.max_blocks)
-          scores[((size_t)pair * D.G + h) * D.max_blocks + j] = j < nb ? (kept ? INFINITY : (float)acc[r]) : -INFINITY;
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < R; ++r) best = acc[r] > best ? acc[r] : best;  // heads of one entry (R divides HC)
-    }
   }
-  if constexpr (!ROWS) {
-    // lanes whose finished sums were heads of the same entry: HC / R of them, neighbours
-    if constexpr (HC / R >= 4) {
-      const double o = partner_f64<1>(best);
-      best = o > best ? o : best;
+
+  const int kk = lane >> 4;  // the head of its quad
+  const int j = j_wave + (lane & 15);
+  auto value = [&](double est) {  // always-kept blocks rank above every score
+    return j < nb ? (j < D.n_sink || j >= nb - D.n_tail ? INFINITY : (float)est) : -INFINITY;
+  };
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int o = 0; o < NQ; ++o) {
+      const int h = o * 4 + kk;
+      if (h < D.G && j < D.max_blocks) scores[((size_t)pair * D.G + h) * D.max_blocks + j] = value(acc[o]);
     }
-    if constexpr (HC / R >= 2) {
-      const double o = partner_f64<0>(best);
-      best = o > best ? o : best;
-    }
-    if (hh_mine == 0 && j < D.max_blocks)
-      scores[(size_t)pair * D.max_blocks + j] = j < nb ? (kept ? INFINITY : (float)best) : -INFINITY;
+  } else {
+    double best = -INFINITY;
+#pragma unroll
+    for (int o = 0; o < NQ; ++o) best = acc[o] > best ? acc[o] : best;
+    const double o16 = partner_f64<4>(best);
+    best = o16 > best ? o16 : best;
+    const double o32 = partner_f64<5>(best);
+    best = o32 > best ? o32 : best;
+    if (kk == 0 && j < D.max_blocks) scores[(size_t)pair * D.max_blocks + j] = value(best);
   }
 }
 
@@ -578,43 +544,29 @@ int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, 
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
-template <int HC, bool ROWS>
-static int launch_score_max_hc(const Dims& D, int dtype, const void* q, const void* digest, float* scores,
-                               uint32_t* arrived, hipStream_t st) {
-  const int lines = 2 * D.d * (dtype == SCOUT_BF16 ? 2 : 4) / 128;
-  const int blocks_per_wg = score_max_entries(lines) * 8 * kScoreWaves;  // 8 entries per wave-wide load
-  dim3 grid((D.max_blocks + blocks_per_wg - 1) / blocks_per_wg, D.Hkv, D.B);
-  dim3 block(kScoreWaves * kWave);
-  if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
-  // Where the line lies, 1024 blocks per pair, us with registers for two waves and without: bf16, d = 128, 8 heads, 512
-  // workgroups 11.6 and 13.6, 1024 18.5 and 21.2; 4 heads 1024 15.0 and 15.5, 1536 23.9 and 23.3, 2048 29.9 and 29.6; bf16, d = 64,
-  // 8 heads, own rows, 768 8.0 and 9.4, 1024 beyond the line 11.6 and 11.7; fp32, d = 128, 8 heads, 1024 15.0 and 16.6, 1536 (16 heads)
-  // 32.5 and 31.5, 4096 76 and 70; fp32, d = 64, 8 heads, 1024 14.1 and 14.8, 16 heads 20.0 and 21.3.  One light pass (up to four
-  // heads; fp32, or the maximum with d = 64) gains only where all workgroups run at once, two waves per SIMD: fp32, d = 64, 4 heads, 512
-  // 4.9 and 5.4, 768 9.8 and 8.9; fp32, d = 128, 520 6.8 and 6.5; bf16, d = 64, 520 5.6 and 5.5.
-  const bool light = D.G <= 4 && (D.d == 64 ? !ROWS : dtype == SCOUT_F32);
-  const long long line = light ? 512 : dtype == SCOUT_BF16 && D.d == 64 ? 768 : 1024;
-  const bool few = (long long)grid.x * grid.y * grid.z <= line;
-#define SCOUT_SCORE_MAX(DT, DH)                                                                                             \
+template <bool ROWS>
+static int launch_score_heads(const Dims& D, int dtype, const void* q, const void* digest, float* scores,
+                              uint32_t* arrived, hipStream_t st) {
+  if (D.max_blocks == 0 || D.Hkv == 0 || D.B == 0) return SCOUT_OK;
+#define SCOUT_SCORE_HEADS_NQ(DT, DH, NQ)                                                                                    \
   do {                                                                                                                      \
-    if (few)                                                                                                                \
-      hipLaunchKernelGGL((score_max_kernel<DT, DH, HC, ROWS, true>), grid, block, 0, st, D, q, digest, scores, arrived);    \
-    else                                                                                                                    \
-      hipLaunchKernelGGL((score_max_kernel<DT, DH, HC, ROWS, false>), grid, block, 0, st, D, q, digest, scores, arrived);   \
+    constexpr int per_wg = HeadTile<DT, DH>::BLOCKS * kScoreWaves;                                                          \
+    hipLaunchKernelGGL((score_heads_kernel<DT, DH, NQ, ROWS>), dim3((D.max_blocks + per_wg - 1) / per_wg, D.Hkv, D.B),      \
+                       dim3(kScoreWaves * kWave), 0, st, D, q, digest, scores, arrived);                                    \
   } while (0)
-  if (dtype == SCOUT_BF16 && D.d == 128) SCOUT_SCORE_MAX(SCOUT_BF16, 128);
-  else if (dtype == SCOUT_BF16) SCOUT_SCORE_MAX(SCOUT_BF16, 64);
-  else if (D.d == 128) SCOUT_SCORE_MAX(SCOUT_F32, 128);
-  else SCOUT_SCORE_MAX(SCOUT_F32, 64);
-#undef SCOUT_SCORE_MAX
+#define SCOUT_SCORE_HEADS(DT, DH)                              \
+  do {                                                         \
+    if (D.G <= 4) SCOUT_SCORE_HEADS_NQ(DT, DH, 1);             \
+    else if (D.G <= 8) SCOUT_SCORE_HEADS_NQ(DT, DH, 2);        \
+    else SCOUT_SCORE_HEADS_NQ(DT, DH, 4);                      \
+  } while (0)
+  if (dtype == SCOUT_BF16 && D.d == 128) SCOUT_SCORE_HEADS(SCOUT_BF16, 128);
+  else if (dtype == SCOUT_BF16) SCOUT_SCORE_HEADS(SCOUT_BF16, 64);
+  else if (D.d == 128) SCOUT_SCORE_HEADS(SCOUT_F32, 128);
+  else SCOUT_SCORE_HEADS(SCOUT_F32, 64);
+#undef SCOUT_SCORE_HEADS
+#undef SCOUT_SCORE_HEADS_NQ
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
-}
-
-static int launch_score_max(const Dims& D, int dtype, const void* q, const void* digest, float* scores, uint32_t* arrived,
-                            hipStream_t st) {
-  // groups of 5 to 8 heads in one pass of eight, every other size in passes of four
-  if (D.G > 4 && D.G <= 8) return launch_score_max_hc<8, false>(D, dtype, q, digest, scores, arrived, st);
-  return launch_score_max_hc<4, false>(D, dtype, q, digest, scores, arrived, st);
 }
 
 // A selection per query head (D describes every query head as a pair of its own that shares its KV head's
@@ -626,8 +578,7 @@ static int launch_score_rows(const Dims& D, int dtype, const void* q, const void
   K.Hkv = D.Hkv / D.share;
   K.share = 1;
   K.share_magic = 0;
-  if (K.G > 4 && K.G <= 8) return launch_score_max_hc<8, true>(K, dtype, q, digest, scores, arrived, st);
-  return launch_score_max_hc<4, true>(K, dtype, q, digest, scores, arrived, st);
+  return launch_score_heads<true>(K, dtype, q, digest, scores, arrived, st);
 }
 
 template <bool MEAN>
@@ -657,7 +608,7 @@ static int launch_score_sum(const Dims& D, int dtype, const void* q, const void*
 int launch_score(const Dims& D, int dtype, const void* q, const void* digest, float* scores, uint32_t* arrived,
                  hipStream_t st) {
   if (D.digest_kind == 1) return D.group_max ? SCOUT_EUNSUPPORTED : launch_score_sum<true>(D, dtype, q, digest, scores, arrived, st);
-  if (D.group_max) return launch_score_max(D, dtype, q, digest, scores, arrived, st);
+  if (D.group_max) return launch_score_heads<false>(D, dtype, q, digest, scores, arrived, st);
   if (D.share > 1) return launch_score_rows(D, dtype, q, digest, scores, arrived, st);
   return launch_score_sum<false>(D, dtype, q, digest, scores, arrived, st);
 }

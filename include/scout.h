@@ -181,6 +181,22 @@ int select_topk(const scout_problem* p, const float* scores, const int32_t* bloc
                 int32_t* sel_host, int32_t* n_host, void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * score_blocks and select_topk for a layer whose host part is about to be
+ * spawned (Alg. 1: the next layer's blocks, chosen with its predicted query):
+ * the same lists, and what the host's worker needs of them in host memory
+ * (pinned, GPU-addressable) by the time the call's work on the stream is done:
+ * no copies behind the selection.
+ *   job_sel  i32 [B][Hkv][k]   out: sel_host
+ *   job_n    i32 [B][Hkv]      out: n_host
+ *   job_q    e   [B][Hq][d]    out: q; 16-byte aligned
+ * Everything else as in score_blocks and select_topk.
+ */
+int scout_select_ahead(const scout_problem* p, const void* q, const void* digest, const int32_t* block_table,
+                       float* scores, int32_t* sel_all, int32_t* sel_gpu, int32_t* slot_gpu, int32_t* n_gpu,
+                       int32_t* sel_host, int32_t* n_host, int32_t* job_sel, int32_t* job_n, void* job_q,
+                       void* stream);
+
+/*
  * GPU-side partial attention (Sec. 3.2; Alg. 1 GPUAttn): for every query head,
  * softmax(sm_scale * q.K^T) V over all valid tokens of the listed resident
  * blocks, returned as a partial result (o, m, l):  m = max logit (natural-log
@@ -252,6 +268,8 @@ int scout_attn_partials(const scout_problem* p, const void* q, const void* k_poo
  * partial (Alg. 1 Merge) in one pass, instead of exporting (o, m, l) and
  * merging in a further launch.  host_* may be all NULL; lse may be NULL.
  *   host_o f32 [B][Hq][d], host_m, host_l f32 [B][Hq];  out e [B][Hq][d];  lse f32 [B][Hq]
+ * host_*: device memory, or pinned host memory, which the kernel then reads over
+ * the link itself.
  * The attention mode must not be changed between the two calls.
  */
 int scout_attn_finish(const scout_problem* p, const float* host_o, const float* host_m,

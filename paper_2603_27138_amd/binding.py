@@ -27,7 +27,7 @@ STATIC_SCRATCH_BYTES = 8 << 20
 
 EXPORTS = ["scout_version", "scout_strerror", "scout_workspace_bytes", "build_digests", "append_token", "score_blocks",
            "select_topk", "sparse_decode_attn", "merge_partials", "periodic_recall", "recall_fetch", "recall_scatter",
-           "scout_layer_step", "scout_set_attn_mode", "scout_attn_partials", "scout_attn_finish",
+           "scout_layer_step", "scout_set_attn_mode", "scout_attn_partials", "scout_attn_finish", "scout_select_ahead",
            "sparse_decode_attn_static"]
 # measurement aids live in a library of their own (include/scout_calib.h)
 CALIB_LIB_PATH = os.path.join(_HERE, "libscout_calib.so")
@@ -72,6 +72,7 @@ def lib():
         L.append_token.argtypes = [pp] + [vp] * 8 + [i64, vp, vp, vp]
         L.score_blocks.argtypes = [pp, vp, vp, vp, vp, sz, vp]
         L.select_topk.argtypes = [pp] + [vp] * 9 + [sz, vp]
+        L.scout_select_ahead.argtypes = [pp] + [vp] * 14
         L.sparse_decode_attn.argtypes = [pp, vp, vp, vp, i64] + [vp] * 7 + [sz, vp]
         L.sparse_decode_attn_static.argtypes = [pp, vp, vp, vp, i64] + [vp] * 6 + [vp]
         L.merge_partials.argtypes = [pp] + [vp] * 9
@@ -268,6 +269,17 @@ def select_topk(p: Problem, scores, block_table, sel_all, sel_gpu, slot_gpu, n_g
           _ptr(n_host), _ptr(ws), ws.numel(), _stream())
 
 
+def select_ahead(p: Problem, q, digest, block_table, scores, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, job_sel, job_n,
+                 job_q):
+    """score_blocks and select_topk, and the host's work list and queries written to job_* (pinned CPU tensors)."""
+    if _recording is None:
+        return _done("scout_select_ahead", (_calls or _load_calls()).select_ahead(
+            p, q, digest, block_table, scores, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, job_sel, job_n, job_q))
+    _call("scout_select_ahead", lib().scout_select_ahead, ctypes.byref(p), _ptr(q), _ptr(digest), _ptr(block_table),
+          _ptr(scores), _ptr(sel_all), _ptr(sel_gpu), _ptr(slot_gpu), _ptr(n_gpu), _ptr(sel_host), _ptr(n_host),
+          _ptr_addressable(job_sel), _ptr_addressable(job_n), _ptr_addressable(job_q), _stream())
+
+
 def sparse_decode_attn(p: Problem, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, o, m, l, ws):
     if _recording is None:
         return _done("sparse_decode_attn", (_calls or _load_calls()).sparse_decode_attn(
@@ -301,6 +313,15 @@ def attn_finish(p: Problem, host_o, host_m, host_l, out, lse, ws):
             p, host_o, host_m, host_l, out, lse, ws))
     _call("scout_attn_finish", lib().scout_attn_finish, ctypes.byref(p), _ptr(host_o), _ptr(host_m), _ptr(host_l),
           _ptr(out), _ptr(lse), _ptr(ws), ws.numel(), _stream())
+
+
+def attn_finish_ahead(p: Problem, host_o, host_m, host_l, out, lse, ws):
+    """attn_finish with the host's partials where its worker left them (pinned CPU tensors)."""
+    if _recording is None:
+        return _done("scout_attn_finish", (_calls or _load_calls()).attn_finish_ahead(
+            p, host_o, host_m, host_l, out, lse, ws))
+    _call("scout_attn_finish", lib().scout_attn_finish, ctypes.byref(p), _ptr_addressable(host_o), _ptr_addressable(host_m),
+          _ptr_addressable(host_l), _ptr(out), _ptr(lse), _ptr(ws), ws.numel(), _stream())
 
 
 def merge_partials(p: Problem, o_a, m_a, l_a, o_b, m_b, l_b, out, lse=None):

@@ -18,7 +18,7 @@ int launch_recall_scatter(const Dims&, int, const void*, long long, const int32_
 int launch_append(const Dims&, int, int32_t*, const void*, const void*, const int32_t*, void*, int32_t*, void*, void*,
                   long long, void*, void*, hipStream_t);
 int launch_topk(const Dims&, const float*, const int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
-                int32_t*, int32_t*, hipStream_t);
+                int32_t*, int32_t*, const HostJob*, hipStream_t);
 int launch_recall(const Dims&, const float*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
                   hipStream_t);
 int launch_attn(const Dims&, int, int, int, const void*, const void*, const void*, long long,
@@ -354,8 +354,25 @@ int select_topk(const scout_problem* p, const float* scores, const int32_t* bloc
   if (rc != SCOUT_OK) return rc;
   if (!scores || !block_table || !sel_all || !sel_gpu || !slot_gpu || !n_gpu || !sel_host || !n_host)
     return SCOUT_EINVAL;
-  return launch_topk(D, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host,
+  return launch_topk(D, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, nullptr,
                      static_cast<hipStream_t>(stream));
+}
+
+int scout_select_ahead(const scout_problem* p, const void* q, const void* digest, const int32_t* block_table,
+                       float* scores, int32_t* sel_all, int32_t* sel_gpu, int32_t* slot_gpu, int32_t* n_gpu,
+                       int32_t* sel_host, int32_t* n_host, int32_t* job_sel, int32_t* job_n, void* job_q, void* stream) {
+  Dims D;
+  int rc = check_problem(p, &D);
+  if (rc != SCOUT_OK) return rc;
+  if (!q || !digest || !scores || !block_table || !sel_all || !sel_gpu || !slot_gpu || !n_gpu || !sel_host || !n_host)
+    return SCOUT_EINVAL;
+  if (!job_sel || !job_n || !job_q) return SCOUT_EINVAL;
+  if (!aligned16(q) || !aligned16(digest) || !aligned16(scores) || !aligned16(job_q)) return SCOUT_EINVAL;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  rc = launch_score(D, p->dtype, q, digest, scores, nullptr, st);
+  if (rc != SCOUT_OK) return rc;
+  const HostJob job{job_sel, job_n, q, job_q, D.d * (p->dtype == SCOUT_BF16 ? 2 : 4)};
+  return launch_topk(D, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, &job, st);
 }
 
 int scout_attn_partials(const scout_problem* p, const void* q, const void* k_pool, const void* v_pool,
@@ -584,7 +601,7 @@ int scout_layer_step(const scout_problem* p, const void* q, const void* digest,
   }
   rc = launch_score(D, p->dtype, q, digest, scores, nullptr, st);
   if (rc != SCOUT_OK) return rc;
-  rc = launch_topk(D, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, st);
+  rc = launch_topk(D, scores, block_table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, nullptr, st);
   if (rc != SCOUT_OK) return rc;
   return run_attn(D, p->dtype, A, q, k_pool, v_pool, n_slots, sel_gpu, slot_gpu, n_gpu, ws, L, E, st);
 }

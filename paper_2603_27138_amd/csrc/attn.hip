@@ -511,7 +511,7 @@ __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pai
 // request.  At most 64 units per wave; sel / slot_list are not read.
 // FOLD: P.nsplit > 1, and the workgroup of a pair that finishes last folds the pair's partials and applies E itself
 // (fold_splits); `flag` is a word of LDS outside smem.
-template <int DT, int DH, int WAVES, int DEPTH, bool PRIVATE = false, bool FOLD = false>
+template <int DT, int DH, int WAVES, int DEPTH, bool PRIVATE = false, bool FOLD = false, bool STRIDE = false>
 __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int split,
                                             const QRegs<DT, DH>& qreg,
                                             const void* __restrict__ k_pool,
@@ -541,10 +541,14 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   // (at most 4096 units over at most 1024 waves: exact); an integer division here delays the first
   // tile request by a noticeable fraction of a microsecond.
   const int n_units = n << ush, n_waves = P.nsplit * WAVES, v = split * WAVES + wave;
-  const int per = P.waves_magic ? (int)__umulhi((uint32_t)n_units, P.waves_magic) : n_units;
-  const int extra = n_units - per * n_waves;
-  const int u0 = v * per + (v < extra ? v : extra);
-  const int u1 = u0 + per + (v < extra ? 1 : 0);
+  int u0 = v, u1 = n_units, step = n_waves;
+  if constexpr (!STRIDE) {
+    const int per = P.waves_magic ? (int)__umulhi((uint32_t)n_units, P.waves_magic) : n_units;
+    const int extra = n_units - per * n_waves;
+    u0 = v * per + (v < extra ? v : extra);
+    u1 = u0 + per + (v < extra ? 1 : 0);
+    step = 1;
+  }
 
   WaveState<L::NR> W;
   // DEPTH units are kept in flight per wave: the loads of the next ones are issued before a unit is
@@ -596,13 +600,13 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
       Entry ent[DEPTH];
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
-        ent[d] = read_entry<DH>(sel, slot_list, u0 + d, u1, ush, S, ctx, n_slots, D.tile_stride);
+        ent[d] = read_entry<DH>(sel, slot_list, u0 + d * step, u1, ush, S, ctx, n_slots, D.tile_stride);
         issue_unit<DT, DH>(buf[d], k_pool, v_pool, ent[d], ln, kg);
       }
-      for (int u = u0; u < u1; u += DEPTH) {
+      for (int u = u0; u < u1; u += DEPTH * step) {
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
-          const Entry nx = read_entry<DH>(sel, slot_list, u + d + DEPTH, u1, ush, S, ctx, n_slots, D.tile_stride);
+          const Entry nx = read_entry<DH>(sel, slot_list, u + (d + DEPTH) * step, u1, ush, S, ctx, n_slots, D.tile_stride);
           consume_unit<DT, DH, decltype(exact)::value>(W, buf[d], qreg, ent[d].valid, scale2, kg);
           ent[d] = nx;
           issue_unit<DT, DH>(buf[d], k_pool, v_pool, nx, ln, kg);
@@ -830,7 +834,7 @@ __device__ __forceinline__ Hint load_hint(const Dims& D, int pair, int lane, con
 // they were issued, and a touch takes a loaded memory system's full latency).  The touch goes through a
 // buffer descriptor that covers the unit, or nothing: no branch, so nothing ever waits for its value.
 // The caller keeps tk and tv alive (an empty asm that names them) until its own later loads have returned.
-template <int DT, int DH, int WAVES>
+template <int DT, int DH, int WAVES, bool STRIDE>
 __device__ __forceinline__ void touch_hint(const Dims& D, const Hint& h, const Partials& P, int v, int lane,
                                            const void* k_pool, const void* v_pool, long long n_slots,
                                            uint32_t& tk, uint32_t& tv) {
@@ -838,9 +842,12 @@ __device__ __forceinline__ void touch_hint(const Dims& D, const Hint& h, const P
   n = n < 0 ? 0 : (n > D.k ? D.k : n);
   const int ush = D.s_shift - 4;
   const int n_units = D.k <= 2 * kWave ? n << ush : 0;
-  const int per = P.waves_magic ? (int)__umulhi((uint32_t)n_units, P.waves_magic) : n_units;
-  const int extra = n_units - per * (P.nsplit * WAVES);
-  const int u0 = v * per + (v < extra ? v : extra);  // the first unit of this wave's share of the old list
+  int u0 = v;  // the first unit of this wave's share of the old list
+  if constexpr (!STRIDE) {
+    const int per = P.waves_magic ? (int)__umulhi((uint32_t)n_units, P.waves_magic) : n_units;
+    const int extra = n_units - per * (P.nsplit * WAVES);
+    u0 = v * per + (v < extra ? v : extra);
+  }
   const int uc = u0 < n_units ? u0 : 0;
   const int e = uc >> ush, sub = uc & ((1 << ush) - 1);
   long long slot = e < kWave ? __builtin_amdgcn_readlane(h.s_lo, e & (kWave - 1))
@@ -901,7 +908,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     int slot[KPL];
     load_keys<WAVES, KPL>(D, scores, table, pair, nb, sw, lane, key, slot);
     __builtin_amdgcn_sched_barrier(0);
-    touch_hint<DT, DH, WAVES>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
+    touch_hint<DT, DH, WAVES, REMAP>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
     __builtin_amdgcn_sched_barrier(0);
     Selector<WAVES, KPL> S{l_x, 0, sw};
     uint32_t sel = 0;
@@ -950,7 +957,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     if (tid == 0) l_n[0] = ng;
   }
   __syncthreads();
-  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P,
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD, REMAP>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P,
                                                                 E, smem, -1, -1, l_n + 1);
   asm volatile("" ::"v"(touched_k), "v"(touched_v));  // the touches stay loads, their registers reserved until they have returned
 }

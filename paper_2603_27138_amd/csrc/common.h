@@ -59,6 +59,15 @@ struct Epilogue {
   int dtype_out;
 };
 
+// What a selection leaves for the host's worker, in host memory that the GPU addresses.
+struct HostJob {
+  int32_t* sel;   // [pairs][k] the offloaded selected blocks, then -1
+  int32_t* n;     // [pairs]
+  const void* q;  // [pairs][G] rows of q_row bytes, copied to q_out
+  void* q_out;
+  int q_row;
+};
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t hi16) {
   return __uint_as_float(hi16 << 16);
 }

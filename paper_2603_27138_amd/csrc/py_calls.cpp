@@ -146,6 +146,7 @@ struct Table {
   decltype(&::append_token) append_token;
   decltype(&::score_blocks) score_blocks;
   decltype(&::select_topk) select_topk;
+  decltype(&::scout_select_ahead) scout_select_ahead;
   decltype(&::sparse_decode_attn) sparse_decode_attn;
   decltype(&::sparse_decode_attn_static) sparse_decode_attn_static;
   decltype(&::scout_attn_partials) scout_attn_partials;
@@ -214,6 +215,20 @@ PyObject* py_select_topk(PyObject*, PyObject* const* a, Py_ssize_t n) {
   SCOUT_RETURN(T.select_topk(p, scores, table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, ws, nws, st));
 }
 
+PyObject* py_select_ahead(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args A("scout_select_ahead", a, n, 14);
+  const auto* p = A.prob();
+  void *q = A.dev(), *digest = A.dev();
+  i32* table = A.dev<i32>();
+  float* scores = A.dev<float>();
+  i32 *sel_all = A.dev<i32>(), *sel_gpu = A.dev<i32>(), *slot_gpu = A.dev<i32>(), *n_gpu = A.dev<i32>(),
+      *sel_host = A.dev<i32>(), *n_host = A.dev<i32>();
+  i32 *job_sel = static_cast<i32*>(A.addressable()), *job_n = static_cast<i32*>(A.addressable());
+  void* job_q = A.addressable();
+  SCOUT_RETURN(T.scout_select_ahead(p, q, digest, table, scores, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, job_sel,
+                                    job_n, job_q, st));
+}
+
 PyObject* py_sparse_decode_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args A("sparse_decode_attn", a, n, 12);
   const auto* p = A.prob();
@@ -251,6 +266,18 @@ PyObject* py_attn_finish(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args A("scout_attn_finish", a, n, 7);
   const auto* p = A.prob();
   float *ho = A.dev<float>(), *hm = A.dev<float>(), *hl = A.dev<float>();
+  void* out = A.dev();
+  float* lse = A.dev<float>();
+  size_t nws;
+  void* ws = A.workspace(&nws);
+  SCOUT_RETURN(T.scout_attn_finish(p, ho, hm, hl, out, lse, ws, nws, st));
+}
+
+PyObject* py_attn_finish_ahead(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args A("scout_attn_finish", a, n, 7);
+  const auto* p = A.prob();
+  float *ho = static_cast<float*>(A.addressable()), *hm = static_cast<float*>(A.addressable()),
+        *hl = static_cast<float*>(A.addressable());
   void* out = A.dev();
   float* lse = A.dev<float>();
   size_t nws;
@@ -339,6 +366,7 @@ PyObject* py_bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   SCOUT_BIND(append_token);
   SCOUT_BIND(score_blocks);
   SCOUT_BIND(select_topk);
+  SCOUT_BIND(scout_select_ahead);
   SCOUT_BIND(sparse_decode_attn);
   SCOUT_BIND(sparse_decode_attn_static);
   SCOUT_BIND(scout_attn_partials);
@@ -375,10 +403,12 @@ PyMethodDef methods[] = {
     SCOUT_METHOD(append_token),
     SCOUT_METHOD(score_blocks),
     SCOUT_METHOD(select_topk),
+    SCOUT_METHOD(select_ahead),
     SCOUT_METHOD(sparse_decode_attn),
     SCOUT_METHOD(sparse_decode_attn_static),
     SCOUT_METHOD(attn_partials),
     SCOUT_METHOD(attn_finish),
+    SCOUT_METHOD(attn_finish_ahead),
     SCOUT_METHOD(merge_partials),
     SCOUT_METHOD(periodic_recall),
     SCOUT_METHOD(recall_fetch),

@@ -5,12 +5,17 @@
 
 namespace scout {
 
-template <int WAVES, int KPL>
+constexpr int kMaxK = 1024;
+
+// AHEAD: the host's work list and the queries it goes with (HostJob) leave in the same launch, by stores to host memory:
+// as copies of their own they cost the stream 5 and 10 us behind the selection, for 4 sequences of 8k tokens.
+template <int WAVES, int KPL, bool AHEAD>
 __global__ __launch_bounds__(WAVES* kWave) void topk_kernel(
     Dims D, const float* __restrict__ scores, const int32_t* __restrict__ table,
     int32_t* __restrict__ sel_all, int32_t* __restrict__ sel_gpu, int32_t* __restrict__ slot_gpu,
-    int32_t* __restrict__ n_gpu, int32_t* __restrict__ sel_host, int32_t* __restrict__ n_host) {
+    int32_t* __restrict__ n_gpu, int32_t* __restrict__ sel_host, int32_t* __restrict__ n_host, HostJob J) {
   __shared__ __attribute__((aligned(16))) int lds[selector_lds_ints<WAVES>()];
+  __shared__ int l_host[AHEAD ? kMaxK : 1];
   const int b = blockIdx.z, pair = grid_pair();  // grid (1, Hkv, B)
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nb = num_blocks_of(D, b);
@@ -19,6 +24,12 @@ __global__ __launch_bounds__(WAVES* kWave) void topk_kernel(
   uint32_t key[KPL];
   int slot[KPL];
   load_keys<WAVES, KPL>(D, scores, table, pair, nb, wave, lane, key, slot);
+  if constexpr (AHEAD) {  // the pair's query rows: contiguous, a multiple of 16 bytes
+    const size_t row = (size_t)D.G * J.q_row, at = pair * row;
+    for (int t = threadIdx.x * 16; t < (int)row; t += WAVES * kWave * 16)
+      *reinterpret_cast<uint4*>(static_cast<char*>(J.q_out) + at + t) =
+          *reinterpret_cast<const uint4*>(static_cast<const char*>(J.q) + at + t);
+  }
   Selector<WAVES, KPL> S{lds, 0, wave};
 
   uint32_t sel = 0;
@@ -42,9 +53,11 @@ __global__ __launch_bounds__(WAVES* kWave) void topk_kernel(
         slot_gpu[out0 + pos_gpu[r]] = slot[r];
       } else {
         sel_host[out0 + pos_all[r] - pos_gpu[r]] = i;
+        if constexpr (AHEAD) l_host[pos_all[r] - pos_gpu[r]] = i;
       }
     }
   }
+  if constexpr (AHEAD) __syncthreads();
   for (int t = threadIdx.x; t < D.k; t += WAVES * kWave) {
     if (t >= k_eff) sel_all[out0 + t] = -1;
     if (t >= ng) {
@@ -52,14 +65,14 @@ __global__ __launch_bounds__(WAVES* kWave) void topk_kernel(
       slot_gpu[out0 + t] = -1;
     }
     if (t >= nh) sel_host[out0 + t] = -1;
+    if constexpr (AHEAD) J.sel[out0 + t] = t < nh ? l_host[t] : -1;
   }
   if (threadIdx.x == 0) {
     n_gpu[pair] = ng;
     n_host[pair] = nh;
+    if constexpr (AHEAD) J.n[pair] = nh;
   }
 }
-
-constexpr int kMaxK = 1024;
 
 template <int WAVES, int KPL>
 __global__ __launch_bounds__(WAVES* kWave) void recall_kernel(
@@ -145,34 +158,40 @@ __global__ __launch_bounds__(WAVES* kWave) void recall_kernel(
 // other (1024 blocks: 4.6 us with 8 waves x 2 keys against 8.9 us with one wave x 16; 4096 blocks:
 // 6.0 us with 16 waves x 4 against 9.3 us with 4 waves x 16).
 
+#define SCOUT_TOPK(WAVES, KPL) topk_kernel<WAVES, KPL, false>
+#define SCOUT_TOPK_AHEAD(WAVES, KPL) topk_kernel<WAVES, KPL, true>
+#define SCOUT_RECALL(WAVES, KPL) recall_kernel<WAVES, KPL>
 #define SCOUT_TOPK_DISPATCH(KERNEL, ...)                                                     \
   do {                                                                                       \
     dim3 grid(1, D.Hkv, D.B);                                                                   \
     if (grid.x == 0) return SCOUT_OK;                                                        \
     if (D.max_blocks <= 256)                                                                 \
-      hipLaunchKernelGGL((KERNEL<1, 4>), grid, dim3(kWave), 0, st, __VA_ARGS__);             \
+      hipLaunchKernelGGL((KERNEL(1, 4)), grid, dim3(kWave), 0, st, __VA_ARGS__);             \
     else if (D.max_blocks <= 1024)                                                           \
-      hipLaunchKernelGGL((KERNEL<8, 2>), grid, dim3(8 * kWave), 0, st, __VA_ARGS__);         \
+      hipLaunchKernelGGL((KERNEL(8, 2)), grid, dim3(8 * kWave), 0, st, __VA_ARGS__);         \
     else if (D.max_blocks <= 4096)                                                           \
-      hipLaunchKernelGGL((KERNEL<16, 4>), grid, dim3(16 * kWave), 0, st, __VA_ARGS__);       \
+      hipLaunchKernelGGL((KERNEL(16, 4)), grid, dim3(16 * kWave), 0, st, __VA_ARGS__);       \
     else if (D.max_blocks <= 16384)                                                          \
-      hipLaunchKernelGGL((KERNEL<16, 16>), grid, dim3(16 * kWave), 0, st, __VA_ARGS__);      \
+      hipLaunchKernelGGL((KERNEL(16, 16)), grid, dim3(16 * kWave), 0, st, __VA_ARGS__);      \
     else                                                                                     \
       return SCOUT_EUNSUPPORTED;                                                             \
   } while (0)
 
 int launch_topk(const Dims& D, const float* scores, const int32_t* table, int32_t* sel_all,
                 int32_t* sel_gpu, int32_t* slot_gpu, int32_t* n_gpu, int32_t* sel_host,
-                int32_t* n_host, hipStream_t st) {
-  SCOUT_TOPK_DISPATCH(topk_kernel, D, scores, table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host,
-                      n_host);
+                int32_t* n_host, const HostJob* job, hipStream_t st) {
+  if (job != nullptr && D.k > kMaxK) return SCOUT_EUNSUPPORTED;
+  if (job != nullptr)
+    SCOUT_TOPK_DISPATCH(SCOUT_TOPK_AHEAD, D, scores, table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, *job);
+  else
+    SCOUT_TOPK_DISPATCH(SCOUT_TOPK, D, scores, table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, HostJob{});
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
 int launch_recall(const Dims& D, const float* scores, int32_t* table, int32_t* recall_blk,
                   int32_t* recall_slot, int32_t* evict_blk, int32_t* n_recall, hipStream_t st) {
   if (D.k > kMaxK) return SCOUT_EUNSUPPORTED;
-  SCOUT_TOPK_DISPATCH(recall_kernel, D, scores, table, recall_blk, recall_slot, evict_blk, n_recall);
+  SCOUT_TOPK_DISPATCH(SCOUT_RECALL, D, scores, table, recall_blk, recall_slot, evict_blk, n_recall);
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 

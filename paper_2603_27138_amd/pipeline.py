@@ -3,16 +3,15 @@
 While the GPU works on layer i, the blocks of layer i+1 are selected with the predicted query, the
 selected blocks that live on the host are handed to the host-side worker threads, and the GPU goes
 on with layer i: its own partial attention (real query) over the resident selected blocks, merged
-with the host's partial that was started during layer i-1.  Every few steps, after a layer's attention,
+with the host's partial that was started during layer i-1.  What goes to the host (work lists, predicted
+queries) and what comes back (partials) is written and read in pinned memory by the kernels themselves.  Every few steps, after a layer's attention,
 the blocks that became important return from the host (Sec. 3.4): the plan is made on the GPU, the
 host packs the planned tiles, a copy engine moves them and a small kernel puts them into the slots the
-plan freed, all beside the following layers' work.  This module only sequences calls and
-copies a few kilobytes of lists and partial results between host and device; every step of the
-method runs in the HIP library (device side) or in the worker threads (host side).
+plan freed, all beside the following layers' work.  This module only sequences calls;
+every step of the method runs in the HIP library (device side) or in the worker threads (host side).
 """
 from __future__ import annotations
 
-import math
 from dataclasses import dataclass
 from typing import Callable, List, Optional
 
@@ -37,14 +36,6 @@ class Layer:
     v_blocks: torch.Tensor
 
 
-def _side_by_side(shapes, dtype, **where):
-    """One flat buffer, then a contiguous view of each shape in it, one behind the other: what travels together
-    between host and device goes as one copy."""
-    sizes = [math.prod(s) for s in shapes]
-    flat = torch.empty(sum(sizes), dtype=dtype, **where)
-    return [flat] + [part.view(s) for part, s in zip(flat.split(sizes), shapes)]
-
-
 class _LayerBuffers:
     def __init__(self, Bn, Hq, Hkv, d, mb, k, tdt):
         dev = dict(device="cuda")
@@ -54,18 +45,17 @@ class _LayerBuffers:
         self.scores = torch.empty(*pairs, mb, **f32)
         self.sel_all, self.sel_gpu, self.slot_gpu = (torch.empty(*pairs, k, **i32) for _ in range(3))
         self.n_gpu = torch.empty(pairs, **i32)
-        # A copy costs what its submission and its place in the queue cost, not its few kilobytes: the host's work list is
-        # one buffer, its partials another (three copies a layer instead of six: 302 -> 283 us a step of four layers,
-        # 4 sequences of 8k tokens).
-        lists, parts = [(*pairs, k), pairs], [(Bn, Hq, d), (Bn, Hq), (Bn, Hq)]
-        self.to_host, self.sel_host, self.n_host = _side_by_side(lists, **i32)
-        self.from_host, self.ho, self.hm, self.hl = _side_by_side(parts, **f32)
+        self.sel_host, self.n_host = torch.empty(*pairs, k, **i32), torch.empty(pairs, **i32)
         self.out = torch.empty(Bn, Hq, d, dtype=tdt, **dev)
         self.lse = torch.empty(Bn, Hq, **f32)
         pin = dict(pin_memory=True)
-        self.to_host_h, self.sel_host_h, self.n_host_h = _side_by_side(lists, torch.int32, **pin)
+        # the host's job and its result: the GPU writes and reads them here.  A copy of these few kilobytes costs what its
+        # submission and its place in the queue cost: three of them a layer were 122 of a step's 287 us (four layers, 4
+        # sequences of 8k tokens).
+        self.sel_host_h, self.n_host_h = torch.empty(*pairs, k, dtype=torch.int32, **pin), torch.empty(pairs, dtype=torch.int32, **pin)
         self.q_pred_h = torch.empty(Bn, Hq, d, dtype=tdt, **pin)
-        self.from_host_h, self.ho_h, self.hm_h, self.hl_h = _side_by_side(parts, torch.float32, **pin)
+        self.ho_h = torch.empty(Bn, Hq, d, dtype=torch.float32, **pin)
+        self.hm_h, self.hl_h = (torch.empty(Bn, Hq, dtype=torch.float32, **pin) for _ in range(2))
         self.selected = torch.cuda.Event()
         # periodic recall: the plan (device, and the part the host needs in pinned memory)
         self.recall_blk, self.recall_slot, self.evict_blk = (torch.empty(*pairs, k, **i32) for _ in range(3))
@@ -118,11 +108,10 @@ class LayerAheadPipeline:
     # -- Algorithm 1, "trigger next layer's CPU-side pre-computation"
     def _trigger(self, i: int, q_pred: torch.Tensor):
         L, b = self.layers[i], self.buf[i]
-        B.score_blocks(self.p, q_pred, L.digest, b.scores, self.ws)
-        B.select_topk(self.p, b.scores, L.block_table, b.sel_all, b.sel_gpu, b.slot_gpu, b.n_gpu, b.sel_host,
-                      b.n_host, self.ws)
-        b.to_host_h.copy_(b.to_host, non_blocking=True)
-        b.q_pred_h.copy_(q_pred, non_blocking=True)
+        B.select_ahead(self.p, q_pred, L.digest, L.block_table, b.scores, b.sel_all, b.sel_gpu, b.slot_gpu, b.n_gpu,
+                       b.sel_host, b.n_host, b.sel_host_h, b.n_host_h, b.q_pred_h)
+        if q_pred.shape != b.q_pred_h.shape or q_pred.dtype != b.q_pred_h.dtype:
+            b.q_pred_h.copy_(q_pred, non_blocking=True)   # what a copy makes of it, or refuses
         b.selected.record()
 
     def _spawn(self, i: int):
@@ -143,8 +132,7 @@ class LayerAheadPipeline:
 
     def _merge(self, i: int):
         b = self.buf[i]
-        b.from_host.copy_(b.from_host_h, non_blocking=True)
-        B.attn_finish(self.p, b.ho, b.hm, b.hl, b.out, b.lse, self.ws)
+        B.attn_finish_ahead(self.p, b.ho_h, b.hm_h, b.hl_h, b.out, b.lse, self.ws)
 
     # -- Sec. 3.4: plan on the GPU (the table changes at once, in stream order) ...
     def _plan_recall(self, i: int, q: torch.Tensor):

@@ -6,8 +6,9 @@
 // counter, heaviest pairs first would not pay here: pairs are small (a few blocks) and there are many
 // more of them than threads.  A thread keeps one online-softmax stream per query head of the pair and
 // walks the pair's blocks once: a block's K rows are widened to binary32 once and used by all G
-// heads, then its V rows likewise.  The query heads of the group are the vector lanes of the logits
-// and of the softmax bookkeeping (no sums across lanes), the channels those of the value product.  Idle threads spin briefly on the job counter before they sleep:
+// heads, then its V rows likewise.  The channels are the vector lanes of both products, four heads (two without
+// AVX-512) at a time so that a row of K or V is loaded once for them; the query heads of the group are those of the softmax
+// bookkeeping.  Idle threads spin briefly on the job counter before they sleep:
 // a layer-step is tens to hundreds of microseconds, a futex wake-up alone is of that order.
 #include <atomic>
 #include <chrono>
@@ -44,6 +45,7 @@ struct Job {
   const int32_t* tile_off = nullptr;
 };
 
+#define SCOUT_HOST_LANES 8
 namespace scout_host_generic {
 using ::Job;
 #include "host_kernels.inc"
@@ -57,7 +59,17 @@ using ::Job;
 #include "host_kernels.inc"
 }  // namespace scout_host_avx2
 #pragma GCC pop_options
+#undef SCOUT_HOST_LANES
+#define SCOUT_HOST_LANES 16
+#pragma GCC push_options
+#pragma GCC target("avx2,fma,avx512f,avx512bw,avx512dq,avx512vl")
+namespace scout_host_avx512 {
+using ::Job;
+#include "host_kernels.inc"
+}  // namespace scout_host_avx512
+#pragma GCC pop_options
 #endif
+#undef SCOUT_HOST_LANES
 
 namespace {
 
@@ -77,12 +89,31 @@ void stage_pair(const Job& J, int pair) {
   }
 }
 
+#ifndef SCOUT_HOST_MAX_ISA
+#define SCOUT_HOST_MAX_ISA 2  // a build with 0 or 1 here runs the other copies whatever the processor has
+#endif
+#if defined(__x86_64__)
+// 0: the plain copy of the loops, 1: AVX2, 2: AVX-512
+int host_isa() {
+  if (SCOUT_HOST_MAX_ISA < 1 || !__builtin_cpu_supports("avx2") || !__builtin_cpu_supports("fma")) return 0;
+  return SCOUT_HOST_MAX_ISA > 1 && __builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512bw") &&
+                 __builtin_cpu_supports("avx512dq") && __builtin_cpu_supports("avx512vl")
+             ? 2
+             : 1;
+}
+#endif
+
 void run_pair(const Job& J, int pair, float* kf, float* vf) {
   if (J.kind == 1) return stage_pair(J, pair);
   const bool wide = J.p.Hq / J.p.Hkv > 8;
 #if defined(__x86_64__)
-  static const bool avx2 = __builtin_cpu_supports("avx2") && __builtin_cpu_supports("fma");
-  if (avx2) {
+  static const int isa = host_isa();
+  if (isa == 2) {
+    if (wide) scout_host_avx512::run_pair_nv<2>(J, pair, kf, vf);
+    else scout_host_avx512::run_pair_nv<1>(J, pair, kf, vf);
+    return;
+  }
+  if (isa == 1) {
     if (wide) scout_host_avx2::run_pair_nv<2>(J, pair, kf, vf);
     else scout_host_avx2::run_pair_nv<1>(J, pair, kf, vf);
     return;
@@ -124,7 +155,7 @@ struct scout_host_worker {
   }
 
   void loop() {
-    std::vector<float> kf((size_t)(kMaxS + 4) * kMaxD), vf((size_t)kMaxS * kMaxD);
+    std::vector<float> kf((size_t)kMaxS * kMaxD), vf((size_t)kMaxS * kMaxD);
     uint64_t seen = 0;
     for (;;) {
       // wait for a new generation: spin for a short while, then sleep

@@ -1388,11 +1388,11 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
                          int32_t* n_host, Partials P, Epilogue E, hipStream_t st) {
   const int pairs = D.B * D.Hkv;
   if (pairs == 0) return SCOUT_OK;
-  dim3 grid(P.nsplit, D.Hkv, D.B), block(8 * kWave);
+  dim3 grid(P.nsplit, D.Hkv, D.B);
   const bool remap = xcd_grid(D, P.nsplit, grid);
   const size_t lds = mfma_smem_bytes(D, 8) + (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4) * sizeof(int);
-#define SCOUT_SA_RUN(DT, DH, KPL, REMAP, FOLD)                                                                     \
-  hipLaunchKernelGGL((select_attend_kernel<DT, DH, KPL, REMAP, FOLD>), grid, block, lds, st, D, q, scores, table, \
+#define SCOUT_SA_RUN(DT, DH, KPL, REMAP, FOLD)                                                                           \
+  hipLaunchKernelGGL((select_attend_kernel<DT, DH, KPL, REMAP, FOLD>), grid, dim3(8 * kWave), lds, st, D, q, scores, table, \
                      k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)
 #define SCOUT_SA(DT, DH, KPL)                                                      \
   do {                                                                             \
@@ -1401,15 +1401,21 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
     else SCOUT_SA_RUN(DT, DH, KPL, false, false);                                  \
   } while (0)
   // All eight waves share the keys: measured faster than one wave selecting alone while seven wait
-  // (46.9 vs 44.1 us per step at 1024 blocks per pair), a lone wave issues too slowly.
+  // (46.9 vs 44.1 us per step at 1024 blocks per pair), a lone wave issues too slowly.  Eight more waves that leave after the
+  // selection cost more than they bring (32 pairs x 8 of 4096 blocks: 30.0 us a step instead of 29.3).  Sizes in between
+  // because a key costs whether it is there or not: a growing sequence has one block more than a power of two (64 pairs x 4
+  // of 1025: 26.9 instead of 27.0 us a step, d = 64 21.3 instead of 21.6; 256 pairs of 2049: 64.2 instead of 64.9).
   const int per_lane = (D.max_blocks + 8 * kWave - 1) / (8 * kWave);
-#define SCOUT_SA_TYPE(DT, DH)                    \
-  do {                                           \
-    if (per_lane <= 2) SCOUT_SA(DT, DH, 2);      \
-    else if (per_lane <= 4) SCOUT_SA(DT, DH, 4); \
-    else if (per_lane <= 8) SCOUT_SA(DT, DH, 8); \
+#define SCOUT_SA_TYPE(DT, DH)                      \
+  do {                                             \
+    if (per_lane <= 2) SCOUT_SA(DT, DH, 2);        \
+    else if (per_lane <= 3) SCOUT_SA(DT, DH, 3);   \
+    else if (per_lane <= 4) SCOUT_SA(DT, DH, 4);   \
+    else if (per_lane <= 6) SCOUT_SA(DT, DH, 6);   \
+    else if (per_lane <= 8) SCOUT_SA(DT, DH, 8);   \
+    else if (per_lane <= 12) SCOUT_SA(DT, DH, 12); \
     else if (per_lane <= 16) SCOUT_SA(DT, DH, 16); \
-    else return SCOUT_EUNSUPPORTED;              \
+    else return SCOUT_EUNSUPPORTED;                \
   } while (0)
   SCOUT_BY_TYPE(dtype, D.d, SCOUT_SA_TYPE);
 #undef SCOUT_SA_TYPE

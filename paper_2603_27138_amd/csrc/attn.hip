@@ -418,7 +418,7 @@ __device__ __forceinline__ void store_split(const SharedPartials& R, int row, in
 // for; part i folds splits i, i + parts, ..., four of them requested at a time, and the parts meet in LDS.
 template <int DH, int WAVES>
 __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pair, const Partials& P, const Epilogue& E,
-                                            float* smem, int* flag) {
+                                            const HostPart* hp, float* smem, int* flag) {
   constexpr int ROW = DH + 4, Q = DH / 4;  // Q: threads per head
   constexpr int NTHREADS = WAVES * kWave;
   const int G = D.G, wstride = G * ROW + 32;
@@ -430,13 +430,6 @@ __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pai
   if (__builtin_amdgcn_readfirstlane(*flag) != P.nsplit - 1) return;
 
   constexpr int kOutPerThread = (16 * DH + NTHREADS - 1) / NTHREADS;
-  HostPart hp[kOutPerThread];
-#pragma unroll
-  for (int t = 0; t < kOutPerThread; ++t) {
-    const int idx = threadIdx.x + t * NTHREADS;
-    const int hh = idx < G * DH ? idx / DH : 0;
-    hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
-  }
   const int slab = threadIdx.x / Q;                               // below 32
   const int part = (int)(((uint32_t)slab * P.g_magic) >> 16);     // slab / G
   const int h = slab - part * G, c = (threadIdx.x % Q) * 4;
@@ -511,14 +504,19 @@ __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pai
 // request.  At most 64 units per wave; sel / slot_list are not read.
 // FOLD: P.nsplit > 1, and the workgroup of a pair that finishes last folds the pair's partials and applies E itself
 // (fold_splits); `flag` is a word of LDS outside smem.
-template <int DT, int DH, int WAVES, int DEPTH, bool PRIVATE = false, bool FOLD = false, bool STRIDE = false>
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+
+// after_gather: called once the wave has consumed its units, for stores that should not hold up its first request.
+template <int DT, int DH, int WAVES, int DEPTH, bool PRIVATE = false, bool FOLD = false, bool STRIDE = false, class After = Nothing>
 __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int split,
                                             const QRegs<DT, DH>& qreg,
                                             const void* __restrict__ k_pool,
                                             const void* __restrict__ v_pool, long long n_slots,
                                             const int32_t* sel, const int32_t* slot_list, int n, int ctx,
                                             const Partials& P, const Epilogue& E, float* smem, int my_sel = -1,
-                                            int my_slot = -1, int* flag = nullptr) {
+                                            int my_slot = -1, int* flag = nullptr, After after_gather = After{}) {
   // per wave: [G][DH + 4] floats of o (padded rows), then m[16], l[16]
   using L = Tile<DT, DH>;
   constexpr int ROW = DH + 4;
@@ -623,6 +621,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
       for (int i = 0; i < 4; ++i) nan |= W.acc[r][i] != W.acc[r][i];
     if (__ballot(nan) != 0) gather(std::true_type{});  // see kWeights32
   }
+  after_gather();
   f32x4(&acc)[L::NR] = W.acc;
   float m_run = W.m, l_run = W.l;
 
@@ -636,7 +635,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   for (int t = 0; t < kOutPerThread; ++t) {
     const int idx = threadIdx.x + t * WAVES * kWave;
     const int hh = idx < G * DH ? idx / DH : 0;
-    if constexpr (!FOLD) hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
+    hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
   }
 
   // fold the waves of the workgroup through LDS
@@ -690,7 +689,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
         }
       }
     }
-    if constexpr (FOLD) fold_splits<DH, WAVES>(D, b, g, pair, P, E, smem, flag);
+    if constexpr (FOLD) fold_splits<DH, WAVES>(D, b, g, pair, P, E, hp, smem, flag);
     return;
   }
 #pragma unroll
@@ -889,7 +888,9 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   const int kpad = (D.k + 3) & ~3;  // keeps what follows 16-byte aligned
   int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
   int* l_slot = l_sel + kpad;
-  int* l_x = l_slot + kpad;
+  int* l_all = l_slot + kpad;   // the workgroup that writes the lists out: all of the selection, and the offloaded part
+  int* l_host = l_all + kpad;
+  int* l_x = l_host + kpad;
   int* l_n = l_x + selector_lds_ints<WAVES>();
 
   QRegs<DT, DH> qreg;
@@ -898,19 +899,25 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
 
   const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
   uint32_t touched_k = 0, touched_v = 0;
+  const size_t out0 = (size_t)pair * D.k;
+  const bool writer = split == 0;
+  int ng, nh, k_eff;
 
   {
     const int sw = wave;
+    float sc[KPL];
+    int slot[KPL];
+    load_scores<WAVES, KPL>(D, scores, table, pair, sw, lane, sc, slot);
+    Selector<WAVES, KPL> S{l_x, 0, sw};
+    S.prepare();
     int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;
     nb = nb < D.max_blocks ? nb : D.max_blocks;
-    const int k_eff = D.k < nb ? D.k : nb;
+    k_eff = D.k < nb ? D.k : nb;
     uint32_t key[KPL];
-    int slot[KPL];
-    load_keys<WAVES, KPL>(D, scores, table, pair, nb, sw, lane, key, slot);
+    mask_keys<WAVES, KPL>(nb, sw, lane, sc, key, slot);
     __builtin_amdgcn_sched_barrier(0);
     touch_hint<DT, DH, WAVES, REMAP>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
     __builtin_amdgcn_sched_barrier(0);
-    Selector<WAVES, KPL> S{l_x, 0, sw};
     uint32_t sel = 0;
     if (k_eff > 0) sel = S.best(key, k_eff, false);
     uint32_t gpu = 0;
@@ -918,47 +925,40 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     for (int r = 0; r < KPL; ++r)
       if (((sel >> r) & 1u) && slot[r] >= 0) gpu |= 1u << r;
     int pos_all[KPL], pos_gpu[KPL];
-    const int ng = S.positions2(sel, pos_all, gpu, pos_gpu);
-    const int nh = k_eff - ng;
-    const size_t out0 = (size_t)pair * D.k;
-    const bool writer = split == 0;
+    ng = S.positions2(sel, pos_all, gpu, pos_gpu);
+    nh = k_eff - ng;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
       if ((sel >> r) & 1u) {
         const int i = (sw * KPL + r) * kWave + lane;
-        if (writer) sel_all[out0 + pos_all[r]] = i;
         if ((gpu >> r) & 1u) {
           l_sel[pos_gpu[r]] = i;
           l_slot[pos_gpu[r]] = slot[r];
-          if (writer) {
-            sel_gpu[out0 + pos_gpu[r]] = i;
-            slot_gpu[out0 + pos_gpu[r]] = slot[r];
-          }
-        } else if (writer) {
-          sel_host[out0 + pos_all[r] - pos_gpu[r]] = i;
+        } else {
+          l_host[pos_all[r] - pos_gpu[r]] = i;
         }
+        l_all[pos_all[r]] = i;
       }
     }
-    const int tid = sw * kWave + lane;
-    if (writer) {
-      for (int t = tid; t < D.k; t += WAVES * kWave) {
-        if (t >= k_eff) sel_all[out0 + t] = -1;
-        if (t >= ng) {
-          sel_gpu[out0 + t] = -1;
-          slot_gpu[out0 + t] = -1;
-        }
-        if (t >= nh) sel_host[out0 + t] = -1;
-      }
-      if (tid == 0) {
-        n_gpu[pair] = ng;
-        n_host[pair] = nh;
-      }
-    }
-    if (tid == 0) l_n[0] = ng;
   }
   __syncthreads();
-  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD, REMAP>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P,
-                                                                E, smem, -1, -1, l_n + 1);
+  // The lists go out behind the tiles: stored here, in front of the first request, they held up the workgroup that writes
+  // them, and with it its pair, by a microsecond.
+  auto write_lists = [&]() __attribute__((always_inline)) {
+    if (!writer) return;
+    for (int t = threadIdx.x; t < D.k; t += WAVES * kWave) {
+      sel_all[out0 + t] = t < k_eff ? l_all[t] : -1;
+      sel_gpu[out0 + t] = t < ng ? l_sel[t] : -1;
+      slot_gpu[out0 + t] = t < ng ? l_slot[t] : -1;
+      sel_host[out0 + t] = t < nh ? l_host[t] : -1;
+    }
+    if (threadIdx.x == 0) {
+      n_gpu[pair] = ng;
+      n_host[pair] = nh;
+    }
+  };
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD, REMAP>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, ng, ctx, P,
+                                                                       E, smem, -1, -1, l_n, write_lists);
   asm volatile("" ::"v"(touched_k), "v"(touched_v));  // the touches stay loads, their registers reserved until they have returned
 }
 
@@ -1028,6 +1028,8 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
   };
   u32x4 raw[kScoreBatch];
   load_batch(raw, wave);
+  Selector<WAVES, KPL> S{l_x, 0, wave};
+  S.prepare();
 
   if (threadIdx.x < 2 * DH) {
     double f = 0.0;
@@ -1074,7 +1076,6 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     key[r] = l_key[i];  // 0 beyond nb
     slot[r] = i < nb ? slot[r] : -1;
   }
-  Selector<WAVES, KPL> S{l_x, 0, wave};
   uint32_t sel = 0;
   if (k_eff > 0) sel = S.best(key, k_eff, false);
   uint32_t gpu = 0;
@@ -1390,7 +1391,7 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
   if (pairs == 0) return SCOUT_OK;
   dim3 grid(P.nsplit, D.Hkv, D.B);
   const bool remap = xcd_grid(D, P.nsplit, grid);
-  const size_t lds = mfma_smem_bytes(D, 8) + (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4) * sizeof(int);
+  const size_t lds = mfma_smem_bytes(D, 8) + (4 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4) * sizeof(int);
 #define SCOUT_SA_RUN(DT, DH, KPL, REMAP, FOLD)                                                                           \
   hipLaunchKernelGGL((select_attend_kernel<DT, DH, KPL, REMAP, FOLD>), grid, dim3(8 * kWave), lds, st, D, q, scores, table, \
                      k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)

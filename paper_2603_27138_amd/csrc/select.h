@@ -29,23 +29,27 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 template <int WAVES>
 __device__ __forceinline__ void wg_exchange(int v, int* lds, int& phase, int wave, int& total,
                                             int& before) {
-  if (WAVES == 1) {
+  if constexpr (WAVES == 1) {
     total = v;
     before = 0;
-    return;
-  }
-  int* buf = lds + (phase & 1) * WAVES;
-  if (lane_id() == 0) buf[wave] = v;
-  __syncthreads();
-  total = 0;
-  before = 0;
+  } else {
+    int* buf = lds + (phase & 1) * WAVES;
+    if (lane_id() == 0) buf[wave] = v;
+    __syncthreads();
+    static_assert(WAVES % 4 == 0, "read four words at a time");
+    int4 x[WAVES / 4];
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) {
-    const int x = buf[w];
-    total += x;
-    before += (w < wave) ? x : 0;
+    for (int w = 0; w < WAVES / 4; ++w) x[w] = reinterpret_cast<const int4*>(buf)[w];
+    total = 0;
+    before = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      const int y = w % 4 == 0 ? x[w / 4].x : w % 4 == 1 ? x[w / 4].y : w % 4 == 2 ? x[w / 4].z : x[w / 4].w;
+      total += y;
+      before += (w < wave) ? y : 0;
+    }
+    ++phase;
   }
-  ++phase;
 }
 
 // Inclusive prefix sum over the 64 lanes on the vector ALU (DPP row shifts, then the two
@@ -74,21 +78,37 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
   return r[0] | r[1];
 }
 
+constexpr int kSelections = 3;  // calls of Selector::best() in one kernel: top-k, best of the missing, worst of the spare
+
 template <int WAVES, int KPL>
 struct Selector {
   int* lds;
   int phase;
   int wave;
   // Histogram rounds done so far by this Selector, over all its best() calls (several waves only).
-  // Round r counts into bin array r % 3 and, after its barrier, clears array (r + 2) % 3 for round
+  // prepare() clears arrays 0 and 1.  Round r counts into bin array r % 3 and, after its barrier, clears array (r + 2) % 3 for round
   // r + 2.  The numbering runs on from one call to the next, which is what makes back-to-back calls
   // safe without a barrier between them: a call that ends with round r (its reads of array r % 3 are
-  // followed by no barrier) leaves array (r + 1) % 3 clean (cleared in round r - 1, or by the first
-  // call's opening clear) and array (r + 2) % 3 being cleared; the next call starts with round r + 1,
+  // followed by no barrier) leaves array (r + 1) % 3 clean (cleared in round r - 1, or by
+  // prepare()) and array (r + 2) % 3 being cleared; the next call starts with round r + 1,
   // touches array r % 3 only after the barrier of that round (its clear for round r + 3), and a wave
   // still reading array r % 3 for the previous call has not yet arrived at the barriers (the common
   // prefix exchange, then round r + 1) that every wave must pass before that clear.  Wave-uniform.
   int hround = 0;
+  int calls = 0;  // of best() so far, at most kSelections
+
+  // LDS: 2 * WAVES words for wg_exchange, an OR and an AND word per call of best(), three bin arrays
+  static constexpr int kWords = 2 * WAVES, kBins = (kWords + 2 * kSelections + 3) & ~3;
+
+  // Clears what best() counts in, for all threads of the workgroup; before the keys have arrived, so that its barrier
+  // costs nothing.
+  __device__ __forceinline__ void prepare() {
+    if (WAVES == 1) return;
+    const int tid = wave * kWave + lane_id();
+    for (int i = tid; i < 2 * 256; i += WAVES * kWave) lds[kBins + i] = 0;
+    if (tid < 2 * kSelections) lds[kWords + tid] = tid & 1 ? -1 : 0;
+    __syncthreads();
+  }
 
   // number of keys >= cand over the whole workgroup
   __device__ __forceinline__ int count_ge(const uint32_t (&key)[KPL], uint32_t cand) {
@@ -155,21 +175,15 @@ struct Selector {
     vo = wave_or(vo);
     va = ~wave_or(~va);
     if (WAVES > 1) {
-      int* buf = lds + (phase & 1) * WAVES;  // same alternation as wg_exchange
-      int* buf2 = lds + 2 * WAVES + (phase & 1) * WAVES;
+      int* word = lds + kWords + 2 * calls;
       if (lane_id() == 0) {
-        buf[wave] = (int)vo;
-        buf2[wave] = (int)va;
+        atomicOr(word, (int)vo);
+        atomicAnd(word + 1, (int)va);
       }
       __syncthreads();
-      vo = 0;
-      va = 0xffffffffu;
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) {
-        vo |= (uint32_t)buf[w];
-        va &= (uint32_t)buf2[w];
-      }
-      ++phase;
+      const int2 both = *reinterpret_cast<const int2*>(word);
+      vo = (uint32_t)both.x;
+      va = (uint32_t)both.y;
     }
     all_or = vo;
     all_and = va;
@@ -186,17 +200,9 @@ struct Selector {
       vo |= key[r];
       va &= key[r] ? key[r] : 0xffffffffu;
     }
-    if constexpr (WAVES > 1) {
-      // Before the first histogram round of this Selector, bin arrays 0 and 1 are cleared here, so that
-      // the barrier inside or_and also publishes the zeros.  Later calls find their arrays clean (see
-      // hround) and must not clear here: a slower wave may still be reading the last round's array.
-      if (hround == 0) {
-        int* hist = lds + 4 * WAVES;
-        for (int i = wave * kWave + lane_id(); i < 2 * 256; i += WAVES * kWave) hist[i] = 0;
-      }
-    }
     uint32_t all_or, all_and;
     or_and(vo, va, all_or, all_and);
+    ++calls;
     const uint32_t diff = all_or ^ all_and;
     // the largest T with  count(key >= T) >= kk  is the kk-th largest key
     uint32_t T = diff ? (all_and & ~(0xffffffffu >> __builtin_clz(diff))) : all_and;
@@ -218,7 +224,7 @@ struct Selector {
       // 256 bins (four per lane), forms the suffix sums with a vector-ALU scan and picks the largest
       // digit whose suffix count, added to the keys already known to be above, still reaches kk.
       // Three bin arrays rotate: the one for the round after next is cleared while this round's is read.
-      int* hist = lds + 4 * WAVES;
+      int* hist = lds + kBins;
       const int tid = wave * kWave + lane_id();
       int n_above = 0;  // keys whose settled bits are larger than T's
       int bit = diff ? 31 - __builtin_clz(diff) : -1;
@@ -289,15 +295,14 @@ struct Selector {
   }
 };
 
-// Keys and table entries of a pair.  Every load is issued unconditionally (the index is clamped
-// into the row, the value masked afterwards) so that all of them are in flight together.
+// Scores and table entries of a pair.  Every load is issued unconditionally (the index is clamped
+// into the row, the value masked by mask_keys) so that all of them are in flight together.
 template <int WAVES, int KPL>
-__device__ __forceinline__ void load_keys(const Dims& D, const float* __restrict__ scores,
-                                          const int32_t* __restrict__ table, int pair, int nb, int wave,
-                                          int lane, uint32_t (&key)[KPL], int (&slot)[KPL]) {
+__device__ __forceinline__ void load_scores(const Dims& D, const float* __restrict__ scores,
+                                            const int32_t* __restrict__ table, int pair, int wave,
+                                            int lane, float (&sc)[KPL], int (&slot)[KPL]) {
   const size_t row = (size_t)pair * D.max_blocks;
   const size_t trow = (size_t)kv_row(D, pair) * D.max_blocks;  // the table belongs to the KV head
-  float sc[KPL];
 #pragma unroll
   for (int r = 0; r < KPL; ++r) {
     const int i = (wave * KPL + r) * kWave + lane;
@@ -305,6 +310,11 @@ __device__ __forceinline__ void load_keys(const Dims& D, const float* __restrict
     sc[r] = scores[row + ic];
     slot[r] = table[trow + ic];
   }
+}
+
+// The keys of the valid blocks; 0 and slot -1 beyond.
+template <int WAVES, int KPL>
+__device__ __forceinline__ void mask_keys(int nb, int wave, int lane, const float (&sc)[KPL], uint32_t (&key)[KPL], int (&slot)[KPL]) {
 #pragma unroll
   for (int r = 0; r < KPL; ++r) {
     const int i = (wave * KPL + r) * kWave + lane;
@@ -315,6 +325,6 @@ __device__ __forceinline__ void load_keys(const Dims& D, const float* __restrict
 
 // LDS words a Selector needs for WAVES waves
 template <int WAVES>
-constexpr int selector_lds_ints() { return 4 * WAVES + 3 * 256; }
+constexpr int selector_lds_ints() { return Selector<WAVES, 1>::kBins + 3 * 256; }
 
 }  // namespace scout

@@ -23,14 +23,17 @@ __global__ __launch_bounds__(WAVES* kWave) void topk_kernel(
 
   uint32_t key[KPL];
   int slot[KPL];
-  load_keys<WAVES, KPL>(D, scores, table, pair, nb, wave, lane, key, slot);
+  float sc[KPL];
+  load_scores<WAVES, KPL>(D, scores, table, pair, wave, lane, sc, slot);
+  Selector<WAVES, KPL> S{lds, 0, wave};
+  S.prepare();
+  mask_keys<WAVES, KPL>(nb, wave, lane, sc, key, slot);
   if constexpr (AHEAD) {  // the pair's query rows: contiguous, a multiple of 16 bytes
     const size_t row = (size_t)D.G * J.q_row, at = pair * row;
     for (int t = threadIdx.x * 16; t < (int)row; t += WAVES * kWave * 16)
       *reinterpret_cast<uint4*>(static_cast<char*>(J.q_out) + at + t) =
           *reinterpret_cast<const uint4*>(static_cast<const char*>(J.q) + at + t);
   }
-  Selector<WAVES, KPL> S{lds, 0, wave};
 
   uint32_t sel = 0;
   if (k_eff > 0) sel = S.best(key, k_eff, false);
@@ -88,8 +91,11 @@ __global__ __launch_bounds__(WAVES* kWave) void recall_kernel(
 
   uint32_t key[KPL];
   int slot[KPL];
-  load_keys<WAVES, KPL>(D, scores, table, pair, nb, wave, lane, key, slot);
+  float sc[KPL];
+  load_scores<WAVES, KPL>(D, scores, table, pair, wave, lane, sc, slot);
   Selector<WAVES, KPL> S{lds, 0, wave};
+  S.prepare();
+  mask_keys<WAVES, KPL>(nb, wave, lane, sc, key, slot);
 
   uint32_t top = 0;
   if (k_eff > 0) top = S.best(key, k_eff, false);

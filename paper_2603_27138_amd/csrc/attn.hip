@@ -865,6 +865,51 @@ __device__ __forceinline__ void touch_hint(const Dims& D, const Hint& h, const P
   tv = __builtin_amdgcn_raw_buffer_load_b32(vr, lane * kStep, 0, 0);
 }
 
+// A pair's lists between the selection and the stores: in LDS.  The resident part is what the attention reads; everything
+// leaves behind the tiles (after_gather).  Stored in front of the first request the lists held up the workgroup that writes
+// them, and with it its pair, by a microsecond.
+struct Lists {
+  int *sel, *slot, *all, *host;  // D.k words each
+  int ng, nh;
+
+  __device__ __forceinline__ Lists(int* lds, int kpad) : sel(lds), slot(lds + kpad), all(lds + 2 * kpad), host(lds + 3 * kpad), ng(0), nh(0) {}
+
+  // of the key array's element r of each lane, as the Selector has them
+  template <int WAVES, int KPL>
+  __device__ __forceinline__ void fill(Selector<WAVES, KPL>& S, const uint32_t (&key)[KPL], const int (&slots)[KPL], int k_eff) {
+    Mask<KPL> chosen{}, gpu;
+    if (k_eff > 0) chosen = S.best(key, k_eff, false);
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) gpu.m[r] = chosen.m[r] & __ballot(slots[r] >= 0);
+    ng = S.emit(chosen, gpu, [&](int r, int i, int at, int at_gpu, bool resident) __attribute__((always_inline)) {
+      if (resident) {
+        sel[at_gpu] = i;
+        slot[at_gpu] = slots[r];
+      } else {
+        host[at - at_gpu] = i;
+      }
+      all[at] = i;
+    });
+    nh = k_eff - ng;
+  }
+
+  __device__ __forceinline__ void store(const Dims& D, int pair, int k_eff, int n_threads, int32_t* sel_all, int32_t* sel_gpu,
+                                        int32_t* slot_gpu, int32_t* n_gpu, int32_t* sel_host, int32_t* n_host) const {
+    const size_t out0 = (size_t)pair * D.k;
+    for (int t = threadIdx.x; t < D.k; t += n_threads) {
+      sel_all[out0 + t] = t < k_eff ? all[t] : -1;
+      sel_gpu[out0 + t] = t < ng ? sel[t] : -1;
+      slot_gpu[out0 + t] = t < ng ? slot[t] : -1;
+      sel_host[out0 + t] = t < nh ? host[t] : -1;
+    }
+    if (threadIdx.x == 0) {
+      n_gpu[pair] = ng;
+      n_host[pair] = nh;
+    }
+  }
+};
+__host__ __device__ constexpr int lists_lds_ints(int kpad) { return 4 * kpad; }
+
 // Selection and attention of a pair in one launch (the non-pipelined description of Sec. 3.2:
 // identify the top-k blocks, then attend to the resident ones).  Every workgroup of the pair
 // repeats the cheap selection from the scores (integer work on a few KiB of keys), keeps the
@@ -884,13 +929,11 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   which_pair<REMAP>(D, b, g, pair, split);
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  // LDS after the fold area: resident list (block, slot), the selector's exchange words, the count
+  // LDS after the fold area: the lists, the selector's exchange words, the word that fold_splits uses
   const int kpad = (D.k + 3) & ~3;  // keeps what follows 16-byte aligned
-  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
-  int* l_slot = l_sel + kpad;
-  int* l_all = l_slot + kpad;   // the workgroup that writes the lists out: all of the selection, and the offloaded part
-  int* l_host = l_all + kpad;
-  int* l_x = l_host + kpad;
+  int* l_lists = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
+  Lists lists(l_lists, kpad);
+  int* l_x = l_lists + lists_lds_ints(kpad);
   int* l_n = l_x + selector_lds_ints<WAVES>();
 
   QRegs<DT, DH> qreg;
@@ -899,9 +942,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
 
   const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
   uint32_t touched_k = 0, touched_v = 0;
-  const size_t out0 = (size_t)pair * D.k;
-  const bool writer = split == 0;
-  int ng, nh, k_eff;
+  int k_eff;
 
   {
     const int sw = wave;
@@ -918,46 +959,13 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     __builtin_amdgcn_sched_barrier(0);
     touch_hint<DT, DH, WAVES, REMAP>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
     __builtin_amdgcn_sched_barrier(0);
-    uint32_t sel = 0;
-    if (k_eff > 0) sel = S.best(key, k_eff, false);
-    uint32_t gpu = 0;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r)
-      if (((sel >> r) & 1u) && slot[r] >= 0) gpu |= 1u << r;
-    int pos_all[KPL], pos_gpu[KPL];
-    ng = S.positions2(sel, pos_all, gpu, pos_gpu);
-    nh = k_eff - ng;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-      if ((sel >> r) & 1u) {
-        const int i = (sw * KPL + r) * kWave + lane;
-        if ((gpu >> r) & 1u) {
-          l_sel[pos_gpu[r]] = i;
-          l_slot[pos_gpu[r]] = slot[r];
-        } else {
-          l_host[pos_all[r] - pos_gpu[r]] = i;
-        }
-        l_all[pos_all[r]] = i;
-      }
-    }
+    lists.fill(S, key, slot, k_eff);
   }
   __syncthreads();
-  // The lists go out behind the tiles: stored here, in front of the first request, they held up the workgroup that writes
-  // them, and with it its pair, by a microsecond.
   auto write_lists = [&]() __attribute__((always_inline)) {
-    if (!writer) return;
-    for (int t = threadIdx.x; t < D.k; t += WAVES * kWave) {
-      sel_all[out0 + t] = t < k_eff ? l_all[t] : -1;
-      sel_gpu[out0 + t] = t < ng ? l_sel[t] : -1;
-      slot_gpu[out0 + t] = t < ng ? l_slot[t] : -1;
-      sel_host[out0 + t] = t < nh ? l_host[t] : -1;
-    }
-    if (threadIdx.x == 0) {
-      n_gpu[pair] = ng;
-      n_host[pair] = nh;
-    }
+    if (split == 0) lists.store(D, pair, k_eff, WAVES * kWave, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host);
   };
-  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD, REMAP>(D, b, g, split, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, ng, ctx, P,
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD, REMAP>(D, b, g, split, qreg, k_pool, v_pool, n_slots, lists.sel, lists.slot, lists.ng, ctx, P,
                                                                        E, smem, -1, -1, l_n, write_lists);
   asm volatile("" ::"v"(touched_k), "v"(touched_v));  // the touches stay loads, their registers reserved until they have returned
 }
@@ -988,11 +996,10 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int kpad = (D.k + 3) & ~3;
-  int* l_sel = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
-  int* l_slot = l_sel + kpad;
-  int* l_x = l_slot + kpad;
-  int* l_n = l_x + selector_lds_ints<WAVES>();
-  uint32_t* l_key = reinterpret_cast<uint32_t*>(l_n + 4);                       // [WAVES * 64 * KPL]
+  int* l_lists = reinterpret_cast<int*>(smem + WAVES * (D.G * (DH + 4) + 32));
+  Lists lists(l_lists, kpad);
+  int* l_x = l_lists + lists_lds_ints(kpad);
+  uint32_t* l_key = reinterpret_cast<uint32_t*>(l_x + selector_lds_ints<WAVES>());  // [WAVES * 64 * KPL]
   double* coef_lds = reinterpret_cast<double*>(l_key + WAVES * kWave * KPL);    // [2][DH]: N_c, P_c
 
   // table entries of the elements this thread will hold in the selection: requested first, used last
@@ -1076,46 +1083,13 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
     key[r] = l_key[i];  // 0 beyond nb
     slot[r] = i < nb ? slot[r] : -1;
   }
-  uint32_t sel = 0;
-  if (k_eff > 0) sel = S.best(key, k_eff, false);
-  uint32_t gpu = 0;
-#pragma unroll
-  for (int r = 0; r < KPL; ++r)
-    if (((sel >> r) & 1u) && slot[r] >= 0) gpu |= 1u << r;
-  int pos_all[KPL], pos_gpu[KPL];
-  const int ng = S.positions2(sel, pos_all, gpu, pos_gpu);
-  const int nh = k_eff - ng;
-  const size_t out0 = (size_t)pair * D.k;
-#pragma unroll
-  for (int r = 0; r < KPL; ++r) {
-    if ((sel >> r) & 1u) {
-      const int i = (wave * KPL + r) * kWave + lane;
-      sel_all[out0 + pos_all[r]] = i;
-      if ((gpu >> r) & 1u) {
-        l_sel[pos_gpu[r]] = i;
-        l_slot[pos_gpu[r]] = slot[r];
-        sel_gpu[out0 + pos_gpu[r]] = i;
-        slot_gpu[out0 + pos_gpu[r]] = slot[r];
-      } else {
-        sel_host[out0 + pos_all[r] - pos_gpu[r]] = i;
-      }
-    }
-  }
-  for (int t = threadIdx.x; t < D.k; t += WAVES * kWave) {
-    if (t >= k_eff) sel_all[out0 + t] = -1;
-    if (t >= ng) {
-      sel_gpu[out0 + t] = -1;
-      slot_gpu[out0 + t] = -1;
-    }
-    if (t >= nh) sel_host[out0 + t] = -1;
-  }
-  if (threadIdx.x == 0) {
-    n_gpu[pair] = ng;
-    n_host[pair] = nh;
-    l_n[0] = ng;
-  }
+  lists.fill(S, key, slot, k_eff);
   __syncthreads();
-  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>()>(D, b, g, 0, qreg, k_pool, v_pool, n_slots, l_sel, l_slot, l_n[0], ctx, P, E, smem);
+  auto write_lists = [&]() __attribute__((always_inline)) {
+    lists.store(D, pair, k_eff, WAVES * kWave, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host);
+  };
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>()>(D, b, g, 0, qreg, k_pool, v_pool, n_slots, lists.sel, lists.slot, lists.ng, ctx, P, E,
+                                                   smem, -1, -1, nullptr, write_lists);
 }
 
 // ---------------------------------------------------------------- VALU family
@@ -1391,7 +1365,7 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
   if (pairs == 0) return SCOUT_OK;
   dim3 grid(P.nsplit, D.Hkv, D.B);
   const bool remap = xcd_grid(D, P.nsplit, grid);
-  const size_t lds = mfma_smem_bytes(D, 8) + (4 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4) * sizeof(int);
+  const size_t lds = mfma_smem_bytes(D, 8) + (lists_lds_ints((D.k + 3) & ~3) + selector_lds_ints<8>() + (size_t)4) * sizeof(int);
 #define SCOUT_SA_RUN(DT, DH, KPL, REMAP, FOLD)                                                                           \
   hipLaunchKernelGGL((select_attend_kernel<DT, DH, KPL, REMAP, FOLD>), grid, dim3(8 * kWave), lds, st, D, q, scores, table, \
                      k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)
@@ -1470,7 +1444,7 @@ int launch_step(const Dims& D, int dtype, const void* q, const void* digest, con
   const int kpl = per_lane <= 2 ? 2 : 4;  // longer rows: see step_kernel_supported
   if (per_lane > 4) return SCOUT_EUNSUPPORTED;
   const size_t lds = mfma_smem_bytes(D, 8) +
-                     (2 * (size_t)((D.k + 3) & ~3) + selector_lds_ints<8>() + 4 + 8 * kWave * kpl) * sizeof(int) +
+                     (lists_lds_ints((D.k + 3) & ~3) + selector_lds_ints<8>() + 8 * kWave * (size_t)kpl) * sizeof(int) +
                      2 * D.d * sizeof(double);
   const char* dg = static_cast<const char*>(digest);
 #define SCOUT_STEP(DT, DH, KPL)                                                                              \

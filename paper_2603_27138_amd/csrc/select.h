@@ -78,6 +78,13 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
   return r[0] | r[1];
 }
 
+// A bit per lane for each of the KPL elements of a lane, wave-uniform.
+template <int KPL>
+struct Mask {
+  uint64_t m[KPL];
+};
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
 constexpr int kSelections = 3;  // calls of Selector::best() in one kernel: top-k, best of the missing, worst of the spare
 
 template <int WAVES, int KPL>
@@ -120,54 +127,40 @@ struct Selector {
     return total;
   }
 
-  // total number of set bits of a per-lane register mask, and (per element) the
-  // number of set elements that precede it in index order
-  __device__ __forceinline__ int positions(uint32_t bits, int (&pos)[KPL]) {
-    int c = 0;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) c += __popcll(__ballot((bits >> r) & 1u));
-    int total, off;
-    wg_exchange<WAVES>(c, lds, phase, wave, total, off);
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-      const uint64_t m = __ballot((bits >> r) & 1u);
-      pos[r] = off + mbcnt64(m);
-      off += __popcll(m);
-    }
-    return total;
-  }
-
-  // positions() of two masks with one exchange: the two per-wave counts travel in the halves of one
-  // word (a workgroup holds at most 16384 elements, so neither half can carry into the other).
-  // Returns the total of the second mask.
-  __device__ __forceinline__ int positions2(uint32_t bits_a, int (&pos_a)[KPL], uint32_t bits_b, int (&pos_b)[KPL]) {
+  // Elements marked by a wave-wide mask per register (scalar registers: what is done with them costs the vector ALU nothing).
+  // offsets(): how many marked elements of a and of b lie in earlier waves, and the totals of the workgroup, with one
+  // exchange: the two per-wave counts travel in the halves of one word (a workgroup holds at most 16384 elements, so neither
+  // half can carry into the other).
+  __device__ __forceinline__ void offsets(const Mask<KPL>& a, const Mask<KPL>& b, int& off_a, int& off_b, int& total_a, int& total_b) {
     int ca = 0, cb = 0;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-      ca += __popcll(__ballot((bits_a >> r) & 1u));
-      cb += __popcll(__ballot((bits_b >> r) & 1u));
+      ca += __popcll(a.m[r]);
+      cb += __popcll(b.m[r]);
     }
     int total, off;
     wg_exchange<WAVES>(ca | (cb << 16), lds, phase, wave, total, off);
-    int off_a = off & 0xffff, off_b = off >> 16;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-      const uint64_t ma = __ballot((bits_a >> r) & 1u), mb = __ballot((bits_b >> r) & 1u);
-      pos_a[r] = off_a + mbcnt64(ma);
-      pos_b[r] = off_b + mbcnt64(mb);
-      off_a += __popcll(ma);
-      off_b += __popcll(mb);
-    }
-    return total >> 16;
+    total = __builtin_amdgcn_readfirstlane(total);
+    off = __builtin_amdgcn_readfirstlane(off);
+    off_a = off & 0xffff;
+    off_b = off >> 16;
+    total_a = total & 0xffff;
+    total_b = total >> 16;
   }
 
-  __device__ __forceinline__ int count(uint32_t bits) {
-    int c = 0;
+  // f(r, i, pos_a, pos_b, in_b) for every element r of this lane that is marked in a: its index, how many marked elements
+  // of a, and of b, precede it, and whether it is marked in b itself.  Returns the total of b.
+  template <class F>
+  __device__ __forceinline__ int emit(const Mask<KPL>& a, const Mask<KPL>& b, F f) {
+    int off_a, off_b, total_a, total_b;
+    offsets(a, b, off_a, off_b, total_a, total_b);
 #pragma unroll
-    for (int r = 0; r < KPL; ++r) c += __popcll(__ballot((bits >> r) & 1u));
-    int total, before;
-    wg_exchange<WAVES>(c, lds, phase, wave, total, before);
-    return total;
+    for (int r = 0; r < KPL; ++r) {
+      if (in_mask(a.m[r])) f(r, (wave * KPL + r) * kWave + lane_id(), off_a + mbcnt64(a.m[r]), off_b + mbcnt64(b.m[r]), in_mask(b.m[r]));
+      off_a += __popcll(a.m[r]);
+      off_b += __popcll(b.m[r]);
+    }
+    return total_b;
   }
 
   // OR and AND of a per-lane word over the whole workgroup
@@ -189,10 +182,10 @@ struct Selector {
     all_and = va;
   }
 
-  // Bits of the kk best candidates (key > 0) under (key descending, then index
+  // The kk best candidates (key > 0) under (key descending, then index
   // ascending, or descending when high_index_first).  Needs 1 <= kk <= number
   // of candidates.
-  __device__ __forceinline__ uint32_t best(const uint32_t (&key)[KPL], int kk, bool high_index_first) {
+  __device__ __forceinline__ Mask<KPL> best(const uint32_t (&key)[KPL], int kk, bool high_index_first) {
     // Bits on which all candidates agree need no search: start below the common prefix.
     uint32_t vo = 0, va = 0xffffffffu;
 #pragma unroll
@@ -270,26 +263,27 @@ struct Selector {
         bit -= nbits;
       }
     }
-    uint32_t ge = 0;
+    Mask<KPL> out;
+    if (n_ge == kk) {  // wave-uniform
 #pragma unroll
-    for (int r = 0; r < KPL; ++r) ge |= (key[r] >= T ? 1u : 0u) << r;
-    if (n_ge == kk) return ge;  // wave-uniform
-    // ties at the threshold: take them in index order until kk are chosen
-    uint32_t gt = 0, eq = 0;
-#pragma unroll
-    for (int r = 0; r < KPL; ++r) {
-      gt |= (key[r] > T ? 1u : 0u) << r;
-      eq |= (key[r] == T ? 1u : 0u) << r;
+      for (int r = 0; r < KPL; ++r) out.m[r] = __ballot(key[r] >= T);
+      return out;
     }
-    int rank[KPL];
-    const int n_eq = positions(eq, rank);
-    const int n_gt = count(gt);
-    const int need = kk - n_gt;
-    uint32_t out = gt;
+    // ties at the threshold: take them in index order until kk are chosen
+    Mask<KPL> eq;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-      const int rk = high_index_first ? (n_eq - 1 - rank[r]) : rank[r];
-      if (((eq >> r) & 1u) && rk < need) out |= 1u << r;
+      out.m[r] = __ballot(key[r] > T);
+      eq.m[r] = __ballot(key[r] == T);
+    }
+    int off, off_gt, n_eq, n_gt;
+    offsets(eq, out, off, off_gt, n_eq, n_gt);
+    const int need = kk - n_gt;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+      const int rank = off + mbcnt64(eq.m[r]);
+      out.m[r] |= __ballot(in_mask(eq.m[r]) && (high_index_first ? n_eq - 1 - rank : rank) < need);
+      off += __popcll(eq.m[r]);
     }
     return out;
   }

@@ -35,31 +35,22 @@ __global__ __launch_bounds__(WAVES* kWave) void topk_kernel(
           *reinterpret_cast<const uint4*>(static_cast<const char*>(J.q) + at + t);
   }
 
-  uint32_t sel = 0;
+  Mask<KPL> sel{}, gpu;
   if (k_eff > 0) sel = S.best(key, k_eff, false);
-
-  uint32_t gpu = 0;
 #pragma unroll
-  for (int r = 0; r < KPL; ++r)
-    if (((sel >> r) & 1u) && slot[r] >= 0) gpu |= 1u << r;
-  int pos_all[KPL], pos_gpu[KPL];
-  const int ng = S.positions2(sel, pos_all, gpu, pos_gpu);
-  const int nh = k_eff - ng;
+  for (int r = 0; r < KPL; ++r) gpu.m[r] = sel.m[r] & __ballot(slot[r] >= 0);
   const size_t out0 = (size_t)pair * D.k;
-#pragma unroll
-  for (int r = 0; r < KPL; ++r) {
-    if ((sel >> r) & 1u) {
-      const int i = (wave * KPL + r) * kWave + lane;
-      sel_all[out0 + pos_all[r]] = i;
-      if ((gpu >> r) & 1u) {
-        sel_gpu[out0 + pos_gpu[r]] = i;
-        slot_gpu[out0 + pos_gpu[r]] = slot[r];
-      } else {
-        sel_host[out0 + pos_all[r] - pos_gpu[r]] = i;
-        if constexpr (AHEAD) l_host[pos_all[r] - pos_gpu[r]] = i;
-      }
+  const int ng = S.emit(sel, gpu, [&](int r, int i, int at, int at_gpu, bool resident) __attribute__((always_inline)) {
+    sel_all[out0 + at] = i;
+    if (resident) {
+      sel_gpu[out0 + at_gpu] = i;
+      slot_gpu[out0 + at_gpu] = slot[r];
+    } else {
+      sel_host[out0 + at - at_gpu] = i;
+      if constexpr (AHEAD) l_host[at - at_gpu] = i;
     }
-  }
+  });
+  const int nh = k_eff - ng;
   if constexpr (AHEAD) __syncthreads();
   for (int t = threadIdx.x; t < D.k; t += WAVES * kWave) {
     if (t >= k_eff) sel_all[out0 + t] = -1;
@@ -97,55 +88,56 @@ __global__ __launch_bounds__(WAVES* kWave) void recall_kernel(
   S.prepare();
   mask_keys<WAVES, KPL>(nb, wave, lane, sc, key, slot);
 
-  uint32_t top = 0;
+  Mask<KPL> top{}, missing, spare;
   if (k_eff > 0) top = S.best(key, k_eff, false);
-
-  uint32_t res = 0;
 #pragma unroll
-  for (int r = 0; r < KPL; ++r)
-    if (slot[r] >= 0) res |= 1u << r;
-  const uint32_t missing = top & ~res;  // important now, but in host memory
-  const uint32_t spare = res & ~top;    // resident, not in the current top-k
-  const int n_missing = S.count(missing);
-  const int n_spare = S.count(spare);
+  for (int r = 0; r < KPL; ++r) {
+    const uint64_t res = __ballot(slot[r] >= 0);
+    missing.m[r] = top.m[r] & ~res;  // important now, but in host memory
+    spare.m[r] = res & ~top.m[r];    // resident, not in the current top-k
+  }
+  int off_m, off_s, n_missing, n_spare;
+  S.offsets(missing, spare, off_m, off_s, n_missing, n_spare);
   const int n = n_missing < n_spare ? n_missing : n_spare;
 
-  uint32_t rec = 0, evi = 0;
+  Mask<KPL> rec{}, evi{};
   if (n > 0) {
     uint32_t kk[KPL];
     if (n == n_missing) {
       rec = missing;
     } else {  // the cache has room for only n of them: best-ranked first
 #pragma unroll
-      for (int r = 0; r < KPL; ++r) kk[r] = ((missing >> r) & 1u) ? key[r] : 0u;
+      for (int r = 0; r < KPL; ++r) kk[r] = in_mask(missing.m[r]) ? key[r] : 0u;
       rec = S.best(kk, n, false);
     }
     // worst-ranked spare blocks go: lowest score first, equal scores by higher index
 #pragma unroll
-    for (int r = 0; r < KPL; ++r) kk[r] = ((spare >> r) & 1u) ? ~key[r] : 0u;
+    for (int r = 0; r < KPL; ++r) kk[r] = in_mask(spare.m[r]) ? ~key[r] : 0u;
     evi = S.best(kk, n, true);
   }
-  int pos_r[KPL], pos_e[KPL];
-  S.positions2(rec, pos_r, evi, pos_e);
   const size_t out0 = (size_t)pair * D.k;
+  int off_r, off_e, n_rec, n_evi;
+  S.offsets(rec, evi, off_r, off_e, n_rec, n_evi);
 #pragma unroll
   for (int r = 0; r < KPL; ++r) {
-    if ((evi >> r) & 1u) {
-      const int i = (wave * KPL + r) * kWave + lane;
-      freed[pos_e[r]] = slot[r];
-      recall_slot[out0 + pos_e[r]] = slot[r];
-      evict_blk[out0 + pos_e[r]] = i;
+    if (in_mask(evi.m[r])) {
+      const int i = (wave * KPL + r) * kWave + lane, at = off_e + mbcnt64(evi.m[r]);
+      freed[at] = slot[r];
+      recall_slot[out0 + at] = slot[r];
+      evict_blk[out0 + at] = i;
       table[(size_t)pair * D.max_blocks + i] = -1;
     }
+    off_e += __popcll(evi.m[r]);
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < KPL; ++r) {
-    if ((rec >> r) & 1u) {
-      const int i = (wave * KPL + r) * kWave + lane;
-      recall_blk[out0 + pos_r[r]] = i;
-      table[(size_t)pair * D.max_blocks + i] = freed[pos_r[r]];
+    if (in_mask(rec.m[r])) {
+      const int i = (wave * KPL + r) * kWave + lane, at = off_r + mbcnt64(rec.m[r]);
+      recall_blk[out0 + at] = i;
+      table[(size_t)pair * D.max_blocks + i] = freed[at];
     }
+    off_r += __popcll(rec.m[r]);
   }
   for (int t = threadIdx.x; t < D.k; t += WAVES * kWave) {
     if (t >= n) {

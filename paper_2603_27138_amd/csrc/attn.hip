@@ -539,6 +539,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   // (at most 4096 units over at most 1024 waves: exact); an integer division here delays the first
   // tile request by a noticeable fraction of a microsecond.
   const int n_units = n << ush, n_waves = P.nsplit * WAVES, v = split * WAVES + wave;
+  // STRIDE: units v, v + n_waves, ... instead.
   int u0 = v, u1 = n_units, step = n_waves;
   if constexpr (!STRIDE) {
     const int per = P.waves_magic ? (int)__umulhi((uint32_t)n_units, P.waves_magic) : n_units;
@@ -916,7 +917,8 @@ __host__ __device__ constexpr int lists_lds_ints(int kpad) { return 4 * kpad; }
 // resident list in LDS and goes straight on to its share of the units; split 0 also writes the
 // lists out, because the host needs to know which selected blocks are its own.
 // FOLD: several splits per pair, folded in this launch (P.arrived).
-template <int DT, int DH, int KPL, bool REMAP, bool FOLD>
+// STRIDE: how the units are dealt to the waves (attend_pair).
+template <int DT, int DH, int KPL, bool REMAP, bool FOLD, bool STRIDE>
 __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     Dims D, const void* __restrict__ q, const float* __restrict__ scores,
     const int32_t* __restrict__ table, const void* __restrict__ k_pool,
@@ -957,7 +959,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     uint32_t key[KPL];
     mask_keys<WAVES, KPL>(nb, sw, lane, sc, key, slot);
     __builtin_amdgcn_sched_barrier(0);
-    touch_hint<DT, DH, WAVES, REMAP>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
+    touch_hint<DT, DH, WAVES, STRIDE>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
     __builtin_amdgcn_sched_barrier(0);
     lists.fill(S, key, slot, k_eff);
   }
@@ -965,7 +967,7 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   auto write_lists = [&]() __attribute__((always_inline)) {
     if (split == 0) lists.store(D, pair, k_eff, WAVES * kWave, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host);
   };
-  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD, REMAP>(D, b, g, split, qreg, k_pool, v_pool, n_slots, lists.sel, lists.slot, lists.ng, ctx, P,
+  attend_pair<DT, DH, WAVES, unit_depth<DT, DH>(), false, FOLD, STRIDE>(D, b, g, split, qreg, k_pool, v_pool, n_slots, lists.sel, lists.slot, lists.ng, ctx, P,
                                                                        E, smem, -1, -1, l_n, write_lists);
   asm volatile("" ::"v"(touched_k), "v"(touched_v));  // the touches stay loads, their registers reserved until they have returned
 }
@@ -1365,15 +1367,22 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
   if (pairs == 0) return SCOUT_OK;
   dim3 grid(P.nsplit, D.Hkv, D.B);
   const bool remap = xcd_grid(D, P.nsplit, grid);
+  // In stride where heads that share blocks run side by side, so that they ask for a shared block at about the same time
+  // (512 heads: 137 instead of 172 MB from HBM, 125 distinct), and from 8 splits on, where a wave has a unit or two: which units
+  // a workgroup touches and takes then hardly depends on the list's length, so the hint lands in the right L2 (4 sequences of
+  // 131k tokens, 8 splits: 113.5 -> 111.5 us a step of four layers; one sequence, 16 splits: 66.5 -> 66.0).  With fewer splits neighbouring units
+  // stay with one wave: 4 splits 105.0, in stride 105.4; 2 splits 136.3 to 137.2 and 136.6 to 137.9 (box to box).
+  const bool stride = P.nsplit >= 8;
   const size_t lds = mfma_smem_bytes(D, 8) + (lists_lds_ints((D.k + 3) & ~3) + selector_lds_ints<8>() + (size_t)4) * sizeof(int);
-#define SCOUT_SA_RUN(DT, DH, KPL, REMAP, FOLD)                                                                           \
-  hipLaunchKernelGGL((select_attend_kernel<DT, DH, KPL, REMAP, FOLD>), grid, dim3(8 * kWave), lds, st, D, q, scores, table, \
-                     k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)
-#define SCOUT_SA(DT, DH, KPL)                                                      \
-  do {                                                                             \
-    if (remap) SCOUT_SA_RUN(DT, DH, KPL, true, false);                             \
-    else if (P.arrived != nullptr) SCOUT_SA_RUN(DT, DH, KPL, false, true);         \
-    else SCOUT_SA_RUN(DT, DH, KPL, false, false);                                  \
+#define SCOUT_SA_RUN(DT, DH, KPL, REMAP, FOLD, STRIDE)                                                                      \
+  hipLaunchKernelGGL((select_attend_kernel<DT, DH, KPL, REMAP, FOLD, STRIDE>), grid, dim3(8 * kWave), lds, st, D, q, scores, \
+                     table, k_pool, v_pool, n_slots, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, P, E)
+#define SCOUT_SA(DT, DH, KPL)                                                                \
+  do {                                                                                       \
+    if (remap) SCOUT_SA_RUN(DT, DH, KPL, true, false, true);                                 \
+    else if (P.arrived != nullptr && stride) SCOUT_SA_RUN(DT, DH, KPL, false, true, true);   \
+    else if (P.arrived != nullptr) SCOUT_SA_RUN(DT, DH, KPL, false, true, false);            \
+    else SCOUT_SA_RUN(DT, DH, KPL, false, false, false);                                     \
   } while (0)
   // All eight waves share the keys: measured faster than one wave selecting alone while seven wait
   // (46.9 vs 44.1 us per step at 1024 blocks per pair), a lone wave issues too slowly.  Eight more waves that leave after the

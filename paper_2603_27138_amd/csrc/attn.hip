@@ -972,6 +972,8 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   asm volatile("" ::"v"(touched_k), "v"(touched_v));  // the touches stay loads, their registers reserved until they have returned
 }
 
+constexpr int kSmallDigestBytes = 128 << 10, kSmallTokens = 512, kSmallBytes = 288 << 10, kSmallPairs = 1024;  // see step_kernel_small
+
 // The whole layer-step of a pair in one launch (the non-pipelined sequence of Sec. 3.2: score every
 // block against its digest, keep the top-k, attend to the resident ones, merge with the host's
 // partial), one workgroup per pair, nothing to combine afterwards: where the pairs alone fill the chip, and where a
@@ -1021,22 +1023,22 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
 #pragma unroll
     for (int h = 0; h < 16; ++h) qv[h] = load1<DT>(q, q0 + (size_t)(h < D.G ? h : D.G - 1) * DH);
   }
-  const int ctx = D.ctx_len[b];
-  int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;
-  nb = nb < D.max_blocks ? nb : D.max_blocks;
-
   const char* dpair = digest + trow * T::EB;
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(dpair), 0, nb * T::EB, 0x00020000);
-  const int n_batches = (nb + T::BLOCKS - 1) / T::BLOCKS;
-  auto load_batch = [&](u32x4(&dst)[kScoreBatch], int batch) {
-    const int base = (batch < n_batches ? batch * T::BLOCKS : nb) * T::EB;  // beyond: reads zeros
+  auto load_batch = [&](u32x4(&dst)[kScoreBatch], int batch, int limit) {  // of the row's first `limit` entries; beyond: reads zeros
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(dpair), 0, limit * T::EB, 0x00020000);
+    const int base = (batch * T::BLOCKS < limit ? batch * T::BLOCKS : limit) * T::EB;
 #pragma unroll
     for (int it = 0; it < kScoreBatch; ++it)
       dst[it] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, base + T::offset(lane, it), 0, 0));
   };
+  // In short rows the first batch does not wait for the sequence's length, a trip to memory (entries beyond the last block are
+  // dropped when they are scored): a step of 16 pairs of 64 fp32 blocks with an append 17.65 -> 17.4 us a layer.  Long rows, and
+  // rows of many pairs, might be read for nothing, and gain nothing: 64.2 and 64.2 us for 256 pairs of 2048 blocks, 512 pairs
+  // of up to 250 blocks 82.9 and 83.3.
   u32x4 raw[kScoreBatch];
-  load_batch(raw, wave);
+  int limit = D.max_blocks;
+  if (D.max_blocks * T::EB > kSmallDigestBytes || D.B * D.Hkv > 256) limit = num_blocks_of(D, b);
+  load_batch(raw, wave, limit);
   Selector<WAVES, KPL> S{l_x, 0, wave};
   S.prepare();
 
@@ -1047,6 +1049,8 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
       if (h < D.G) f += (double)(fpos ? fmaxf(qv[h], 0.0f) : fminf(qv[h], 0.0f));
     coef_lds[(fpos ? DH : 0) + fc] = f;
   }
+  const int ctx = D.ctx_len[b], nb = num_blocks(D, ctx);
+  const int n_batches = (nb + T::BLOCKS - 1) / T::BLOCKS;
   // rows of the key array that no batch will write
   for (int i = n_batches * T::BLOCKS + threadIdx.x; i < WAVES * kWave * KPL; i += WAVES * kWave) l_key[i] = 0u;
   __syncthreads();
@@ -1068,7 +1072,7 @@ __global__ __launch_bounds__(8 * kWave) void step_kernel(
   };
   for (int batch = wave; batch < n_batches; batch += WAVES) {
     score_batch(raw, batch);
-    load_batch(raw, batch + WAVES);
+    load_batch(raw, batch + WAVES, nb);
   }
   if (scores != nullptr)  // the row's tail beyond the last batch
     for (int j = n_batches * T::BLOCKS + threadIdx.x; j < D.max_blocks; j += WAVES * kWave) scores[srow + j] = -INFINITY;
@@ -1433,7 +1437,6 @@ bool step_kernel_supported(const Dims& D, int dtype) {
 // rounds and the attention's part has fewer waves in flight than in a kernel of its own, so it is right only where the digests are
 // half of the tiles or more (2 * max_blocks >= k * S): fp32, d = 128, 32 blocks and 16 units, 1536 pairs 92.1 against 86.3; bf16,
 // d = 64, 128 blocks and 32 units, 4096 pairs 140.6 and 133.4; 512 blocks and 32 units 188.9 and 202.2; 256 and 16 133.9 and 138.9.
-constexpr int kSmallDigestBytes = 128 << 10, kSmallTokens = 512, kSmallBytes = 288 << 10, kSmallPairs = 1024;
 bool step_kernel_small(const Dims& D, int dtype) {
   const int row_bytes = 2 * D.d * (dtype == SCOUT_BF16 ? 2 : 4);  // of a token's K and V, and of a digest entry
   return step_kernel_takes(D) && D.max_blocks * row_bytes <= kSmallDigestBytes && D.k * D.S <= kSmallTokens &&

@@ -102,6 +102,15 @@ __device__ __forceinline__ int num_blocks(const Dims& D, int ctx) {
 }
 __device__ __forceinline__ int num_blocks_of(const Dims& D, int b) { return num_blocks(D, D.ctx_len[b]); }
 
+// A sequence's length as a load in flight: a vector load, so that where it stands among the others, and when it is waited
+// for (arrived_ctx), is the program's choice; the compiler moves a scalar load, and whoever waits for one waits for all of them.
+__device__ __forceinline__ uint32_t request_ctx(const Dims& D, int b) {
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(D.ctx_len), 0, D.B * (int)sizeof(int32_t), 0x00020000);
+  return __builtin_amdgcn_raw_buffer_load_b32(rs, b * (int)sizeof(int32_t), 0, 0);
+}
+__device__ __forceinline__ int arrived_ctx(uint32_t requested) { return __builtin_amdgcn_readfirstlane((int)requested); }
+
 // number of lanes below this one whose bit is set in a 64-bit wave mask
 __device__ __forceinline__ int mbcnt64(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),

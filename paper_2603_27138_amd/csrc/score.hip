@@ -266,9 +266,11 @@ constexpr int kScoreWaves = 4;      // waves per workgroup
 // MEAN: the digest entry is one row of binary32 sums of the block's keys (mean pooling) whatever the
 // element type of the queries; the score is (sum over heads of q) . sums / count, so there is one
 // coefficient vector instead of two and a division by the block's token count at the end.
+// AHEAD: the first `ahead` workgroups of a row (ahead_groups) ask for their digests without waiting for the sequence's length,
+// a trip to memory in which it would have nothing to do; what lies beyond the last block is dropped afterwards.
 template <int DT, int DH, bool MEAN>
 __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
-    Dims D, const void* q, const void* digest, float* scores, uint32_t* arrived) {
+    Dims D, const void* q, const void* digest, float* scores, uint32_t* arrived, int ahead) {
   using T = ScoreTile<DT, DH, MEAN>;
   constexpr int ESZ = (DT == SCOUT_BF16) ? 2 : 4;  // bytes per query element
   constexpr int EB = T::EB, BLK_PER_WAVE = T::BLOCKS;
@@ -281,11 +283,11 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   const int b = blockIdx.z, g = blockIdx.y;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int nb = num_blocks_of(D, b);
-  if (arrived != nullptr && blockIdx.x == 0 && threadIdx.x == 0) arrived[pair] = 0;  // see launch_score
+  auto clear_counter = [&]() { if (arrived != nullptr && blockIdx.x == 0 && threadIdx.x == 0) arrived[pair] = 0; };  // see launch_score
   const int j_wave = (blockIdx.x * kScoreWaves + wave) * BLK_PER_WAVE;
   const bool active = j_wave < D.max_blocks;  // a wave past the row still helps with the fold
 
+  const uint32_t ctx = request_ctx(D, b);  // ahead of the queries: who waits for it does not wait for them
   // the group's queries first: thread t takes channel t % DH, negative (t < DH) or positive parts
   const int fc = threadIdx.x % DH;
   const bool fpos = threadIdx.x >= DH;
@@ -301,11 +303,15 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   }
 
   // (the query loads above do not wait for the sequence's length; this is the first thing that does)
+  const bool blind = (int)blockIdx.x < ahead;
+  int nb = D.max_blocks;
+  if (!blind) nb = num_blocks(D, arrived_ctx(ctx));
   if ((int)blockIdx.x * kScoreWaves * BLK_PER_WAVE >= nb) {
     // the whole workgroup lies beyond the sequence's last block (a ragged batch has many of these):
     // nothing to read, only the row's tail to mark
     const int j = (int)blockIdx.x * kScoreWaves * BLK_PER_WAVE + threadIdx.x;
     if (threadIdx.x < kScoreWaves * BLK_PER_WAVE && j < D.max_blocks) scores[(size_t)pair * D.max_blocks + j] = -INFINITY;
+    clear_counter();
     return;
   }
   const char* dpair = static_cast<const char*>(digest) + (size_t)kv_row(D, pair) * D.max_blocks * EB;
@@ -317,6 +323,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   for (int it = 0; it < kScoreBatch; ++it)
     raw[it] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, j_wave * EB + T::offset(lane, it), 0, 0));
   __builtin_amdgcn_sched_barrier(0);
+  if (blind) nb = num_blocks(D, arrived_ctx(ctx));
 
   {
     double f = 0.0;
@@ -326,6 +333,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
     if (threadIdx.x < 2 * DH) coef_lds[fpos ? 1 : 0][fc] = f;  // MEAN: both rows hold the plain sum
   }
   __syncthreads();
+  clear_counter();
   double coef[T::NL][T::EPL];
   T::coefficients(coef, coef_lds[0], lane);
   double sc = T::scores(raw, coef, lane);
@@ -333,7 +341,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   if (T::writer(lane) && j < D.max_blocks) {
     const bool kept = j < D.n_sink || j >= nb - D.n_tail;  // always-kept blocks rank above every score
     if (MEAN) {  // sums -> means: the block's token count (the last block may be partly filled)
-      int cnt = D.ctx_len[b] - j * D.S;
+      int cnt = arrived_ctx(ctx) - j * D.S;
       cnt = cnt > D.S ? D.S : (cnt < 1 ? 1 : cnt);
       sc = sc / (double)cnt;
     }
@@ -377,7 +385,7 @@ struct HeadTile {
 // NQ: quads of heads (1, 2, 4); heads beyond G repeat head G - 1, which leaves the maximum as it is.
 template <int DT, int DH, int NQ, bool ROWS>
 __global__ __launch_bounds__(kScoreWaves* kWave) void score_heads_kernel(Dims D, const void* q, const void* digest,
-                                                                         float* scores, uint32_t* arrived) {
+                                                                         float* scores, uint32_t* arrived, int ahead) {
   using T = HeadTile<DT, DH>;
   constexpr int EPL = T::EPL, EB = T::EB, NU = T::NU, STEPS = T::STEPS;
   constexpr int NT = kScoreWaves * kWave, HEADS = 4 * NQ;
@@ -394,17 +402,23 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_heads_kernel(Dims D,
   const int b = blockIdx.z, g = blockIdx.y;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int nb = num_blocks_of(D, b);
+  const uint32_t ctx = request_ctx(D, b);
+  const bool blind = (int)blockIdx.x < ahead;  // see score_kernel
+  int nb = D.max_blocks;
+  if (!blind) nb = num_blocks(D, arrived_ctx(ctx));
   const int j_wave = (blockIdx.x * kScoreWaves + wave) * T::BLOCKS;
   const bool active = j_wave < D.max_blocks;
   const int n_rows = ROWS ? D.G : 1;  // rows of `scores` per pair
-  if (arrived != nullptr && blockIdx.x == 0 && (int)threadIdx.x < n_rows) arrived[pair * n_rows + threadIdx.x] = 0;
+  auto clear_counters = [&]() {
+    if (arrived != nullptr && blockIdx.x == 0 && (int)threadIdx.x < n_rows) arrived[pair * n_rows + threadIdx.x] = 0;
+  };
   if ((int)blockIdx.x * kScoreWaves * T::BLOCKS >= nb) {  // as in score_kernel: only the rows' tails to mark
     for (int t = threadIdx.x; t < kScoreWaves * T::BLOCKS; t += NT) {
       const int j = (int)blockIdx.x * kScoreWaves * T::BLOCKS + t;
       if (j < D.max_blocks)
         for (int r = 0; r < n_rows; ++r) scores[((size_t)pair * n_rows + r) * D.max_blocks + j] = -INFINITY;
     }
+    clear_counters();
     return;
   }
 
@@ -437,6 +451,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_heads_kernel(Dims D,
   for (int u = 0; u < NU; ++u)  // requested in the order of use
     raw[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff0 + u * 64, 0, 0));
   __builtin_amdgcn_sched_barrier(0);
+  if (blind) nb = num_blocks(D, arrived_ctx(ctx));
 #pragma unroll
   for (int i = 0; i < QPT; ++i) {
     int h, p, kk, s;
@@ -445,6 +460,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_heads_kernel(Dims D,
     coef_lds[coef_at(h, p + NU / 2, kk, s)] = (double)fmaxf(qreg[i], 0.0f);
   }
   __syncthreads();
+  clear_counters();
 
   f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
   const f64x2* coef = reinterpret_cast<const f64x2*>(coef_lds) + (WIDE ? lane : (lane >> 4) * 4 + (lane & 3));
@@ -544,6 +560,15 @@ int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, 
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
+// Workgroups of each row that ask for their digests before they know the row's length: 128 in all (4 MiB, what memory
+// delivers in the time of that trip), so that rows that are much shorter than max_blocks cost no more than that; with more pairs one
+// of each row, none beyond 256 pairs, whose launches the trip is a small part of.  Steps of four layers: 16 sequences x 8 heads x 1024 blocks
+// 135.9 -> 134.5 us, 8 x 8 104.5 -> 103.4, one sequence 65.7 -> 64.8, 4 x 8 x 4096 111.3 -> 110.5; 256 ragged pairs (two layers) 125.6 -> 125.2.
+static int ahead_groups(const Dims& D) {
+  const int pairs = D.B * D.Hkv;
+  return pairs <= 256 ? (128 + pairs - 1) / pairs : 0;
+}
+
 template <bool ROWS>
 static int launch_score_heads(const Dims& D, int dtype, const void* q, const void* digest, float* scores,
                               uint32_t* arrived, hipStream_t st) {
@@ -552,7 +577,7 @@ static int launch_score_heads(const Dims& D, int dtype, const void* q, const voi
   do {                                                                                                                      \
     constexpr int per_wg = HeadTile<DT, DH>::BLOCKS * kScoreWaves;                                                          \
     hipLaunchKernelGGL((score_heads_kernel<DT, DH, NQ, ROWS>), dim3((D.max_blocks + per_wg - 1) / per_wg, D.Hkv, D.B),      \
-                       dim3(kScoreWaves * kWave), 0, st, D, q, digest, scores, arrived);                                    \
+                       dim3(kScoreWaves * kWave), 0, st, D, q, digest, scores, arrived, ahead_groups(D));                   \
   } while (0)
 #define SCOUT_SCORE_HEADS(DT, DH)                              \
   do {                                                         \
@@ -591,13 +616,13 @@ static int launch_score_sum(const Dims& D, int dtype, const void* q, const void*
   dim3 block(kScoreWaves * kWave);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
   if (dtype == SCOUT_BF16 && D.d == 128)
-    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
+    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
   else if (dtype == SCOUT_BF16 && D.d == 64)
-    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
+    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
   else if (dtype == SCOUT_F32 && D.d == 128)
-    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
+    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
   else if (dtype == SCOUT_F32 && D.d == 64)
-    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived);
+    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
   else
     return SCOUT_EUNSUPPORTED;
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;

@@ -37,6 +37,7 @@ __device__ __forceinline__ float exp2_diff(float a, float b) {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -102,6 +103,71 @@ __device__ __forceinline__ void finish(const Dims& D, const Epilogue& E, int bh,
   if (E.lse != nullptr && c == 0) E.lse[bh] = ls > 0.0f ? ms + logf(ls) : -INFINITY;
 }
 
+// The same for CH consecutive channels of a head, c on, per thread: the weights of the two partials are made once for them.
+// Two: of four, the divisions are a chain that few threads run; of one, every thread makes weights of its own.
+constexpr int CH = 2;
+typedef __attribute__((ext_vector_type(CH))) float fch;
+// The arrays may start anywhere that an element of theirs may.
+typedef fch fch_any __attribute__((aligned(4)));
+typedef __attribute__((ext_vector_type(CH))) uint16_t hch;
+typedef hch hch_any __attribute__((aligned(2)));
+
+struct HostParts {
+  fch o;
+  float m, l;
+};
+
+__device__ __forceinline__ HostParts load_hosts(const Dims& D, const Epilogue& E, int bh, int c) {
+  HostParts hp{};
+  hp.m = -INFINITY;
+  if (E.mode == 2 && E.host_o != nullptr) {
+    hp.m = E.host_m[bh];
+    hp.l = E.host_l[bh];
+    hp.o = *reinterpret_cast<const fch_any*>(E.host_o + (size_t)bh * D.d + c);
+  }
+  return hp;
+}
+
+__device__ __forceinline__ void finish_channels(const Dims& D, const Epilogue& E, int bh, int c, fch acc, float l, float M2,
+                                                const HostParts& hp) {
+  const float m_nat = M2 * kLn2;  // -inf stays -inf
+  fch r;
+#pragma unroll
+  for (int i = 0; i < CH; ++i) r[i] = l > 0.0f ? acc[i] / l : 0.0f;
+  const size_t at = (size_t)bh * D.d + c;
+  if (E.mode == 1) {
+    *reinterpret_cast<fch_any*>(E.o + at) = r;
+    if (c == 0) {
+      E.m[bh] = m_nat;
+      E.l[bh] = l;
+    }
+    return;
+  }
+  const float mb = hp.m, lb = hp.l;
+  float ms = -INFINITY;
+  if (l > 0.0f) ms = fmaxf(ms, m_nat);
+  if (lb > 0.0f) ms = fmaxf(ms, mb);
+  const float wa = l > 0.0f ? l * expf(m_nat - ms) : 0.0f;
+  const float wb = lb > 0.0f ? lb * expf(mb - ms) : 0.0f;
+  const float ls = wa + wb;
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    float x = 0.0f;
+    if (wa > 0.0f) x += wa * r[i];
+    if (wb > 0.0f) x += wb * hp.o[i];
+    r[i] = ls > 0.0f ? x / ls : 0.0f;
+  }
+  if (E.dtype_out == SCOUT_BF16) {
+    hch w;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) w[i] = (uint16_t)f32_to_bf16_bits(r[i]);
+    *reinterpret_cast<hch_any*>(static_cast<uint16_t*>(E.out) + at) = w;
+  } else {
+    *reinterpret_cast<fch_any*>(static_cast<float*>(E.out) + at) = r;
+  }
+  if (E.lse != nullptr && c == 0) E.lse[bh] = ls > 0.0f ? ms + logf(ls) : -INFINITY;
+}
+
 // The work of a pair is cut into units of 16 tokens (a block of S tokens is S/16 units; a unit's K
 // rows and V rows are contiguous, 4 KiB each at bf16, d = 128).  The pair's units are dealt to the waves that share
 // the pair (all waves of all its workgroups) in contiguous ranges whose lengths differ by at most
@@ -129,7 +195,6 @@ __device__ __forceinline__ void finish(const Dims& D, const Epilogue& E, int bh,
 constexpr int kUnitTokens = 16;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 // How a unit of (element type DT, head dim DH) lies in the lanes.
 template <int DT, int DH>
@@ -403,25 +468,67 @@ __device__ __forceinline__ SharedPartials shared_partials(const Partials& P, int
                         __builtin_amdgcn_make_buffer_rsrc(P.l + row0, 0, rows * 4, 0x00020000)};
 }
 
-// Four channels from c on of row `row`; the thread with the first channels stores m and l too.
-__device__ __forceinline__ void store_split(const SharedPartials& R, int row, int c, int dh, float4 o, float m, float l) {
-  const u32x4 w = {__float_as_uint(o.x), __float_as_uint(o.y), __float_as_uint(o.z), __float_as_uint(o.w)};
-  __builtin_amdgcn_raw_buffer_store_b128(w, R.o, (row * dh + c) * 4, 0, kAgentScope);
+// CH channels from c on of row `row`; the thread with the first channels stores m and l too.
+typedef __attribute__((ext_vector_type(CH))) uint32_t uch;
+__device__ __forceinline__ void store_split(const SharedPartials& R, int row, int c, int dh, fch o, float m, float l) {
+  static_assert(CH == 2, "one 8-byte store");
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uch, o), R.o, (row * dh + c) * 4, 0, kAgentScope);
   if (c == 0) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m), R.m, row * 4, 0, kAgentScope);
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(l), R.l, row * 4, 0, kAgentScope);
   }
 }
 
+// Splits s0, s0 + step, ... of head h, channels c on: four requested at a time.
+template <int DH>
+__device__ __forceinline__ void gather_splits(const Partials& P, const SharedPartials& R, int G, int h, int c, int s0, int step, fch& o,
+                                              float& l, float& M) {
+  constexpr int GROUP = 4;
+  M = -INFINITY;
+  l = 0.0f;
+  o = fch{};
+  for (; s0 < P.nsplit; s0 += GROUP * step) {
+    fch w[GROUP];
+    float ms[GROUP], ls[GROUP];
+#pragma unroll
+    for (int j = 0; j < GROUP; ++j) {  // rows beyond the last split lie outside the descriptors and read as zeros
+      const int row = (s0 + j * step) * G + h;
+      w[j] = __builtin_bit_cast(fch, __builtin_amdgcn_raw_buffer_load_b64(R.o, (row * DH + c) * 4, 0, kAgentScope));
+      ms[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(R.m, row * 4, 0, kAgentScope));
+      ls[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(R.l, row * 4, 0, kAgentScope));
+    }
+    float Mn = M;
+#pragma unroll
+    for (int j = 0; j < GROUP; ++j) {
+      if (s0 + j * step >= P.nsplit) ms[j] = -INFINITY;
+      Mn = fmaxf(Mn, ms[j]);
+    }
+    const float f0 = exp2_diff(M, Mn);
+    o *= f0;
+    l *= f0;
+#pragma unroll
+    for (int j = 0; j < GROUP; ++j) {
+      if (s0 + j * step < P.nsplit) {
+        const float f = exp2_diff(ms[j], Mn);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) o[i] += f * w[j][i];
+        l += f * ls[j];
+      }
+    }
+    M = Mn;
+  }
+}
+
 // Every thread of the workgroup calls this after its store_split calls.  `flag`: a word of LDS outside smem.
-// The threads take 4 channels of a head each, as many times over (`parts`) as the workgroup has threads and smem areas
-// for; part i folds splits i, i + parts, ..., four of them requested at a time, and the parts meet in LDS.
+// A thread takes CH channels of a head.  Up to four splits it takes all of them, one trip, and finishes its channels; of more, the
+// workgroup's threads take them in `parts`, as many as it has threads and smem areas for (part i: splits i, i + parts, ...), which
+// meet in LDS.  hp: the host's partial for the thread's first channels.
 template <int DH, int WAVES>
 __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pair, const Partials& P, const Epilogue& E,
-                                            const HostPart* hp, float* smem, int* flag) {
-  constexpr int ROW = DH + 4, Q = DH / 4;  // Q: threads per head
-  constexpr int NTHREADS = WAVES * kWave;
-  const int G = D.G, wstride = G * ROW + 32;
+                                            const HostParts& hp, float* smem, int* flag) {
+  constexpr int ROW = DH + 4, Q = DH / CH;  // Q: threads per head
+  constexpr int NT = WAVES * kWave;
+  const int G = D.G, wstride = G * ROW + 32, bh0 = b * D.Hq + g * G;
   __builtin_amdgcn_s_waitcnt(0);  // the partial's stores have been acknowledged
   __syncthreads();
   if (threadIdx.x == 0)
@@ -429,71 +536,49 @@ __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pai
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(*flag) != P.nsplit - 1) return;
 
-  constexpr int kOutPerThread = (16 * DH + NTHREADS - 1) / NTHREADS;
-  const int slab = threadIdx.x / Q;                               // below 32
-  const int part = (int)(((uint32_t)slab * P.g_magic) >> 16);     // slab / G
-  const int h = slab - part * G, c = (threadIdx.x % Q) * 4;
-  int parts = (int)(((uint32_t)(NTHREADS / Q) * P.g_magic) >> 16);  // NTHREADS / Q is 16 or 32
+  const SharedPartials R = shared_partials<DH>(P, pair, G);
+  int parts = (int)(((uint32_t)(NT / Q) * P.g_magic) >> 16);  // NT / Q / G
   parts = parts < WAVES ? parts : WAVES;
   parts = parts < P.nsplit ? parts : P.nsplit;
-  const SharedPartials R = shared_partials<DH>(P, pair, G);
-  if (part < parts) {
-    constexpr int GROUP = 4;
-    float M = -INFINITY, l = 0.0f;
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = part; s0 < P.nsplit; s0 += GROUP * parts) {
-      u32x4 w[GROUP];
-      float ms[GROUP], ls[GROUP];
-#pragma unroll
-      for (int j = 0; j < GROUP; ++j) {  // rows beyond the last split lie outside the descriptors and read as zeros
-        const int row = (s0 + j * parts) * G + h;
-        w[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(R.o, (row * DH + c) * 4, 0, kAgentScope));
-        ms[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(R.m, row * 4, 0, kAgentScope));
-        ls[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(R.l, row * 4, 0, kAgentScope));
-      }
-      float Mn = M;
-#pragma unroll
-      for (int j = 0; j < GROUP; ++j) {
-        if (s0 + j * parts >= P.nsplit) ms[j] = -INFINITY;
-        Mn = fmaxf(Mn, ms[j]);
-      }
-      const float f0 = exp2_diff(M, Mn);
-      o.x *= f0; o.y *= f0; o.z *= f0; o.w *= f0;
-      l *= f0;
-#pragma unroll
-      for (int j = 0; j < GROUP; ++j) {
-        if (s0 + j * parts < P.nsplit) {
-          const float f = exp2_diff(ms[j], Mn);
-          o.x += f * __uint_as_float(w[j][0]); o.y += f * __uint_as_float(w[j][1]);
-          o.z += f * __uint_as_float(w[j][2]); o.w += f * __uint_as_float(w[j][3]);
-          l += f * ls[j];
-        }
-      }
-      M = Mn;
+  if (parts <= 1 || P.nsplit <= 4) {
+    for (int item = threadIdx.x; item < G * Q; item += NT) {
+      const int h = item / Q, c = (item % Q) * CH;
+      float M, l;
+      fch o;
+      gather_splits<DH>(P, R, G, h, c, 0, 1, o, l, M);
+      finish_channels(D, E, bh0 + h, c, o, l, M, item < NT ? hp : load_hosts(D, E, bh0 + h, c));
     }
+    return;
+  }
+  const int slab = threadIdx.x / Q;                              // below 16
+  const int part = (int)(((uint32_t)slab * P.g_magic) >> 16);    // slab / G
+  const int h = slab - part * G, c = (threadIdx.x % Q) * CH;
+  float M, l;
+  fch o;
+  if (part < parts) {
+    gather_splits<DH>(P, R, G, h, c, part, parts, o, l, M);
     float* area = smem + (size_t)part * wstride;
-    *reinterpret_cast<float4*>(area + h * ROW + c) = o;
+    *reinterpret_cast<fch*>(area + h * ROW + c) = o;
     if (c == 0) {
       area[G * ROW + h] = M;
       area[G * ROW + 16 + h] = l;
     }
   }
   __syncthreads();
+  if (slab >= G) return;
+  M = -INFINITY;
+  l = 0.0f;
+  o = fch{};
+  for (int w = 0; w < parts; ++w) M = fmaxf(M, smem[(size_t)w * wstride + G * ROW + h]);
+  for (int w = 0; w < parts; ++w) {
+    const float* base = smem + (size_t)w * wstride;
+    const float f = exp2_diff(base[G * ROW + h], M);
+    const fch x = *reinterpret_cast<const fch*>(base + h * ROW + c);
 #pragma unroll
-  for (int t = 0; t < kOutPerThread; ++t) {
-    const int idx = threadIdx.x + t * NTHREADS;
-    if (idx >= G * DH) break;
-    const int hh = idx / DH, cc = idx % DH;
-    float M = -INFINITY, o = 0.0f, l = 0.0f;
-    for (int w = 0; w < parts; ++w) M = fmaxf(M, smem[(size_t)w * wstride + G * ROW + hh]);
-    for (int w = 0; w < parts; ++w) {
-      const float* base = smem + (size_t)w * wstride;
-      const float f = exp2_diff(base[G * ROW + hh], M);
-      o += f * base[hh * ROW + cc];
-      l += f * base[G * ROW + 16 + hh];
-    }
-    finish(D, E, b * D.Hq + g * G + hh, cc, o, l, M, hp[t]);
+    for (int i = 0; i < CH; ++i) o[i] += f * x[i];
+    l += f * base[G * ROW + 16 + h];
   }
+  finish_channels(D, E, bh0 + h, c, o, l, M, hp);
 }
 
 // The attention of one workgroup: its share (split) of the pair's list, folded over the waves
@@ -629,15 +714,11 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   // lanes kg = 0..3 of a head saw disjoint tokens under a common maximum
   l_run = sum_xor32(sum_xor16(l_run));
 
-  // the host's partial for the outputs this thread will finish: requested now, used after the fold
-  constexpr int kOutPerThread = (16 * DH + WAVES * kWave - 1) / (WAVES * kWave);
-  HostPart hp[kOutPerThread];
-#pragma unroll
-  for (int t = 0; t < kOutPerThread; ++t) {
-    const int idx = threadIdx.x + t * WAVES * kWave;
-    const int hh = idx < G * DH ? idx / DH : 0;
-    hp[t] = load_host(D, E, b * D.Hq + g * G + hh, idx % DH);
-  }
+  // CH channels of a head per thread, as many times over as it takes.  The host's partial for the first of them is requested
+  // now and used after the fold.
+  constexpr int Q = DH / CH, NT = WAVES * kWave;
+  const int bh0 = b * D.Hq + g * G;
+  const HostParts hp = load_hosts(D, E, bh0 + ((int)threadIdx.x < G * Q ? threadIdx.x / Q : 0), (threadIdx.x % Q) * CH);
 
   // fold the waves of the workgroup through LDS
   float* wo = smem + (size_t)wave * wstride;
@@ -659,58 +740,39 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   }
   __syncthreads();
   const size_t pbase = (size_t)pair * P.nsplit + split;
-  if (FOLD || E.mode == 0) {
-    // partial of this split: four channels per thread, 16-byte LDS reads and one 16-byte store
-    for (int item = threadIdx.x; item < G * (DH / 4); item += WAVES * kWave) {
-      const int h = item / (DH / 4), c = (item % (DH / 4)) * 4;
-      float mw[WAVES];
-      float M = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) {
-        mw[w] = smem[(size_t)w * wstride + G * ROW + h];
-        M = fmaxf(M, mw[w]);
-      }
-      float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-      float l = 0.0f;
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) {
-        const float* base = smem + (size_t)w * wstride;
-        const float f = exp2_diff(mw[w], M);
-        const float4 x = *reinterpret_cast<const float4*>(base + h * ROW + c);
-        o.x += f * x.x; o.y += f * x.y; o.z += f * x.z; o.w += f * x.w;
-        l += f * base[G * ROW + 16 + h];
-      }
-      if constexpr (FOLD) {
-        store_split(shared_partials<DH>(P, pair, G), split * G + h, c, DH, o, M, l);
-      } else {
-        *reinterpret_cast<float4*>(P.o + (pbase * G + h) * DH + c) = o;
-        if (c == 0) {
-          P.m[pbase * G + h] = M;
-          P.l[pbase * G + h] = l;
-        }
-      }
-    }
-    if constexpr (FOLD) fold_splits<DH, WAVES>(D, b, g, pair, P, E, hp, smem, flag);
-    return;
-  }
-#pragma unroll
-  for (int t = 0; t < kOutPerThread; ++t) {
-    const int idx = threadIdx.x + t * WAVES * kWave;
-    if (idx >= G * DH) break;
-    const int h = idx / DH, c = idx % DH;
+  for (int item = threadIdx.x; item < G * Q; item += NT) {
+    const int h = item / Q, c = (item % Q) * CH;
+    float mw[WAVES];
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) M = fmaxf(M, smem[(size_t)w * wstride + G * ROW + h]);
-    float o = 0.0f, l = 0.0f;
+    for (int w = 0; w < WAVES; ++w) {
+      mw[w] = smem[(size_t)w * wstride + G * ROW + h];
+      M = fmaxf(M, mw[w]);
+    }
+    fch o{};
+    float l = 0.0f;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
       const float* base = smem + (size_t)w * wstride;
-      const float f = exp2_diff(base[G * ROW + h], M);
-      o += f * base[h * ROW + c];
+      const float f = exp2_diff(mw[w], M);
+      const fch x = *reinterpret_cast<const fch*>(base + h * ROW + c);
+#pragma unroll
+      for (int i = 0; i < CH; ++i) o[i] += f * x[i];
       l += f * base[G * ROW + 16 + h];
     }
-    finish(D, E, b * D.Hq + g * G + h, c, o, l, M, hp[t]);
+    if constexpr (FOLD) {
+      store_split(shared_partials<DH>(P, pair, G), split * G + h, c, DH, o, M, l);
+    } else if (E.mode == 0) {
+      *reinterpret_cast<fch*>(P.o + (pbase * G + h) * DH + c) = o;
+      if (c == 0) {
+        P.m[pbase * G + h] = M;
+        P.l[pbase * G + h] = l;
+      }
+    } else {
+      finish_channels(D, E, bh0 + h, c, o, l, M, item < NT ? hp : load_hosts(D, E, bh0 + h, c));
+    }
   }
+  if constexpr (FOLD) fold_splits<DH, WAVES>(D, b, g, pair, P, E, hp, smem, flag);
 }
 
 // Which (sequence, KV head, pair, split) a workgroup of the attention kernels works on.  Normally the grid

@@ -61,3 +61,26 @@ def test_fold_in_the_launch(dtype, d, G, k, nsplits):
         assert torch.equal(torch.isfinite(outs[0][1]), fin)
         top = max(1.0, dev.lse[fin].abs().max().item())
         assert (outs[0][1] - dev.lse)[fin].abs().max().item() <= (2.0 ** -8 if bf16 else 1.2e-5 * top), nsplit
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("nsplit", [1, 3, 9])
+def test_outputs_and_host_partials_may_start_at_any_element(dtype, d, nsplit):
+    """The epilogues take channels two at a time: arrays that start one element behind an aligned address give the same bits."""
+    cfg = W.shrink(W.tiny(), name=f"odd-{dtype}", B=2, Hq=8, Hkv=2, d=d, S=16, dtype=dtype, ctx=(16 * 90 + 5, 16 * 41), k=40, p_host=0.3)
+    wl = W.generate(cfg)
+    dev = Dev(wl)
+    dev.build_digests()
+    dev.set_host_partials_from_oracle(harness.run_all(wl))
+    odd = lambda t: torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape).copy_(t)
+    outs = []
+    B.set_attn_mode(0, nsplit, 0)
+    try:
+        for shift in (lambda t: t.clone(), odd):
+            ho, hm, hl, out, lse = (shift(t) for t in (dev.host_o, dev.host_m, dev.host_l, dev.out, dev.lse))
+            B.layer_step(dev.p, dev.q, dev.digest, dev.block_table, dev.k_pool, dev.v_pool, dev.n_slots, ho, hm, hl, dev.scores, dev.sel_all,
+                         dev.sel_gpu, dev.slot_gpu, dev.n_gpu, dev.sel_host, dev.n_host, out, lse, dev.ws)
+            outs.append((out, lse))
+    finally:
+        B.set_attn_mode(0, 0, 0)
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])

@@ -1000,11 +1000,8 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   int* l_x = l_lists + lists_lds_ints(kpad);
   int* l_n = l_x + selector_lds_ints<WAVES>();
 
-  QRegs<DT, DH> qreg;
-  load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
   const int ctx = D.ctx_len[b];  // once, here: the attention below must not wait for it again
-
-  const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
+  QRegs<DT, DH> qreg;
   uint32_t touched_k = 0, touched_v = 0;
   int k_eff;
 
@@ -1012,7 +1009,15 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
     const int sw = wave;
     float sc[KPL];
     int slot[KPL];
+    // In the order of use, because a wait for one load is a wait for those before it: what is selected from, the hint, the queries
+    // (which the attention needs).  With the queries and the hint in front: 16 sequences of 32k tokens 131.7 us a step instead of 130.2, 8 sequences
+    // 101.8 instead of 99.7.
     load_scores<WAVES, KPL>(D, scores, table, pair, sw, lane, sc, slot);
+    __builtin_amdgcn_sched_barrier(0);
+    const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
+    __builtin_amdgcn_sched_barrier(0);
+    load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
+    __builtin_amdgcn_sched_barrier(0);
     Selector<WAVES, KPL> S{l_x, 0, sw};
     S.prepare();
     int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;

@@ -268,7 +268,11 @@ constexpr int kScoreWaves = 4;      // waves per workgroup
 // coefficient vector instead of two and a division by the block's token count at the end.
 // AHEAD: the first `ahead` workgroups of a row (ahead_groups) ask for their digests without waiting for the sequence's length,
 // a trip to memory in which it would have nothing to do; what lies beyond the last block is dropped afterwards.
-template <int DT, int DH, bool MEAN>
+//
+// NH: query rows that a thread asks for, the group's and, up to 4, 8 or 16, its last one again: narrow loads in front of the
+// digests'.  Sixteen for whatever group: 8 sequences x 8 heads of 64 channels, groups of four, 79.4 us a step instead of 78.5, one sequence
+// 64.7 and 64.25; groups of eight 0.1 %.
+template <int DT, int DH, bool MEAN, int NH>
 __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
     Dims D, const void* q, const void* digest, float* scores, uint32_t* arrived, int ahead) {
   using T = ScoreTile<DT, DH, MEAN>;
@@ -292,9 +296,9 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   const int fc = threadIdx.x % DH;
   const bool fpos = threadIdx.x >= DH;
   const char* qbase = static_cast<const char*>(q) + (((size_t)b * D.Hq + g * D.G) * DH + fc) * ESZ;
-  float qv[16];
+  float qv[NH];
 #pragma unroll
-  for (int h = 0; h < 16; ++h) {  // rows beyond the group re-read its last row and are ignored below
+  for (int h = 0; h < NH; ++h) {  // rows beyond the group re-read its last row and are ignored below
     const int hs = h < D.G ? h : D.G - 1;
     if (DT == SCOUT_BF16)
       qv[h] = __uint_as_float((uint32_t) * reinterpret_cast<const uint16_t*>(qbase + (size_t)hs * DH * ESZ) << 16);
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
   {
     double f = 0.0;
 #pragma unroll
-    for (int h = 0; h < 16; ++h)
+    for (int h = 0; h < NH; ++h)
       if (h < D.G) f += MEAN ? (double)qv[h] : (double)(fpos ? fmaxf(qv[h], 0.0f) : fminf(qv[h], 0.0f));
     if (threadIdx.x < 2 * DH) coef_lds[fpos ? 1 : 0][fc] = f;  // MEAN: both rows hold the plain sum
   }
@@ -615,16 +619,21 @@ static int launch_score_sum(const Dims& D, int dtype, const void* q, const void*
   dim3 grid((D.max_blocks + blocks_per_wg - 1) / blocks_per_wg, D.Hkv, D.B);
   dim3 block(kScoreWaves * kWave);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SCOUT_OK;
-  if (dtype == SCOUT_BF16 && D.d == 128)
-    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
-  else if (dtype == SCOUT_BF16 && D.d == 64)
-    hipLaunchKernelGGL((score_kernel<SCOUT_BF16, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
-  else if (dtype == SCOUT_F32 && D.d == 128)
-    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 128, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
-  else if (dtype == SCOUT_F32 && D.d == 64)
-    hipLaunchKernelGGL((score_kernel<SCOUT_F32, 64, MEAN>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D));
-  else
-    return SCOUT_EUNSUPPORTED;
+#define SCOUT_SCORE_NH(DT, DH, NH) \
+  hipLaunchKernelGGL((score_kernel<DT, DH, MEAN, NH>), grid, block, 0, st, D, q, digest, scores, arrived, ahead_groups(D))
+#define SCOUT_SCORE(DT, DH)                      \
+  do {                                           \
+    if (D.G <= 4) SCOUT_SCORE_NH(DT, DH, 4);     \
+    else if (D.G <= 8) SCOUT_SCORE_NH(DT, DH, 8); \
+    else SCOUT_SCORE_NH(DT, DH, 16);             \
+  } while (0)
+  if (dtype == SCOUT_BF16 && D.d == 128) SCOUT_SCORE(SCOUT_BF16, 128);
+  else if (dtype == SCOUT_BF16 && D.d == 64) SCOUT_SCORE(SCOUT_BF16, 64);
+  else if (dtype == SCOUT_F32 && D.d == 128) SCOUT_SCORE(SCOUT_F32, 128);
+  else if (dtype == SCOUT_F32 && D.d == 64) SCOUT_SCORE(SCOUT_F32, 64);
+  else return SCOUT_EUNSUPPORTED;
+#undef SCOUT_SCORE
+#undef SCOUT_SCORE_NH
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 

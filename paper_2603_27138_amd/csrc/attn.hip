@@ -1417,15 +1417,12 @@ int launch_attn(const Dims& D, int dtype, int family, int waves, const void* q, 
 }
 
 // Whether the last workgroup of a pair folds its splits, or a launch of its own does.  One workgroup folds nsplit * G * d
-// floats where combine_kernel has one per head, so it pays for few heads or many splits, and with 8 heads of 128 channels also
-// where all workgroups run at once (the fold of one does not hold up the next).  A step with the fold in the launch over
-// one without, bf16, d = 128, lists of 32 to 128 blocks: 1 to 4 heads 0.94 to 1.00 whatever the splits; 8 heads: 8 splits 0.95, 4
-// splits 0.99, 96 pairs x 3 1.01 to 1.02, 128 x 2 0.995 to 1.00, 184 x 2 1.005; 16 heads: 8 splits 0.99, 4 splits 1.01 to 1.02, 3
-// splits 1.02 to 1.03, 2 splits 1.01 to 1.02.  d = 64: up to 8 heads 0.93 to 1.00; 16 heads 0.93 to 0.98 from 4 splits on, 96 x 3 1.00 to
-// 1.02, 128 x 2 1.00, 184 x 2 1.00 to 1.01.  fp32, d = 128: 0.96 to 1.00 from 4 splits on, 128 x 2 0.98 to 1.00, 184 x 2 1.01 to 1.04.
-bool fold_pays(const Dims& D, int nsplit) {
-  return nsplit * 256 >= D.G * D.d || (D.G * D.d <= 1024 && D.B * D.Hkv * nsplit <= 256);
-}
+// floats where combine_kernel has one per head, so it does not pay for many heads and few splits.  A step of two layers, us, fold in the launch
+// and in one of its own, pairs x splits of 512 blocks: bf16, d = 128, 4 heads 184 x 2 78.2 and 79.6; 8 heads 64 x 4 34.65 and 37.3,
+// 96 x 3 53.4 and 54.3, 184 x 2 80.3 and 82.0; 16 heads 64 x 4 39.9 and 40.0, 96 x 3 58.5 and 58.2, 128 x 2 57.3 and 57.0, 184 x 2 87.1 and
+// 85.4.  d = 64, 16 heads: 128 x 2 36.5 and 39.0, 184 x 2 49.5 and 51.2.  fp32, d = 128, 256 blocks: 8 heads 128 x 2 90.7 and 94.0, 184 x 2 146.7 and
+// 147.2; 16 heads 64 x 4 59.8 and 60.8.
+bool fold_pays(const Dims& D, int nsplit) { return D.G * D.d <= 1024 || nsplit >= 4; }
 
 bool select_attend_supported(const Dims& D) { return D.max_blocks <= 8 * kWave * 16; }
 

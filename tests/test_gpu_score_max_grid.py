@@ -1,5 +1,5 @@
-"""Head-wise scores in launches on both sides of the line between the two register budgets of the kernel: the same blocks
-give the same bits in a launch of few workgroups (a part of the batch at a time) and of many, and they are the binary64
+"""Head-wise scores in launches of few workgroups and of many (around the sizes at which the instances of an earlier kernel
+changed): the same blocks give the same bits in a launch of a part of the batch at a time and of the whole, and they are the binary64
 scores rounded to binary32 (two summation orders in binary64 differ by less than 2^-40 of the sum of magnitudes, so the
 rounded values by at most one step of 2^-23)."""
 import pytest

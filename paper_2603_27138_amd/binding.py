@@ -186,8 +186,11 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _ptr_addressable(t: torch.Tensor):
-    """Device tensor, or a CPU tensor in pinned memory (which the GPU addresses at the same pointer)."""
+    """Device tensor, or a CPU tensor in pinned memory (which the GPU addresses at the same pointer, and which the allocator
+    of pinned memory keeps back until the current stream's work is done, also if the tensor is dropped before)."""
     assert t.is_contiguous() and (t.is_cuda or t.is_pinned()), "need a CUDA tensor or a pinned CPU tensor"
+    if isinstance(t, torch.Tensor) and not t.is_cuda:
+        (_calls or _load_calls()).used_by_stream(t)
     return ctypes.c_void_p(t.data_ptr())
 
 

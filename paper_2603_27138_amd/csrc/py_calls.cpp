@@ -9,6 +9,8 @@
 // torch throws becomes the Python exception that its own calls raise (entry).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+#include <ATen/DeviceAccelerator.h>
+#include <ATen/core/CachingHostAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -30,6 +32,16 @@ void* address_by(PyObject* f, PyObject* arg) {
   Py_XDECREF(r);
   Py_XDECREF(value);
   return address;
+}
+
+// A pinned tensor that work on the current stream reads or writes: its memory goes to another tensor only after that work,
+// however early the tensor itself is dropped.  (The allocator of pinned memory knows of copies by itself, of kernels it does not;
+// memory that is not its own it leaves alone.)
+void used_by_stream(const at::Tensor& t) {
+  const at::DeviceType device = at::accelerator::getAccelerator(true).value();
+  const at::DataPtr& memory = t.storage().data_ptr();
+  at::getHostAllocator(device)->record_event(memory.get(), memory.get_context(),
+                                             at::accelerator::getCurrentStream(at::accelerator::getDeviceIndex()));
 }
 
 // One argument list on its way to the C ABI: problem, tensors by position, then workspace and stream.
@@ -92,6 +104,7 @@ struct Args {
       ok = false;
       return nullptr;
     }
+    if (!t.is_cuda()) used_by_stream(t);
     return t.data_ptr();
   }
   template <class T = void>
@@ -384,6 +397,16 @@ PyObject* py_bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Py_RETURN_NONE;
 }
 
+// used_by_stream(pinned tensor)
+PyObject* py_used_by_stream(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 1 || !THPVariable_Check(a[0])) {
+    PyErr_SetString(PyExc_TypeError, "used_by_stream(tensor)");
+    return nullptr;
+  }
+  used_by_stream(THPVariable_Unpack(a[0]));
+  Py_RETURN_NONE;
+}
+
 // Nothing that torch throws passes into the interpreter's C frames.
 template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
 PyObject* entry(PyObject* self, PyObject* const* a, Py_ssize_t n) {
@@ -399,6 +422,7 @@ PyObject* entry(PyObject* self, PyObject* const* a, Py_ssize_t n) {
 #define SCOUT_METHOD(NAME) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(entry<py_##NAME>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
     SCOUT_METHOD(bind),
+    SCOUT_METHOD(used_by_stream),
     SCOUT_METHOD(build_digests),
     SCOUT_METHOD(append_token),
     SCOUT_METHOD(score_blocks),

@@ -36,6 +36,15 @@ class Layer:
     v_blocks: torch.Tensor
 
 
+def _in_form_of(q: torch.Tensor, like: torch.Tensor) -> torch.Tensor:
+    """q as `like` has it, before anything reads its memory as that: a query of another element type or with fewer dimensions is
+    converted and repeated as copy_ would do it, and refused where copy_ refuses it."""
+    if q.shape == like.shape and q.dtype == like.dtype:
+        return q
+    assert q.is_contiguous(), "device tensors must be contiguous CUDA tensors"
+    return q.detach().to(like.dtype).expand(like.shape).contiguous()
+
+
 class _LayerBuffers:
     def __init__(self, Bn, Hq, Hkv, d, mb, k, tdt):
         dev = dict(device="cuda")
@@ -108,10 +117,9 @@ class LayerAheadPipeline:
     # -- Algorithm 1, "trigger next layer's CPU-side pre-computation"
     def _trigger(self, i: int, q_pred: torch.Tensor):
         L, b = self.layers[i], self.buf[i]
+        q_pred = _in_form_of(q_pred, b.q_pred_h)
         B.select_ahead(self.p, q_pred, L.digest, L.block_table, b.scores, b.sel_all, b.sel_gpu, b.slot_gpu, b.n_gpu,
                        b.sel_host, b.n_host, b.sel_host_h, b.n_host_h, b.q_pred_h)
-        if q_pred.shape != b.q_pred_h.shape or q_pred.dtype != b.q_pred_h.dtype:
-            b.q_pred_h.copy_(q_pred, non_blocking=True)   # what a copy makes of it, or refuses
         b.selected.record()
 
     def _spawn(self, i: int):

@@ -172,6 +172,9 @@ class LayerAheadPipeline:
                              L.k_pool, L.v_pool, L.n_slots)
             b.arrived = torch.cuda.Event()
             b.arrived.record()
+        # used here on another stream than their own: dropped with the pipeline, they wait for it
+        for t in (self.staged, self.tile_off, b.recall_blk, b.recall_slot, b.n_recall, L.k_pool, L.v_pool, self.ctx_len):
+            t.record_stream(self.copy_stream)
 
     def step(self, qs: List[torch.Tensor], q_preds: List[torch.Tensor], host: bool = True):
         """One decode step over all layers.  qs[i]: the real query of layer i, q_preds[i]: the one

@@ -1,5 +1,6 @@
 """Pinned host memory that kernels read or write belongs to them until they are done: a tensor that is dropped behind a call that
-is still queued must not come back from the allocator of pinned memory for somebody else before that call has run."""
+is still queued must not come back from the allocator of pinned memory for somebody else before that call has run.  The same holds for
+device memory that a recall uses on the pipeline's copy stream."""
 import gc
 
 import pytest
@@ -102,3 +103,30 @@ def test_a_dropped_pipeline_waits_for_the_stream():
     assert busy, "the stream was not kept busy for long enough"
     assert not were & now
     assert torch.equal(outs[0], want[0])
+
+
+def test_a_dropped_pipeline_waits_for_its_copy_stream():
+    _, ctx = _problem()
+    q, digest, table, kp, vp = _device_state()
+    table[0, 0, ::2] = -1
+    kb, vb = (torch.randn(Bn, Hkv, mb, S, d).pin_memory() for _ in range(2))
+    pipe = P.LayerAheadPipeline(Bn, Hq, Hkv, d, S, B.F32, mb, k, ctx, [P.Layer(digest, table, kp, vp, mb, kb, vb)], n_threads=1,
+                                recall_every=1)
+    digest[:, :, ::2] += 100.0        # the blocks in host memory are the important ones
+    q.fill_(1.0)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(pipe.copy_stream):
+        torch.cuda._sleep(BUSY)
+    pipe.step([q], [q])
+    assert pipe.recalled_tiles > 0
+    done, b = pipe.buf[0].arrived, pipe.buf[0]
+    mine = [pipe.staged, pipe.tile_off, b.recall_blk, b.recall_slot, b.n_recall]
+    sizes, were = [t.numel() * t.element_size() for t in mine], {t.data_ptr() for t in mine}
+    pipe.close()
+    del pipe, b, mine
+    gc.collect()
+    fresh = [torch.empty(n, dtype=torch.uint8, device="cuda") for n in sizes for _ in range(8)]
+    busy = not done.query()
+    torch.cuda.synchronize()
+    assert busy, "the copy stream was not kept busy for long enough"
+    assert not were & {t.data_ptr() for t in fresh}

@@ -5,7 +5,7 @@
 
 namespace scout {
 
-constexpr int kMaxK = 1024;
+constexpr int kMaxK = 1024;  // what check_problem lets through
 
 // AHEAD: the host's work list and the queries it goes with (HostJob) leave in the same launch, by stores to host memory:
 // as copies of their own they cost the stream 5 and 10 us behind the selection, for 4 sequences of 8k tokens.
@@ -161,8 +161,8 @@ __global__ __launch_bounds__(WAVES* kWave) void recall_kernel(
 #define SCOUT_RECALL(WAVES, KPL) recall_kernel<WAVES, KPL>
 #define SCOUT_TOPK_DISPATCH(KERNEL, ...)                                                     \
   do {                                                                                       \
-    dim3 grid(1, D.Hkv, D.B);                                                                   \
-    if (grid.x == 0) return SCOUT_OK;                                                        \
+    if (D.B == 0) return SCOUT_OK;                                                           \
+    dim3 grid(1, D.Hkv, D.B);                                                                \
     if (D.max_blocks <= 256)                                                                 \
       hipLaunchKernelGGL((KERNEL(1, 4)), grid, dim3(kWave), 0, st, __VA_ARGS__);             \
     else if (D.max_blocks <= 1024)                                                           \
@@ -178,7 +178,6 @@ __global__ __launch_bounds__(WAVES* kWave) void recall_kernel(
 int launch_topk(const Dims& D, const float* scores, const int32_t* table, int32_t* sel_all,
                 int32_t* sel_gpu, int32_t* slot_gpu, int32_t* n_gpu, int32_t* sel_host,
                 int32_t* n_host, const HostJob* job, hipStream_t st) {
-  if (job != nullptr && D.k > kMaxK) return SCOUT_EUNSUPPORTED;
   if (job != nullptr)
     SCOUT_TOPK_DISPATCH(SCOUT_TOPK_AHEAD, D, scores, table, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host, *job);
   else

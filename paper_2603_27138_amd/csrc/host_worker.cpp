@@ -5,11 +5,11 @@
 // A job is the list of (sequence, KV head) pairs of one layer-step.  Threads take pairs from an atomic
 // counter, heaviest pairs first would not pay here: pairs are small (a few blocks) and there are many
 // more of them than threads.  A thread keeps one online-softmax stream per query head of the pair and
-// walks the pair's blocks once: a block's K rows are widened to binary32 once and used by all G
-// heads, then its V rows likewise.  The channels are the vector lanes of both products, four heads (two without
-// AVX-512) at a time so that a row of K or V is loaded once for them; the query heads of the group are those of the softmax
-// bookkeeping.  Idle threads spin briefly on the job counter before they sleep:
-// a layer-step is tens to hundreds of microseconds, a futex wake-up alone is of that order.
+// walks the pair's blocks once: a block's K rows for all G heads, then its V rows likewise.  The channels are the vector lanes of
+// both products, several heads at a time so that a row of K or V is loaded once for them (host_kernels.inc says how many, and
+// where the heads are the lanes of the logits instead); the query heads of the group are those of the softmax
+// bookkeeping.  The AVX-512 copy reads bf16 rows as they lie, the others widen a block's rows to binary32 first.  Idle threads
+// spin briefly on the job counter before they sleep: a layer-step is tens to hundreds of microseconds, a futex wake-up alone is of that order.
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -46,12 +46,15 @@ struct Job {
 };
 
 #define SCOUT_HOST_LANES 8
+#define SCOUT_HOST_HEAD_LANES 0
 namespace scout_host_generic {
 using ::Job;
 #include "host_kernels.inc"
 }  // namespace scout_host_generic
 
 #if defined(__x86_64__)
+#undef SCOUT_HOST_HEAD_LANES
+#define SCOUT_HOST_HEAD_LANES 1
 #pragma GCC push_options
 #pragma GCC target("avx2,fma")
 namespace scout_host_avx2 {
@@ -61,6 +64,8 @@ using ::Job;
 #pragma GCC pop_options
 #undef SCOUT_HOST_LANES
 #define SCOUT_HOST_LANES 16
+#undef SCOUT_HOST_HEAD_LANES
+#define SCOUT_HOST_HEAD_LANES 0
 #pragma GCC push_options
 #pragma GCC target("avx2,fma,avx512f,avx512bw,avx512dq,avx512vl")
 namespace scout_host_avx512 {
@@ -70,6 +75,7 @@ using ::Job;
 #pragma GCC pop_options
 #endif
 #undef SCOUT_HOST_LANES
+#undef SCOUT_HOST_HEAD_LANES
 
 namespace {
 

@@ -25,7 +25,7 @@ def test_narrower_copies_pass_the_workers_tests(tmp_path, isa):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("G", [1, 2, 3, 5, 8, 9, 16])
+@pytest.mark.parametrize("G", [1, 2, 3, 5, 8, 9, 13, 16])
 @pytest.mark.parametrize("d,S,ctx", [(8, 16, 33), (40, 7, 30), (64, 16, 48), (128, 64, 65), (248, 5, 23), (256, 32, 63)])
 def test_edges_of_the_blocks(dtype, G, d, S, ctx):
     from paper_2603_27138_amd import host as H

@@ -141,7 +141,11 @@ struct scout_host_worker {
   Job queued;
   bool has_queued = false;
   uint64_t submitted = 0, completed = 0, waited = 0;  // jobs handed in, finished, reported by wait()
-  std::chrono::steady_clock::time_point t_start[2], t_end[2];  // of job number n, at n % 2
+  std::chrono::steady_clock::time_point t_start;  // of the running job
+  // What job number n took, at n % kTimes.  A caller may leave any number of finished jobs unreported; one that is more than kTimes behind
+  // gets the time of a later job.
+  static constexpr int kTimes = 64;
+  double seconds[kTimes] = {};
   std::atomic<uint64_t> generation{0};  // bumped at every submit
   std::atomic<uint64_t> ticket{0};      // (generation << 32) | next pair: a thread still leaving the
                                         // previous job can never take a pair of the next one
@@ -150,11 +154,11 @@ struct scout_host_worker {
   std::atomic<bool> in_flight{false};
 
   // Make J the running job.  Caller holds `mu` and notifies cv_job afterwards.
-  void start_locked(const Job& J, uint64_t number) {
+  void start_locked(const Job& J) {
     job = J;
     pairs_left.store(J.pairs, std::memory_order_relaxed);
     in_flight.store(true, std::memory_order_release);
-    t_start[number & 1] = std::chrono::steady_clock::now();
+    t_start = std::chrono::steady_clock::now();
     const uint64_t gen = generation.load(std::memory_order_relaxed) + 1;
     ticket.store((gen & 0xffffffffu) << 32, std::memory_order_release);
     generation.store(gen, std::memory_order_release);
@@ -193,11 +197,11 @@ struct scout_host_worker {
           bool next = false;
           {
             std::lock_guard<std::mutex> lk(mu);
-            t_end[completed & 1] = now;
+            seconds[completed % kTimes] = std::chrono::duration<double>(now - t_start).count();
             ++completed;
             if (has_queued) {  // the job that waited behind this one starts now
               has_queued = false;
-              start_locked(queued, completed);
+              start_locked(queued);
               next = true;
             } else {
               in_flight.store(false, std::memory_order_release);
@@ -222,7 +226,7 @@ static int publish(scout_host_worker* w, const Job& J) {
       w->queued = J;
       w->has_queued = true;
     } else {
-      w->start_locked(J, w->submitted);
+      w->start_locked(J);
       started = true;
     }
     ++w->submitted;
@@ -332,7 +336,7 @@ int scout_host_wait(scout_host_worker* w, double* seconds) {
     for (int i = 0; i < 10; ++i) __builtin_ia32_pause();
   std::unique_lock<std::mutex> lk(w->mu);
   if (!ok) w->cv_done.wait(lk, [&] { return w->completed > mine; });
-  if (seconds != nullptr) *seconds = std::chrono::duration<double>(w->t_end[mine & 1] - w->t_start[mine & 1]).count();
+  if (seconds != nullptr) *seconds = w->seconds[mine % scout_host_worker::kTimes];
   w->waited = mine + 1;
   return 0;
 }

@@ -193,6 +193,31 @@ def test_stage_recall_rejects_a_short_buffer_and_takes_an_empty_plan():
         w.close()
 
 
+def test_every_job_is_reported_with_its_own_time():
+    """A job is accepted whenever none waits behind the running one, however many finished ones have not been reported yet:
+    each keeps its own time until then."""
+    dims = dict(dtype="bf16", B=32, Hq=8, Hkv=2, d=128, S=32, mb=24, k=20)
+    ctx, q, kb, vb, sel, n = _case(seed=31, **dims)
+    full, none = np.full_like(n, 20), np.zeros_like(n)
+    sel = np.tile(np.arange(20, dtype=np.int32), n.shape + (1,))
+    ctx = np.full_like(ctx, 24 * 32)
+    worker = H.HostWorker(1)
+    try:
+        p = H.HostProblem(dims["B"], dims["Hq"], dims["Hkv"], dims["d"], dims["S"], H.BF16, dims["mb"], dims["k"], 0.0)
+        lens = [full, none, none, full, none]
+        for cnt in lens:
+            o = np.empty((dims["B"], dims["Hq"], dims["d"]), np.float32)
+            m, l = np.empty(o.shape[:2], np.float32), np.empty(o.shape[:2], np.float32)
+            worker.submit(p, q, kb, vb, sel, cnt, ctx, o, m, l)
+            while not worker.done():
+                pass
+        sec = [worker.wait() for _ in lens]
+        assert min(sec) > 0.0 and worker.wait() == 0.0
+        assert min(sec[0], sec[3]) > max(sec[1], sec[2], sec[4])   # 1280 blocks against none
+    finally:
+        worker.close()
+
+
 def test_two_jobs_outstanding_are_run_in_order_and_a_third_is_refused():
     """Alg. 1 spawns layer i+1's host job while layer i's may still be running: the worker takes one job
     behind the running one, wait() reports them oldest first, and both give what they give alone."""

@@ -1,6 +1,7 @@
 """Digests that are requested before the sequence's length is known: whatever lies beyond the last block (here NaN patterns and
 infinities) must leave no trace in scores, lists and outputs, for empty, short and full sequences, in every kernel that asks ahead
-(scores of every kind, the one-launch step of short rows) and on both sides of the line in the number of pairs."""
+(scores of every kind, with as many heads as each of its instances takes: 4, 8, 16; the one-launch step of short rows) and on both
+sides of the line in the number of pairs."""
 import pytest
 import torch
 
@@ -12,8 +13,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("kind", ["sum", "mean", "max", "per_head"])
 @pytest.mark.parametrize("Bn,Hkv,mb", [(3, 1, 200), (3, 43, 70), (3, 86, 70)])
-def test_scores_beyond_the_last_block(dtype, d, kind, Bn, Hkv, mb):
-    S, G, tdt = 16, 4, torch.float32 if dtype == "f32" else torch.bfloat16
+@pytest.mark.parametrize("G", [4, 8, 11])
+def test_scores_beyond_the_last_block(dtype, d, kind, Bn, Hkv, mb, G):
+    S, tdt = 16, torch.float32 if dtype == "f32" else torch.bfloat16
     ctx = torch.tensor([0, 5 * S + 3, mb * S], dtype=torch.int32, device="cuda")
     opts = dict(digest_kind=int(kind == "mean"), group_max=int(kind == "max"), per_head=int(kind == "per_head"))
     p = B.make_problem(Bn, G * Hkv, Hkv, d, S, B.F32 if dtype == "f32" else B.BF16, mb, 4, ctx, **opts)
@@ -34,7 +36,7 @@ def test_scores_beyond_the_last_block(dtype, d, kind, Bn, Hkv, mb):
     assert torch.isfinite(got[1][1, :, :6]).all() and torch.isfinite(got[1][2]).all()
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)])
 @pytest.mark.parametrize("Bn,Hkv", [(3, 1), (3, 100)])
 def test_one_launch_step_beyond_the_last_block(dtype, d, Bn, Hkv):
     S, G, mb, k, tdt = 16, 4, 120, 8, torch.float32 if dtype == "f32" else torch.bfloat16

@@ -1,7 +1,7 @@
-"""Head-wise scores in launches of few workgroups and of many (around the sizes at which the instances of an earlier kernel
-changed): the same blocks give the same bits in a launch of a part of the batch at a time and of the whole, and they are the binary64
-scores rounded to binary32 (two summation orders in binary64 differ by less than 2^-40 of the sum of magnitudes, so the
-rounded values by at most one step of 2^-23)."""
+"""Head-wise scores in launches of few workgroups and of many: the same blocks give the same bits in a launch of a part of the batch
+at a time and of the whole, where the first workgroups ask for their digests before they know the sequence's length in the one and
+not in the other (up to 256 pairs, and beyond); and they are the binary64 scores rounded to binary32 (two summation orders in
+binary64 differ by less than 2^-40 of the sum of magnitudes, so the rounded values by at most one step of 2^-23)."""
 import pytest
 import torch
 
@@ -10,11 +10,12 @@ from paper_2603_27138_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,d,line", [("bf16", 128, 1024), ("bf16", 64, 768), ("f32", 64, 1024), ("f32", 128, 1024),
+@pytest.mark.parametrize("dtype,d,line", [("bf16", 128, 256), ("bf16", 64, 256), ("f32", 64, 256), ("f32", 128, 256),
+                                          ("bf16", 128, 1024), ("bf16", 64, 768), ("f32", 64, 1024), ("f32", 128, 1024),
                                           ("bf16", 64, 512), ("f32", 64, 512), ("f32", 128, 512)])
-@pytest.mark.parametrize("G", [3, 8, 11])
+@pytest.mark.parametrize("G", [1, 3, 4, 5, 8, 9, 11, 16])   # up to 4, 8 and 16 heads run in instances of their own
 @pytest.mark.parametrize("per_head", [0, 1])
-def test_both_register_budgets(dtype, d, line, G, per_head):
+def test_few_pairs_and_many(dtype, d, line, G, per_head):
     tdt, nb, S = (torch.bfloat16 if dtype == "bf16" else torch.float32), 19, 16   # one workgroup per pair
     Bn = line + 3
     gen = torch.Generator(device="cuda").manual_seed(7 + G)

@@ -56,116 +56,87 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float x, float y) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){x, y}, bf16x2));
 }
 
-// The host's partial for one output element (mode 2 only); loaded ahead of the point of use so
-// that its latency hides behind the fold.
-struct HostPart {
-  float o, m, l;
+// N consecutive channels of a head.  The arrays may start anywhere that an element of theirs may.
+template <int N>
+struct Channels {
+  typedef __attribute__((ext_vector_type(N))) float f;
+  typedef f f_any __attribute__((aligned(4)));
+  typedef __attribute__((ext_vector_type(N))) uint16_t h;
+  typedef h h_any __attribute__((aligned(2)));
 };
-
-__device__ __forceinline__ HostPart load_host(const Dims& D, const Epilogue& E, int bh, int c) {
-  HostPart hp{0.0f, -INFINITY, 0.0f};
-  if (E.mode == 2 && E.host_o != nullptr) {
-    hp.m = E.host_m[bh];
-    hp.l = E.host_l[bh];
-    hp.o = E.host_o[(size_t)bh * D.d + c];
-  }
-  return hp;
-}
-
-// acc: unnormalised weighted value sum of channel c, l: weight sum, M2: base-2 maximum
-__device__ __forceinline__ void finish(const Dims& D, const Epilogue& E, int bh, int c, float acc,
-                                       float l, float M2, const HostPart& hp) {
-  const float m_nat = M2 * kLn2;  // -inf stays -inf
-  const float o_norm = l > 0.0f ? acc / l : 0.0f;
-  if (E.mode == 1) {
-    E.o[(size_t)bh * D.d + c] = o_norm;
-    if (c == 0) {
-      E.m[bh] = m_nat;
-      E.l[bh] = l;
-    }
-    return;
-  }
-  const float mb = hp.m, lb = hp.l, ob = hp.o;
-  float ms = -INFINITY;
-  if (l > 0.0f) ms = fmaxf(ms, m_nat);
-  if (lb > 0.0f) ms = fmaxf(ms, mb);
-  const float wa = l > 0.0f ? l * expf(m_nat - ms) : 0.0f;
-  const float wb = lb > 0.0f ? lb * expf(mb - ms) : 0.0f;
-  const float ls = wa + wb;
-  float r = 0.0f;
-  if (wa > 0.0f) r += wa * o_norm;
-  if (wb > 0.0f) r += wb * ob;
-  r = ls > 0.0f ? r / ls : 0.0f;
-  if (E.dtype_out == SCOUT_BF16)
-    static_cast<uint16_t*>(E.out)[(size_t)bh * D.d + c] = (uint16_t)f32_to_bf16_bits(r);
-  else
-    static_cast<float*>(E.out)[(size_t)bh * D.d + c] = r;
-  if (E.lse != nullptr && c == 0) E.lse[bh] = ls > 0.0f ? ms + logf(ls) : -INFINITY;
-}
-
-// The same for CH consecutive channels of a head, c on, per thread: the weights of the two partials are made once for them.
-// Two: of four, the divisions are a chain that few threads run; of one, every thread makes weights of its own.
+// Channels per thread in the epilogues of the attention: the weights of the two partials are made once for them.  Two: of four, the
+// divisions are a chain that few threads run; of one, every thread makes weights of its own.
 constexpr int CH = 2;
-typedef __attribute__((ext_vector_type(CH))) float fch;
-// The arrays may start anywhere that an element of theirs may.
-typedef fch fch_any __attribute__((aligned(4)));
-typedef __attribute__((ext_vector_type(CH))) uint16_t hch;
-typedef hch hch_any __attribute__((aligned(2)));
+typedef Channels<CH>::f fch;
 
-struct HostParts {
-  fch o;
+// The host's partial for a thread's channels (mode 2 only); loaded ahead of the point of use so
+// that its latency hides behind the fold.
+template <int N>
+struct HostPart {
+  typename Channels<N>::f o;
   float m, l;
 };
 
-__device__ __forceinline__ HostParts load_hosts(const Dims& D, const Epilogue& E, int bh, int c) {
-  HostParts hp{};
+template <int N>
+__device__ __forceinline__ HostPart<N> load_host(const Dims& D, const Epilogue& E, int bh, int c) {
+  HostPart<N> hp{};
   hp.m = -INFINITY;
   if (E.mode == 2 && E.host_o != nullptr) {
     hp.m = E.host_m[bh];
     hp.l = E.host_l[bh];
-    hp.o = *reinterpret_cast<const fch_any*>(E.host_o + (size_t)bh * D.d + c);
+    hp.o = *reinterpret_cast<const typename Channels<N>::f_any*>(E.host_o + (size_t)bh * D.d + c);
   }
   return hp;
 }
 
-__device__ __forceinline__ void finish_channels(const Dims& D, const Epilogue& E, int bh, int c, fch acc, float l, float M2,
-                                                const HostParts& hp) {
-  const float m_nat = M2 * kLn2;  // -inf stays -inf
-  fch r;
+// Merge of the partial (oa, ma, la) of head bh, channels c on, with the other one: `at` is the place of the channels in `out`.
+template <int N>
+__device__ __forceinline__ void merge_channels(void* out, int dtype_out, float* lse, size_t at, int bh, int c,
+                                               typename Channels<N>::f oa, float ma, float la, const HostPart<N>& other) {
+  const float mb = other.m, lb = other.l;
+  float ms = -INFINITY;
+  if (la > 0.0f) ms = fmaxf(ms, ma);
+  if (lb > 0.0f) ms = fmaxf(ms, mb);
+  const float wa = la > 0.0f ? la * expf(ma - ms) : 0.0f;
+  const float wb = lb > 0.0f ? lb * expf(mb - ms) : 0.0f;
+  const float ls = wa + wb;
+  typename Channels<N>::f r;
 #pragma unroll
-  for (int i = 0; i < CH; ++i) r[i] = l > 0.0f ? acc[i] / l : 0.0f;
+  for (int i = 0; i < N; ++i) {
+    float x = 0.0f;
+    if (wa > 0.0f) x += wa * oa[i];
+    if (wb > 0.0f) x += wb * other.o[i];
+    r[i] = ls > 0.0f ? x / ls : 0.0f;
+  }
+  if (dtype_out == SCOUT_BF16) {
+    typename Channels<N>::h w;
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = (uint16_t)f32_to_bf16_bits(r[i]);
+    *reinterpret_cast<typename Channels<N>::h_any*>(static_cast<uint16_t*>(out) + at) = w;
+  } else {
+    *reinterpret_cast<typename Channels<N>::f_any*>(static_cast<float*>(out) + at) = r;
+  }
+  if (lse != nullptr && c == 0) lse[bh] = ls > 0.0f ? ms + logf(ls) : -INFINITY;
+}
+
+// acc: unnormalised weighted value sums of the channels, l: weight sum, M2: base-2 maximum
+template <int N>
+__device__ __forceinline__ void finish(const Dims& D, const Epilogue& E, int bh, int c, typename Channels<N>::f acc, float l, float M2,
+                                       const HostPart<N>& hp) {
+  const float m_nat = M2 * kLn2;  // -inf stays -inf
+  typename Channels<N>::f r;
+#pragma unroll
+  for (int i = 0; i < N; ++i) r[i] = l > 0.0f ? acc[i] / l : 0.0f;
   const size_t at = (size_t)bh * D.d + c;
   if (E.mode == 1) {
-    *reinterpret_cast<fch_any*>(E.o + at) = r;
+    *reinterpret_cast<typename Channels<N>::f_any*>(E.o + at) = r;
     if (c == 0) {
       E.m[bh] = m_nat;
       E.l[bh] = l;
     }
     return;
   }
-  const float mb = hp.m, lb = hp.l;
-  float ms = -INFINITY;
-  if (l > 0.0f) ms = fmaxf(ms, m_nat);
-  if (lb > 0.0f) ms = fmaxf(ms, mb);
-  const float wa = l > 0.0f ? l * expf(m_nat - ms) : 0.0f;
-  const float wb = lb > 0.0f ? lb * expf(mb - ms) : 0.0f;
-  const float ls = wa + wb;
-#pragma unroll
-  for (int i = 0; i < CH; ++i) {
-    float x = 0.0f;
-    if (wa > 0.0f) x += wa * r[i];
-    if (wb > 0.0f) x += wb * hp.o[i];
-    r[i] = ls > 0.0f ? x / ls : 0.0f;
-  }
-  if (E.dtype_out == SCOUT_BF16) {
-    hch w;
-#pragma unroll
-    for (int i = 0; i < CH; ++i) w[i] = (uint16_t)f32_to_bf16_bits(r[i]);
-    *reinterpret_cast<hch_any*>(static_cast<uint16_t*>(E.out) + at) = w;
-  } else {
-    *reinterpret_cast<fch_any*>(static_cast<float*>(E.out) + at) = r;
-  }
-  if (E.lse != nullptr && c == 0) E.lse[bh] = ls > 0.0f ? ms + logf(ls) : -INFINITY;
+  merge_channels<N>(E.out, E.dtype_out, E.lse, at, bh, c, r, m_nat, l, hp);
 }
 
 // The work of a pair is cut into units of 16 tokens (a block of S tokens is S/16 units; a unit's K
@@ -525,7 +496,7 @@ __device__ __forceinline__ void gather_splits(const Partials& P, const SharedPar
 // meet in LDS.  hp: the host's partial for the thread's first channels.
 template <int DH, int WAVES>
 __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pair, const Partials& P, const Epilogue& E,
-                                            const HostParts& hp, float* smem, int* flag) {
+                                            const HostPart<CH>& hp, float* smem, int* flag) {
   constexpr int ROW = DH + 4, Q = DH / CH;  // Q: threads per head
   constexpr int NT = WAVES * kWave;
   const int G = D.G, wstride = G * ROW + 32, bh0 = b * D.Hq + g * G;
@@ -546,7 +517,7 @@ __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pai
       float M, l;
       fch o;
       gather_splits<DH>(P, R, G, h, c, 0, 1, o, l, M);
-      finish_channels(D, E, bh0 + h, c, o, l, M, item < NT ? hp : load_hosts(D, E, bh0 + h, c));
+      finish<CH>(D, E, bh0 + h, c, o, l, M, item < NT ? hp : load_host<CH>(D, E, bh0 + h, c));
     }
     return;
   }
@@ -578,7 +549,7 @@ __device__ __forceinline__ void fold_splits(const Dims& D, int b, int g, int pai
     for (int i = 0; i < CH; ++i) o[i] += f * x[i];
     l += f * base[G * ROW + 16 + h];
   }
-  finish_channels(D, E, bh0 + h, c, o, l, M, hp);
+  finish<CH>(D, E, bh0 + h, c, o, l, M, hp);
 }
 
 // The attention of one workgroup: its share (split) of the pair's list, folded over the waves
@@ -718,7 +689,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
   // now and used after the fold.
   constexpr int Q = DH / CH, NT = WAVES * kWave;
   const int bh0 = b * D.Hq + g * G;
-  const HostParts hp = load_hosts(D, E, bh0 + ((int)threadIdx.x < G * Q ? threadIdx.x / Q : 0), (threadIdx.x % Q) * CH);
+  const HostPart<CH> hp = load_host<CH>(D, E, bh0 + ((int)threadIdx.x < G * Q ? threadIdx.x / Q : 0), (threadIdx.x % Q) * CH);
 
   // fold the waves of the workgroup through LDS
   float* wo = smem + (size_t)wave * wstride;
@@ -769,7 +740,7 @@ __device__ __forceinline__ void attend_pair(const Dims& D, int b, int g, int spl
         P.l[pbase * G + h] = l;
       }
     } else {
-      finish_channels(D, E, bh0 + h, c, o, l, M, item < NT ? hp : load_hosts(D, E, bh0 + h, c));
+      finish<CH>(D, E, bh0 + h, c, o, l, M, item < NT ? hp : load_host<CH>(D, E, bh0 + h, c));
     }
   }
   if constexpr (FOLD) fold_splits<DH, WAVES>(D, b, g, pair, P, E, hp, smem, flag);
@@ -1005,31 +976,28 @@ __global__ __launch_bounds__(8 * kWave) void select_attend_kernel(
   uint32_t touched_k = 0, touched_v = 0;
   int k_eff;
 
-  {
-    const int sw = wave;
-    float sc[KPL];
-    int slot[KPL];
-    // In the order of use, because a wait for one load is a wait for those before it: what is selected from, the hint, the queries
-    // (which the attention needs).  With the queries and the hint in front: 16 sequences of 32k tokens 131.7 us a step instead of 130.2, 8 sequences
-    // 101.8 instead of 99.7.
-    load_scores<WAVES, KPL>(D, scores, table, pair, sw, lane, sc, slot);
-    __builtin_amdgcn_sched_barrier(0);
-    const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
-    __builtin_amdgcn_sched_barrier(0);
-    load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
-    __builtin_amdgcn_sched_barrier(0);
-    Selector<WAVES, KPL> S{l_x, 0, sw};
-    S.prepare();
-    int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;
-    nb = nb < D.max_blocks ? nb : D.max_blocks;
-    k_eff = D.k < nb ? D.k : nb;
-    uint32_t key[KPL];
-    mask_keys<WAVES, KPL>(nb, sw, lane, sc, key, slot);
-    __builtin_amdgcn_sched_barrier(0);
-    touch_hint<DT, DH, WAVES, STRIDE>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
-    __builtin_amdgcn_sched_barrier(0);
-    lists.fill(S, key, slot, k_eff);
-  }
+  float sc[KPL];
+  int slot[KPL];
+  // In the order of use, because a wait for one load is a wait for those before it: what is selected from, the hint, the queries
+  // (which the attention needs).  With the queries and the hint in front: 16 sequences of 32k tokens 131.7 us a step instead of 130.2, 8 sequences
+  // 101.8 instead of 99.7.
+  load_scores<WAVES, KPL>(D, scores, table, pair, wave, lane, sc, slot);
+  __builtin_amdgcn_sched_barrier(0);
+  const Hint hint = load_hint(D, pair, lane, slot_gpu, n_gpu);
+  __builtin_amdgcn_sched_barrier(0);
+  load_q<DT, DH>(qreg, D, q, b, g, lane & 15, lane >> 4);
+  __builtin_amdgcn_sched_barrier(0);
+  Selector<WAVES, KPL> S{l_x, 0, wave};
+  S.prepare();
+  int nb = (ctx < 0 ? 0 : ctx + D.S - 1) >> D.s_shift;
+  nb = nb < D.max_blocks ? nb : D.max_blocks;
+  k_eff = D.k < nb ? D.k : nb;
+  uint32_t key[KPL];
+  mask_keys<WAVES, KPL>(nb, wave, lane, sc, key, slot);
+  __builtin_amdgcn_sched_barrier(0);
+  touch_hint<DT, DH, WAVES, STRIDE>(D, hint, P, split * WAVES + wave, lane, k_pool, v_pool, n_slots, touched_k, touched_v);
+  __builtin_amdgcn_sched_barrier(0);
+  lists.fill(S, key, slot, k_eff);
   __syncthreads();
   auto write_lists = [&]() __attribute__((always_inline)) {
     if (split == 0) lists.store(D, pair, k_eff, WAVES * kWave, sel_all, sel_gpu, slot_gpu, n_gpu, sel_host, n_host);
@@ -1293,7 +1261,7 @@ __global__ void combine_kernel(Dims D, Partials P, Epilogue E) {
   const int pair = grid_pair(), bh = pair * D.G + h;
   const int c = threadIdx.x;
   const size_t p0 = (size_t)pair * P.nsplit;
-  const HostPart hp = load_host(D, E, bh, c);
+  const HostPart<1> hp = load_host<1>(D, E, bh, c);
   // one pass with a running maximum, GROUP splits at a time: every load of a group is independent
   // of the others, so a group costs one trip to memory (GROUP covers the split count where it can)
   float M = -INFINITY, acc = 0.0f, l = 0.0f;
@@ -1324,7 +1292,7 @@ __global__ void combine_kernel(Dims D, Partials P, Epilogue E) {
     }
     M = Mn;
   }
-  finish(D, E, bh, c, acc, l, M, hp);
+  finish<1>(D, E, bh, c, acc, l, M, hp);
 }
 
 // Stand-alone merge of two partials given in natural-log units (Alg. 1 Merge).
@@ -1334,28 +1302,15 @@ __global__ void merge_kernel(Dims D, const float* __restrict__ o_a, const float*
                              const float* __restrict__ m_b, const float* __restrict__ l_b,
                              void* __restrict__ out, float* __restrict__ lse) {
   const int bh = blockIdx.x, c = threadIdx.x;
-  const float ma = m_a[bh], la = l_a[bh];
-  float mb = -INFINITY, lb = 0.0f, ob = 0.0f;
+  const size_t at = (size_t)bh * D.d + c;
+  HostPart<1> b{};
+  b.m = -INFINITY;
   if (o_b != nullptr) {
-    mb = m_b[bh];
-    lb = l_b[bh];
-    ob = o_b[(size_t)bh * D.d + c];
+    b.m = m_b[bh];
+    b.l = l_b[bh];
+    b.o = o_b[at];
   }
-  float ms = -INFINITY;
-  if (la > 0.0f) ms = fmaxf(ms, ma);
-  if (lb > 0.0f) ms = fmaxf(ms, mb);
-  const float wa = la > 0.0f ? la * expf(ma - ms) : 0.0f;
-  const float wb = lb > 0.0f ? lb * expf(mb - ms) : 0.0f;
-  const float ls = wa + wb;
-  float r = 0.0f;
-  if (wa > 0.0f) r += wa * o_a[(size_t)bh * D.d + c];
-  if (wb > 0.0f) r += wb * ob;
-  r = ls > 0.0f ? r / ls : 0.0f;
-  if (DT_OUT == SCOUT_BF16)
-    static_cast<uint16_t*>(out)[(size_t)bh * D.d + c] = (uint16_t)f32_to_bf16_bits(r);
-  else
-    static_cast<float*>(out)[(size_t)bh * D.d + c] = r;
-  if (lse != nullptr && c == 0) lse[bh] = ls > 0.0f ? ms + logf(ls) : -INFINITY;
+  merge_channels<1>(out, DT_OUT, lse, at, bh, c, o_a[at], m_a[bh], l_a[bh], b);
 }
 
 // ------------------------------------------------------------ host launchers
@@ -1455,8 +1410,10 @@ int launch_select_attend(const Dims& D, int dtype, const void* q, const float* s
   // All eight waves share the keys: measured faster than one wave selecting alone while seven wait
   // (46.9 vs 44.1 us per step at 1024 blocks per pair), a lone wave issues too slowly.  Eight more waves that leave after the
   // selection cost more than they bring (32 pairs x 8 of 4096 blocks: 30.0 us a step instead of 29.3).  Sizes in between
-  // because a key costs whether it is there or not: a growing sequence has one block more than a power of two (64 pairs x 4
-  // of 1025: 26.9 instead of 27.0 us a step, d = 64 21.3 instead of 21.6; 256 pairs of 2049: 64.2 instead of 64.9).
+  // because a key costs whether it is there or not, and a growing sequence has one block more than a power of two.  A step of groups
+  // of four, us, without the sizes in between and with them: 3 keys, 64 pairs of 1025 blocks 18.5 and 18.3, of 1500 20.5 and 20.1; 6 keys, 8
+  // of 2500 14.6 and 14.1, 64 of 2500 26.6 and 26.0; 12 keys, 8 of 5000 17.9 and 16.2, 32 of 4097 26.5 and 25.4, 64 of 6100 45.9 and 44.9; 192 pairs
+  // of 1500, one workgroup each, 34.9 and 35.1.
   const int per_lane = (D.max_blocks + 8 * kWave - 1) / (8 * kWave);
 #define SCOUT_SA_TYPE(DT, DH)                      \
   do {                                             \

@@ -187,7 +187,6 @@ int launch_topk(const Dims& D, const float* scores, const int32_t* table, int32_
 
 int launch_recall(const Dims& D, const float* scores, int32_t* table, int32_t* recall_blk,
                   int32_t* recall_slot, int32_t* evict_blk, int32_t* n_recall, hipStream_t st) {
-  if (D.k > kMaxK) return SCOUT_EUNSUPPORTED;
   SCOUT_TOPK_DISPATCH(SCOUT_RECALL, D, scores, table, recall_blk, recall_slot, evict_blk, n_recall);
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }

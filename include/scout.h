@@ -186,10 +186,11 @@ int select_topk(const scout_problem* p, const float* scores, const int32_t* bloc
  * the same lists, and what the host's worker needs of them in host memory
  * (pinned, GPU-addressable) by the time the call's work on the stream is done:
  * no copies behind the selection.
- *   job_sel  i32 [B][Hkv][k]   out: sel_host
- *   job_n    i32 [B][Hkv]      out: n_host
+ *   job_sel  i32 [B][Hkv][k]   out: sel_host ([B][Hq][k] with per_head, as the lists)
+ *   job_n    i32 [B][Hkv]      out: n_host ([B][Hq] with per_head)
  *   job_q    e   [B][Hq][d]    out: q; 16-byte aligned
- * Everything else as in score_blocks and select_topk.
+ * They are written by the GPU: they have to stay allocated until the call's work on
+ * the stream is done.  Everything else as in score_blocks and select_topk.
  */
 int scout_select_ahead(const scout_problem* p, const void* q, const void* digest, const int32_t* block_table,
                        float* scores, int32_t* sel_all, int32_t* sel_gpu, int32_t* slot_gpu, int32_t* n_gpu,
@@ -269,7 +270,8 @@ int scout_attn_partials(const scout_problem* p, const void* q, const void* k_poo
  * merging in a further launch.  host_* may be all NULL; lse may be NULL.
  *   host_o f32 [B][Hq][d], host_m, host_l f32 [B][Hq];  out e [B][Hq][d];  lse f32 [B][Hq]
  * host_*: device memory, or pinned host memory, which the kernel then reads over
- * the link itself.
+ * the link itself: it has to stay allocated until the call's work on the stream is
+ * done.
  * The attention mode must not be changed between the two calls.
  */
 int scout_attn_finish(const scout_problem* p, const float* host_o, const float* host_m,

@@ -271,7 +271,8 @@ constexpr int kScoreWaves = 4;      // waves per workgroup
 //
 // NH: query rows that a thread asks for, the group's and, up to 4, 8 or 16, its last one again: narrow loads in front of the
 // digests'.  Sixteen for whatever group: 8 sequences x 8 heads of 64 channels, groups of four, 79.4 us a step instead of 78.5, one sequence
-// 64.7 and 64.25; groups of eight 0.1 %.
+// 64.7 and 64.25.  The launch alone, us, sixteen rows and eight: groups of five, bf16, d = 64, 8 pairs x 1024 blocks 3.09 and 2.98,
+// 64 x 1024 3.87 and 3.67, d = 128 5.15 and 4.88; groups of eight 3.90 and 3.71, 5.40 and 5.20, fp32, d = 128 11.89 and 11.88.
 template <int DT, int DH, bool MEAN, int NH>
 __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
     Dims D, const void* q, const void* digest, float* scores, uint32_t* arrived, int ahead) {
@@ -367,8 +368,11 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void score_kernel(
 //  * the coefficients are made once per workgroup, as binary64 in LDS, in the order of use.
 // A wave takes 16 entries.  Bound by the matrix cores behind the head of the stream: 64 pairs x 1024 blocks, bf16, d = 128,
 // eight heads: the multiply-adds take 4.0 us at the rate of the 4x4x4 (7.9 ns per instruction and SIMD; 16x16x4: 28 ns for
-// four times the work), the launch 9.5 (11.4 on the vector ALU; 7.2 with the heads summed); 16 heads 13.1 (19.1), 4 heads
-// 8.0 (8.7); 8 pairs x 600 blocks 4.1 (6.3); 128 x 1024, 16 heads, d = 64 12.7 (18.5), fp32, d = 128 27.1 (38.6).  32 entries per wave, which
+// four times the work).  The launch, us, digests from memory (on the vector ALU in brackets): 10.8 (13.1); 12 heads, through 16x16x4
+// with four of its rows repeated, 14.1 (17.4), 4 heads 9.4 (10.2); 8 pairs x 600 blocks 4.4 (6.4), 12 heads 5.4 (8.8); 256 x 1024,
+// 12 heads 48.3 (55.0); d = 64, 12 heads 8.6 (10.5), 4 heads 6.0 (6.4); fp32, d = 128, 12 heads 16.8 (21.2), 4 heads 14.7 (15.4); fp32, d = 64,
+// 4 heads 8.3 (9.1).  Only where up to four heads find the digests in the caches, as a model of one or two layers may, the vector ALU was
+// faster: bf16, d = 128, 64 x 1024 7.9 (7.5), fp32, d = 64 6.7 (5.4), fp32, d = 128, 8 x 600 4.3 (4.0).  32 entries per wave, which
 // halves the reads of coefficients, lengthen the chain behind a wave's last load: 10.6 at 64 pairs, 6.2 at 8.
 //
 // ROWS: every head's estimate goes to a row of its own, scores[B][Hq][max_blocks] (a selection per query head:
@@ -564,10 +568,10 @@ int launch_digest(const Dims& D, int dtype, const void* k_blocks, void* digest, 
   return hipGetLastError() == hipSuccess ? SCOUT_OK : SCOUT_EHIP;
 }
 
-// Workgroups of each row that ask for their digests before they know the row's length: 128 in all (4 MiB, what memory
-// delivers in the time of that trip), so that rows that are much shorter than max_blocks cost no more than that; with more pairs one
-// of each row, none beyond 256 pairs, whose launches the trip is a small part of.  Steps of four layers: 16 sequences x 8 heads x 1024 blocks
-// 135.9 -> 134.5 us, 8 x 8 104.5 -> 103.4, one sequence 65.7 -> 64.8, 4 x 8 x 4096 111.3 -> 110.5; 256 ragged pairs (two layers) 125.6 -> 125.2.
+// Workgroups of each row that ask for their digests before they know the row's length: 128 in all, rounded up to whole ones per row,
+// so that at most 256 do (254 of 127 pairs, one per row of 129 to 256 pairs), of 32 KiB each, 64 KiB in score_heads_kernel with fp32, d = 128:
+// rows that are much shorter than max_blocks read 8 (16) MiB for nothing at the most.  None beyond 256 pairs, whose launches the trip
+// is a small part of.  Steps of four layers: 16 sequences x 8 heads x 1024 blocks 135.9 -> 134.5 us, 8 x 8 104.5 -> 103.4, one sequence 65.7 -> 64.8, 4 x 8 x 4096 111.3 -> 110.5; 256 ragged pairs (two layers) 125.6 -> 125.2.
 static int ahead_groups(const Dims& D) {
   const int pairs = D.B * D.Hkv;
   return pairs <= 256 ? (128 + pairs - 1) / pairs : 0;
